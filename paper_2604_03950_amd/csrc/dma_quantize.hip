@@ -143,34 +143,86 @@ block_amax_kernel(float* __restrict__ amax, int64_t S, int64_t block_rows, int64
     for (int64_t r = r0 + threadIdx.x; r < r1; r += 64) p[r] = a;
 }
 
-// Per-tensor maximum in three steps: block maxima over runs of TENSOR_RUN rows (block_amax_kernel), one workgroup that
-// reduces the first row of every run into amax[0], and a grid that copies amax[0] to every row.
-constexpr int64_t TENSOR_RUN = 1024;
-__global__ void __launch_bounds__(1024)
-tensor_reduce_kernel(float* __restrict__ amax, int64_t rows)
+// Maximum over the 256 threads of a workgroup, returned to all of them.
+DMA_DEV float workgroup_max(float a)
 {
-    __shared__ float part[16];
-    float a = 0.f;
-    for (int64_t r = (int64_t)threadIdx.x * TENSOR_RUN; r < rows; r += 1024 * TENSOR_RUN) a = fmaxf(a, amax[r]);
+    __shared__ float part[QUANT_THREADS / 64];
     a = wave_max(a);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        a = part[0];
+    a = part[0];
 #pragma unroll
-        for (int w = 1; w < 16; ++w) a = fmaxf(a, part[w]);
-        amax[0] = a;
+    for (int w = 1; w < QUANT_THREADS / 64; ++w) a = fmaxf(a, part[w]);
+    return a;
+}
+
+// Maximum magnitude that the thread sees of n contiguous 16-byte chunks when `stride` threads share them: four loads in
+// flight per thread.
+DMA_DEV float strided_amax(const v4i* __restrict__ x, int64_t first, int64_t n, int64_t stride)
+{
+    float a = 0.f;
+    for (int64_t i = first; i < n; i += QUANT_UNROLL * stride) {
+        v4i w[QUANT_UNROLL];
+#pragma unroll
+        for (int u = 0; u < QUANT_UNROLL; ++u) w[u] = (i + u * stride < n) ? x[i + u * stride] : v4i{0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < QUANT_UNROLL; ++u) {
+            float v[8];
+            unpack8<false>(w[u], 1.f, v);
+            a = fmaxf(a, amax8(v));
+        }
     }
+    return a;
+}
+
+// Per-block maximum in one pass: a workgroup reads the rows of its block and writes their maximum to each of them.
+// Taken for blocks of FUSED_MIN .. FUSED_MAX rows: below, most of the threads would have nothing to read; above, few
+// workgroups would read long runs one after the other.
+constexpr int64_t FUSED_MIN = 32, FUSED_MAX = 1024;
+__global__ void __launch_bounds__(QUANT_THREADS)
+block_amax_fused_kernel(const v4i* __restrict__ x, int64_t S, int lanes_per_row, int64_t block_rows, int64_t blocks_per_matrix,
+                        float c, int prescale, float* __restrict__ amax)
+{
+    const int64_t mtx = blockIdx.x / blocks_per_matrix, blk = blockIdx.x % blocks_per_matrix;
+    const int64_t r0 = blk * block_rows, r1 = (r0 + block_rows < S) ? r0 + block_rows : S;
+    const float a = workgroup_max(strided_amax(x + (mtx * S + r0) * lanes_per_row, threadIdx.x, (r1 - r0) * lanes_per_row, QUANT_THREADS));
+    float* p = amax + mtx * S;
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += QUANT_THREADS) p[r] = prescale ? __fmul_rn(a, c) : a;
+}
+
+// Per-tensor maximum in two launches, the first bound by the read of x, the second by its launch: up to TENSOR_PARTS
+// workgroups leave the maxima of their shares in amax[0 .. parts), then every workgroup of the second grid reduces
+// those and writes the result to its rows.  Workgroups of the second grid overwrite the partial maxima while others
+// read them, which does no harm: a cell holds its partial maximum or the maximum of all, and the maximum over any such
+// mixture is the same number.  (Four launches -- row maxima, runs of 1024 rows, one workgroup over the runs, a copy to
+// every row -- stood here before: see the measurement at launch_group_amax.)
+constexpr int64_t TENSOR_PARTS = 1024;
+__global__ void __launch_bounds__(QUANT_THREADS)
+tensor_parts_kernel(const v4i* __restrict__ x, int64_t chunks, float c, int prescale, float* __restrict__ amax)
+{
+    const int64_t first = (int64_t)blockIdx.x * QUANT_THREADS + threadIdx.x;
+    const float a = workgroup_max(strided_amax(x, first, chunks, (int64_t)gridDim.x * QUANT_THREADS));
+    if (threadIdx.x == 0) amax[blockIdx.x] = prescale ? __fmul_rn(a, c) : a;
 }
 __global__ void __launch_bounds__(QUANT_THREADS)
-broadcast_first_kernel(float* __restrict__ amax, int64_t rows)
+tensor_spread_kernel(float* amax, int64_t rows, int parts)
 {
-    const int64_t r = (int64_t)blockIdx.x * QUANT_THREADS + threadIdx.x;
-    const float a = amax[0];              // row 0 is rewritten with the value it already holds
-    if (r < rows) amax[r] = a;
+    float a = 0.f;
+    for (int i = threadIdx.x; i < parts; i += QUANT_THREADS)
+        a = fmaxf(a, __hip_atomic_load(amax + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    a = workgroup_max(a);
+    const int64_t base = (int64_t)blockIdx.x * QUANT_UNROLL * QUANT_THREADS + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < QUANT_UNROLL; ++u) {
+        const int64_t r = base + u * QUANT_THREADS;
+        if (r < rows) __hip_atomic_store(amax + r, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // granularity: 1 = the row, 2 = blocks of block_rows rows of each [S, D] matrix, 3 = everything.  D is 64 or 128.
+// Bound by launches at the sizes of one prefill: for 32 heads of 4096 x 128, per tensor 18.8 -> 12.7 us and per block of
+// 128 rows 12.8 -> 10.5 us against one launch per step of the reduction (call to call, the host's part included); the
+// maxima of Q and K and the forward of 32 / 8 heads at S = 4096 together 211.9 -> 199.1 us.
 int launch_group_amax(const void* x, int64_t n_mat, int64_t S, int D, int is_query, int granularity, int64_t block_rows,
                       float* amax, hipStream_t stream)
 {
@@ -180,19 +232,25 @@ int launch_group_amax(const void* x, int64_t n_mat, int64_t S, int D, int is_que
     if (blocks > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED_;
     const float c = (float)(1.4426950408889634074 / sqrt((double)D));
     // every size check comes before the first launch: on error nothing has been enqueued
-    const int64_t bpm = granularity == 2 ? (S + block_rows - 1) / block_rows : 0;
-    const int64_t runs = (rows + TENSOR_RUN - 1) / TENSOR_RUN;
+    const int64_t bpm = granularity == 2 ? (S - 1) / block_rows + 1 : 0;
     if (D != 128 && D != 64) return DMA_ERR_UNSUPPORTED_;
-    if ((granularity == 2 && n_mat * bpm > 0x7fffffffLL) || (granularity == 3 && runs > 0x7fffffffLL)) return DMA_ERR_UNSUPPORTED_;
+    if (granularity == 2 && n_mat * bpm > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED_;
+    if (granularity == 3) {
+        // a share is at least a workgroup's worth of unrolled loads, so there are never more parts than rows
+        const int64_t shares = (blocks + QUANT_UNROLL - 1) / QUANT_UNROLL;
+        const int parts = (int)(shares < TENSOR_PARTS ? shares : TENSOR_PARTS);
+        const int64_t spread = (rows + QUANT_UNROLL * QUANT_THREADS - 1) / (QUANT_UNROLL * QUANT_THREADS);
+        const int rc = launch(tensor_parts_kernel, dim3((unsigned)parts), dim3(QUANT_THREADS), stream, (const v4i*)x, chunks, c, is_query, amax);
+        if (rc != DMA_OK_) return rc;
+        return launch(tensor_spread_kernel, dim3((unsigned)spread), dim3(QUANT_THREADS), stream, amax, rows, parts);
+    }
+    if (granularity == 2 && block_rows >= FUSED_MIN && block_rows <= FUSED_MAX)
+        return launch(block_amax_fused_kernel, dim3((unsigned)(n_mat * bpm)), dim3(QUANT_THREADS), stream, (const v4i*)x, S, D / 8,
+                      block_rows, bpm, c, is_query, amax);
     int rc = D == 128 ? launch(row_amax_kernel<16>, dim3((unsigned)blocks), dim3(QUANT_THREADS), stream, (const v4i*)x, rows, c, is_query, amax)
                       : launch(row_amax_kernel<8>, dim3((unsigned)blocks), dim3(QUANT_THREADS), stream, (const v4i*)x, rows, c, is_query, amax);
     if (rc == DMA_OK_ && granularity == 2)
         rc = launch(block_amax_kernel, dim3((unsigned)(n_mat * bpm)), dim3(64), stream, amax, S, block_rows, bpm);
-    if (granularity == 3) {
-        if (rc == DMA_OK_) rc = launch(block_amax_kernel, dim3((unsigned)runs), dim3(64), stream, amax, rows, TENSOR_RUN, runs);
-        if (rc == DMA_OK_) rc = launch(tensor_reduce_kernel, dim3(1), dim3(1024), stream, amax, rows);
-        if (rc == DMA_OK_) rc = launch(broadcast_first_kernel, dim3((unsigned)((rows + QUANT_THREADS - 1) / QUANT_THREADS)), dim3(QUANT_THREADS), stream, amax, rows);
-    }
     return rc;
 }
 

@@ -531,6 +531,30 @@ def test_group_amax_bit_exact(dma, oracle, D, S):
             assert np.array_equal(got.cpu().numpy(), want), (D, S, is_query, name, br)
 
 
+@pytest.mark.parametrize("n_mat,S,D,block_rows", [
+    (1, 1, 64, 0), (1, 63, 128, 0), (1, 64, 128, 0), (3, 65, 128, 0),       # one share, its last row, two shares
+    (1, 65536, 128, 0), (5, 13109, 128, 0), (2, 65537, 64, 0),              # as many shares as there are, and past it
+    (2, 100, 128, 31), (2, 100, 128, 32), (3, 1025, 64, 1024), (2, 1026, 128, 1025), (1, 7, 64, 64),
+])
+@pytest.mark.parametrize("is_query", [False, True])
+def test_group_amax_routes_bit_exact(dma, n_mat, S, D, block_rows, is_query):
+    """Both routes to a block's maximum and the two-launch tensor maximum, at the edges of their ranges and with the
+    maximum in the last row.  A maximum has one right answer; the pre-scale is one binary32 multiply of it."""
+    import torch
+    gen = torch.Generator().manual_seed(S)
+    x = torch.randn((n_mat, S, D), generator=gen).to(torch.bfloat16)
+    x[-1, -1, -1] = -40.0
+    step = block_rows or S
+    a = x.float().abs().amax(-1)
+    want = torch.stack([torch.cat([a[m, r:r + step].max().expand(min(step, S - r)) for r in range(0, S, step)]) for m in range(n_mat)])
+    if not block_rows:
+        want = a.max().expand(n_mat, S)
+    if is_query:
+        want = want * torch.tensor(1.4426950408889634074 / D ** 0.5, dtype=torch.float32)
+    got = dma.dma_mx_group_amax(x.cuda(), is_query, dma.GRAN_BLOCK if block_rows else dma.GRAN_TENSOR, block_rows)
+    assert torch.equal(got.cpu(), want)
+
+
 @pytest.mark.parametrize("gran", ["block", "tensor"])
 @pytest.mark.parametrize("cfg,S,causal,sink", [("tiny", 256, True, 0), ("tiny", 200, False, 0), ("prefill_8k", 512, True, 0),
                                               ("prefill_8k", 640, True, 1), ("prefill_8k", 300, False, 0)])
