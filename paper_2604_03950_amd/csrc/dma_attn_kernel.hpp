@@ -926,8 +926,9 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int qrow_in_tile = (wave % C::WPT) * 32;
         const int qrow = it * BT + qrow_in_tile;
         // this item visits key tiles [0, nt).  A filled-up tile of the last group (it >= N) has no rows: it asks for no
-        // key tile of its own and its waves only help with the staging, so that the other wave of the SIMD has it to
-        // itself in what is the longest item of the head (S = 613, 32 / 8 heads, five tiles: 25.8 -> 21.6 us).
+        // key tile of its own, and on band tiles its waves only help with the staging: one step less in the longest item
+        // of the head (S = 613, 32 / 8 heads, five tiles: 25.8 -> 22.1 us).  On main tiles they compute zeros: a branch
+        // there cost the ragged sizes 5 % (S = 2500: 71.4 us with it, 69.2 without).
         const int nt = causal ? min(last + 1, N) : N;
         const bool exists = !GENERAL || it < N;
         auto tile_hi = [&](int qt, int jt) __attribute__((always_inline)) {             // does query tile qt compute key tile jt in the high format?
@@ -1056,14 +1057,6 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 load_v(vreg, vhead, (jt + 2) * BT, S, tid);
             } else {
                 if (jt + 1 < nt) stage_next(jt + 1, buf ^ 1);
-                if (!exists) {
-                    if (jt + 2 < nt) {
-                        load_k(jt + 2);
-                        load_v(vreg, vhead, (jt + 2) * BT, S, tid);
-                    }
-                    __syncthreads();
-                    return;
-                }
                 score_part<C, LO, false, PT, PVMX>(qr_lo, qs_lo, klo_at(buf), kslo_at(buf), lofs.score_k, lofs.score_s, kts_at(buf), q_sq, false, BT, qrow_in_tile, lane, c, m, mfloor, l, o, pb,
                                          [&]() __attribute__((always_inline)) { if (!PT && jt + 2 < nt) load_k(jt + 2); });
                 // With the Step-2 scale the softmax part holds the key scales as well: K requested in the middle of it
