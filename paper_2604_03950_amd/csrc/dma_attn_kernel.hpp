@@ -888,7 +888,8 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     // the K/V stream of a unit stays in one L2.
     // Logical tiles per sequence; the last one may be partial.  When N is not a multiple of TPW (GENERAL instances only)
     // the last group is filled up with query tiles that lie wholly past the end of the sequence: their rows load as
-    // zeros, their waves multiply nothing, and their stores are dropped by the bounds of the output's buffer resource.
+    // zeros, their waves compute zeros on main tiles and nothing on band tiles, and their stores are dropped by the bounds
+    // of the output's buffer resource.
     const int N = (S + BT - 1) / BT;
     const int NG = (N + TPW - 1) / TPW;  // tile groups
     const int group = Hq / Hkv;
@@ -926,11 +927,14 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int qrow_in_tile = (wave % C::WPT) * 32;
         const int qrow = it * BT + qrow_in_tile;
         // this item visits key tiles [0, nt).  A filled-up tile of the last group (it >= N) has no rows: it asks for no
-        // key tile of its own, and on band tiles its waves only help with the staging: one step less in the longest item
-        // of the head (S = 613, 32 / 8 heads, five tiles: 25.8 -> 22.1 us).  On main tiles they compute zeros: a branch
-        // there cost the ragged sizes 5 % (S = 2500: 71.4 us with it, 69.2 without).
+        // key tile of its own, and its waves compute no band tile (jlast: the last key tile the wave computes as one), so the
+        // other wave of the SIMD has it to itself there.  S = 613, 32 / 8 heads, five tiles: 25.85 us with the step and
+        // the band tiles, 23.04 without the step, 21.79 without both; S = 300: 20.23, 17.13 and 15.74.  One bound per wave
+        // and no test in the main step, because the sizes with an even number of tiles pay for what lives through it (a
+        // flag of its own and a second test in `needs`: 5 VGPRs and up to 36 spilled SGPRs more; S = 2500: 67.9 us before
+        // there was any of this, 68.3 with the flag, 68.05 with the bound).
         const int nt = causal ? min(last + 1, N) : N;
-        const bool exists = !GENERAL || it < N;
+        const int jlast = (GENERAL && TPW > 1 && it >= N) ? -1 : causal ? it : N;
         auto tile_hi = [&](int qt, int jt) __attribute__((always_inline)) {             // does query tile qt compute key tile jt in the high format?
             if (!TWO) return false;
             if (jt < sink) return true;
@@ -961,7 +965,10 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             if constexpr (TWO) {
 #pragma unroll
                 for (int w = 0; w < TPW; ++w) {
-                    if ((causal && jt > it0 + w) || (GENERAL && it0 + w >= N)) continue;
+                    // a filled-up tile needs nothing.  Tested only with the Step-2 scale, where staging a format for its sake
+                    // is dear (S = 613, 32 / 8 heads, per token: 25.5 us with the test, 26.2 without); without the scale S = 613
+                    // takes 21.8 us as it is, 22.0 with this test and a flag for it
+                    if ((causal && jt > it0 + w) || (PT && it0 + w >= N)) continue;
                     const bool h = tile_hi(it0 + w, jt);
                     any_hi |= h;
                     any_lo |= !h;
@@ -1070,7 +1077,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         };
         auto band_step = [&](int jt) __attribute__((always_inline)) {
             const int buf = jt & 1;
-            const bool active = exists && (!causal || jt <= it);
+            const bool active = jt <= jlast;
             const bool diagonal = causal && jt == it;
             // keys of this tile that exist (a partial last tile; under the causal mask the diagonal rule covers it)
             const int key_limit = causal ? BT : min(BT, S - jt * BT);

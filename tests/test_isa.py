@@ -43,3 +43,32 @@ def test_fp4_convert_groups_read_four_registers(tmp_path, lo, hi):
             del open_groups[dst]
             n_groups += 1
     assert not open_groups and n_groups == len(lines) // 4
+
+
+def test_general_instances_keep_their_registers(tmp_path):
+    """What the GENERAL instances of the default pair hold in registers.  A value that lives through the tile loops for the
+    sake of a rare shape (the filled-up tile of an odd number of tiles) is paid for by every ragged length: in spilled
+    scalar registers, which are moved to and from vector lanes, and in vector registers.  Each limit lies between the
+    count with one bound per wave (247 VGPRs; 31, 61, 116, 15, 28 spilled SGPRs) and with a flag and a second test
+    beside it (252; 36, 93, 143, 30, 35)."""
+    out = tmp_path / "inst_2_3.s"
+    flags = [f for f in B.HIPCC_FLAGS if f != "-fPIC"]
+    subprocess.run(["hipcc"] + flags + ["-DDMA_LO=2", "-DDMA_HI=3", "-S", "--cuda-device-only", "-o", str(out),
+                                        os.path.join(B.CSRC, "dma_attn_inst.hip")],
+                   check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+    counts = {}
+    for block in re.split(r"(?=- \.agpr_count)", open(out).read()):
+        name = re.search(r"\.name:\s+(_ZN3dma19dma_attn_fwd_kernel\S+)", block)
+        if name:
+            key = tuple(int(n) for n in re.findall(r"L[ib](\d+)E", name.group(1)))
+            counts[key] = {f: int(re.search(rf"\.{f}:\s+(\d+)", block).group(1))
+                           for f in ("vgpr_count", "vgpr_spill_count", "sgpr_spill_count")}
+    # (D, tile, tiles per workgroup, low, high, general, per-token scale, MX-format P V): most spilled SGPRs
+    limits = {(128, 128, 2, 2, 3, 1, 0, 0): 33, (128, 128, 2, 2, 3, 1, 0, 1): 75, (128, 128, 1, 2, 3, 1, 0, 0): 125,
+              (64, 64, 2, 2, 3, 1, 0, 0): 22, (64, 64, 1, 2, 3, 1, 0, 0): 31}
+    for key, limit in limits.items():
+        assert counts[key]["sgpr_spill_count"] <= limit, (key, counts[key])
+    assert counts[(128, 128, 2, 2, 3, 1, 0, 0)]["vgpr_count"] <= 250
+    # only the MX-format P V spills vector registers
+    for key, c in counts.items():
+        assert key[7] == 1 or c["vgpr_spill_count"] == 0, (key, c)
