@@ -990,11 +990,14 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         float kam[C::CPT];                               // group maxima of the key rows in kreg (when given)
 #pragma unroll
         for (int r = 0; r < C::CPT; ++r) kam[r] = 0.f;
-        auto load_k = [&](int jt) __attribute__((always_inline)) {                   // K tile jt (and its group maxima) into the registers
-            load_tile<C, GENERAL>(kreg, khead, jt * BT, S, tid);
+        auto load_kam = [&](int jt) __attribute__((always_inline)) {                 // the group maxima of K tile jt, when given
             if constexpr (PT) {
                 if (amax_given) load_key_amax<C>(kam, kam_head, jt * BT, S, tid);
             }
+        };
+        auto load_k = [&](int jt) __attribute__((always_inline)) {                   // K tile jt (and its group maxima) into the registers
+            load_tile<C, GENERAL>(kreg, khead, jt * BT, S, tid);
+            load_kam(jt);
         };
         PTile<C, PVMX> pb;
         v4i qr_lo[QRLO], qr_hi[QRHI];
@@ -1043,7 +1046,15 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // they work, but the forward was measured 8 % slower than with V going through registers.)
         // On main tiles K of tile jt+2 is requested in the middle of the score part (after its MFMAs), V after it:
         // the two bursts of requests (every wave of the workgroup issues them at about the same point) are half as
-        // long, and the matrix part of the score has 32 registers more.
+        // long, and the matrix part of the score has 32 registers more.  With the Step-2 scale (PT) the softmax part holds
+        // the key scales as well, and K requested in the middle of it spilled 113 registers at D = 128: there K is
+        // requested after it, and nothing spills but 50 registers of the FP8-MFMA pair (tensor scale at S = 4096, 32 / 8
+        // heads, with the group maxima: 199.3 -> 172.5 us).  At D = 64 a thread holds two 16-byte chunks each of K and V and
+        // nothing ever spilled: both are requested as soon as the last ones are staged, which covers the
+        // latency where a CU holds few workgroups, and the group maxima after the scores, where their bounds check and
+        // branch stand in nobody's way.  S = 2500 / 4096, 32 / 8 heads, per token: 60.1 / 122.3 us in the middle, 61.3 / 121.3
+        // after it, 60.1 / 120.2 as it is; tensor scale: 74.3 / 139.8, 74.7 / 135.9, 73.5 / 136.7.
+        constexpr bool KV_AT_ONCE = PT && D == 64;
         auto main_step = [&](int jt) __attribute__((always_inline)) {
             const int buf = jt & 1;
             if constexpr (!GENERAL && !PT && !PVMX) {
@@ -1064,13 +1075,15 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 load_v(vreg, vhead, (jt + 2) * BT, S, tid);
             } else {
                 if (jt + 1 < nt) stage_next(jt + 1, buf ^ 1);
+                if (KV_AT_ONCE && jt + 2 < nt) {
+                    load_tile<C, GENERAL>(kreg, khead, (jt + 2) * BT, S, tid);
+                    load_v(vreg, vhead, (jt + 2) * BT, S, tid);
+                }
                 score_part<C, LO, false, PT, PVMX>(qr_lo, qs_lo, klo_at(buf), kslo_at(buf), lofs.score_k, lofs.score_s, kts_at(buf), q_sq, false, BT, qrow_in_tile, lane, c, m, mfloor, l, o, pb,
                                          [&]() __attribute__((always_inline)) { if (!PT && jt + 2 < nt) load_k(jt + 2); });
-                // With the Step-2 scale the softmax part holds the key scales as well: K requested in the middle of it
-                // spilled 113 registers.  Requested here nothing spills: tensor scale at S = 4096, 32 / 8 heads, with
-                // the group maxima: 199.3 -> 172.5 us.
-                if (PT && jt + 2 < nt) load_k(jt + 2);
-                if (jt + 2 < nt) load_v(vreg, vhead, (jt + 2) * BT, S, tid);
+                if (PT && !KV_AT_ONCE && jt + 2 < nt) load_k(jt + 2);
+                if (KV_AT_ONCE && jt + 2 < nt) load_kam(jt + 2);
+                if (!KV_AT_ONCE && jt + 2 < nt) load_v(vreg, vhead, (jt + 2) * BT, S, tid);
             }
             pv(v_at(buf), lofs, lane, o, pb);
             __syncthreads();
