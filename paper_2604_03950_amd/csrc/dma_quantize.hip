@@ -143,16 +143,19 @@ block_amax_kernel(float* __restrict__ amax, int64_t S, int64_t block_rows, int64
     for (int64_t r = r0 + threadIdx.x; r < r1; r += 64) p[r] = a;
 }
 
-// Maximum over the 256 threads of a workgroup, returned to all of them.
+// Maximum over the THREADS threads of a workgroup, returned to all of them.
+template <int THREADS>
 DMA_DEV float workgroup_max(float a)
 {
-    __shared__ float part[QUANT_THREADS / 64];
     a = wave_max(a);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
-    __syncthreads();
-    a = part[0];
+    if constexpr (THREADS > 64) {
+        __shared__ float part[THREADS / 64];
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = a;
+        __syncthreads();
+        a = part[0];
 #pragma unroll
-    for (int w = 1; w < QUANT_THREADS / 64; ++w) a = fmaxf(a, part[w]);
+        for (int w = 1; w < THREADS / 64; ++w) a = fmaxf(a, part[w]);
+    }
     return a;
 }
 
@@ -176,18 +179,33 @@ DMA_DEV float strided_amax(const v4i* __restrict__ x, int64_t first, int64_t n, 
 }
 
 // Per-block maximum in one pass: a workgroup reads the rows of its block and writes their maximum to each of them.
-// Taken for blocks of FUSED_MIN .. FUSED_MAX rows: below, most of the threads would have nothing to read; above, few
-// workgroups would read long runs one after the other.
-constexpr int64_t FUSED_MIN = 32, FUSED_MAX = 1024;
-__global__ void __launch_bounds__(QUANT_THREADS)
+// Taken for blocks of FUSED_MIN .. FUSED_MAX rows: below, most lanes of a wave would have nothing to read; above, few
+// workgroups would read long runs one after the other.  Bound by launch and memory latency up to some thousand blocks,
+// by the read above.  The workgroup is as wide as the block asks for (GPU time per call, replayed from a graph; the two
+// launches of the general route, this kernel with 256 threads for every block, and as it is):
+//   one wave: a block of one round of its loads (4 chunks per lane, 256 chunks), and below 512 chunks when there are
+//     many blocks: with 256 threads most would load one chunk or none, and the short workgroups turn over slowly.
+//     D = 64, 32 rows: 3.8, 2.4, 2.3 us at 64 blocks, 5.5, 6.5, 3.5 at 4096, 30.4, 40.8, 21.0 at 32768;
+//     D = 64, 40 rows: 4.7, 3.3, 2.8 at 818 blocks, 30.1, 33.4, 22.4 at 26214 (50 blocks: 4.1, 2.4, 2.5 with one wave)
+//   1024 threads: from 8192 chunks, where 256 would read eight rounds or more one after the other, and no more blocks than
+//     the chip has CUs: beyond that a CU hides the latency with several workgroups, and a second wave of wide ones is
+//     nearly empty.  D = 128, 512 rows: 5.2, 4.9, 3.9 us with one block, 9.7, 5.8, 4.7 with 256, 12.7, 7.7, 8.8 with 320;
+//     1024 rows: 6.5 .. 8.1, 7.9, 5.5 with one, 12.4, 9.0, 6.4 with 128, 18.8, 12.6, 12.6 with 256, 21.2, 14.1, 16.6 with
+//     320 (4096 chunks: no clear gain)
+//   256 threads: between.
+constexpr int64_t FUSED_MIN = 32, FUSED_MAX = 1024;                             // rows
+constexpr int64_t WAVE_CHUNKS = 64 * QUANT_UNROLL, WIDE_CHUNKS = 8192;          // 16-byte chunks of a block
+constexpr int64_t MANY_BLOCKS = 512, CU_BLOCKS = 256;
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
 block_amax_fused_kernel(const v4i* __restrict__ x, int64_t S, int lanes_per_row, int64_t block_rows, int64_t blocks_per_matrix,
                         float c, int prescale, float* __restrict__ amax)
 {
     const int64_t mtx = blockIdx.x / blocks_per_matrix, blk = blockIdx.x % blocks_per_matrix;
     const int64_t r0 = blk * block_rows, r1 = (r0 + block_rows < S) ? r0 + block_rows : S;
-    const float a = workgroup_max(strided_amax(x + (mtx * S + r0) * lanes_per_row, threadIdx.x, (r1 - r0) * lanes_per_row, QUANT_THREADS));
+    const float a = workgroup_max<THREADS>(strided_amax(x + (mtx * S + r0) * lanes_per_row, threadIdx.x, (r1 - r0) * lanes_per_row, THREADS));
     float* p = amax + mtx * S;
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += QUANT_THREADS) p[r] = prescale ? __fmul_rn(a, c) : a;
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += THREADS) p[r] = prescale ? __fmul_rn(a, c) : a;
 }
 
 // Per-tensor maximum in two launches, the first bound by the read of x, the second by its launch: up to TENSOR_PARTS
@@ -195,13 +213,13 @@ block_amax_fused_kernel(const v4i* __restrict__ x, int64_t S, int lanes_per_row,
 // those and writes the result to its rows.  Workgroups of the second grid overwrite the partial maxima while others
 // read them, which does no harm: a cell holds its partial maximum or the maximum of all, and the maximum over any such
 // mixture is the same number.  (Four launches -- row maxima, runs of 1024 rows, one workgroup over the runs, a copy to
-// every row -- stood here before: see the measurement at launch_group_amax.)
+// every row -- stood here before; the figures are at launch_group_amax.)
 constexpr int64_t TENSOR_PARTS = 1024;
 __global__ void __launch_bounds__(QUANT_THREADS)
 tensor_parts_kernel(const v4i* __restrict__ x, int64_t chunks, float c, int prescale, float* __restrict__ amax)
 {
     const int64_t first = (int64_t)blockIdx.x * QUANT_THREADS + threadIdx.x;
-    const float a = workgroup_max(strided_amax(x, first, chunks, (int64_t)gridDim.x * QUANT_THREADS));
+    const float a = workgroup_max<QUANT_THREADS>(strided_amax(x, first, chunks, (int64_t)gridDim.x * QUANT_THREADS));
     if (threadIdx.x == 0) amax[blockIdx.x] = prescale ? __fmul_rn(a, c) : a;
 }
 __global__ void __launch_bounds__(QUANT_THREADS)
@@ -210,7 +228,7 @@ tensor_spread_kernel(float* amax, int64_t rows, int parts)
     float a = 0.f;
     for (int i = threadIdx.x; i < parts; i += QUANT_THREADS)
         a = fmaxf(a, __hip_atomic_load(amax + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    a = workgroup_max(a);
+    a = workgroup_max<QUANT_THREADS>(a);
     const int64_t base = (int64_t)blockIdx.x * QUANT_UNROLL * QUANT_THREADS + threadIdx.x;
 #pragma unroll
     for (int u = 0; u < QUANT_UNROLL; ++u) {
@@ -220,9 +238,9 @@ tensor_spread_kernel(float* amax, int64_t rows, int parts)
 }
 
 // granularity: 1 = the row, 2 = blocks of block_rows rows of each [S, D] matrix, 3 = everything.  D is 64 or 128.
-// Bound by launches at the sizes of one prefill: for 32 heads of 4096 x 128, per tensor 18.8 -> 12.7 us and per block of
-// 128 rows 12.8 -> 10.5 us against one launch per step of the reduction (call to call, the host's part included); the
-// maxima of Q and K and the forward of 32 / 8 heads at S = 4096 together 211.9 -> 199.1 us.
+// Bound by launches at the sizes of one prefill: for 32 heads of 4096 x 128, per tensor 16.0 -> 11.2 us and per block of
+// 128 rows 10.2 -> 7.6 us against one launch per step of the reduction (call to call, the host's part included), 16.0 ->
+// 7.2 and 7.9 -> 4.8 us of GPU time.
 int launch_group_amax(const void* x, int64_t n_mat, int64_t S, int D, int is_query, int granularity, int64_t block_rows,
                       float* amax, hipStream_t stream)
 {
@@ -244,9 +262,15 @@ int launch_group_amax(const void* x, int64_t n_mat, int64_t S, int D, int is_que
         if (rc != DMA_OK_) return rc;
         return launch(tensor_spread_kernel, dim3((unsigned)spread), dim3(QUANT_THREADS), stream, amax, rows, parts);
     }
-    if (granularity == 2 && block_rows >= FUSED_MIN && block_rows <= FUSED_MAX)
-        return launch(block_amax_fused_kernel, dim3((unsigned)(n_mat * bpm)), dim3(QUANT_THREADS), stream, (const v4i*)x, S, D / 8,
-                      block_rows, bpm, c, is_query, amax);
+    if (granularity == 2 && block_rows >= FUSED_MIN && block_rows <= FUSED_MAX) {
+        const int64_t per_block = block_rows * (D / 8);
+        auto fused = [&](auto kernel, int threads) {
+            return launch(kernel, dim3((unsigned)(n_mat * bpm)), dim3(threads), stream, (const v4i*)x, S, D / 8, block_rows, bpm, c, is_query, amax);
+        };
+        if (per_block <= WAVE_CHUNKS || (per_block < 2 * WAVE_CHUNKS && n_mat * bpm > MANY_BLOCKS)) return fused(block_amax_fused_kernel<64>, 64);
+        if (per_block >= WIDE_CHUNKS && n_mat * bpm <= CU_BLOCKS) return fused(block_amax_fused_kernel<1024>, 1024);
+        return fused(block_amax_fused_kernel<QUANT_THREADS>, QUANT_THREADS);
+    }
     int rc = D == 128 ? launch(row_amax_kernel<16>, dim3((unsigned)blocks), dim3(QUANT_THREADS), stream, (const v4i*)x, rows, c, is_query, amax)
                       : launch(row_amax_kernel<8>, dim3((unsigned)blocks), dim3(QUANT_THREADS), stream, (const v4i*)x, rows, c, is_query, amax);
     if (rc == DMA_OK_ && granularity == 2)

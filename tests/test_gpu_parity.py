@@ -555,6 +555,43 @@ def test_group_amax_routes_bit_exact(dma, n_mat, S, D, block_rows, is_query):
     assert torch.equal(got.cpu(), want)
 
 
+@pytest.mark.parametrize("n_mat,S,D,block_rows", [
+    (1, 131072, 128, 0), (2, 131073, 64, 0), (3, 300, 128, 0),             # 1024 partial maxima and two rounds per share; few
+    (3, 64, 64, 32), (40, 1056, 64, 32),                                   # one wave: a block is one round of its loads
+    (5, 120, 64, 40), (40, 1023, 64, 63), (40, 1023, 64, 33),              # ... below two rounds: few blocks / many blocks
+    (2, 200, 128, 32), (3, 511, 128, 511), (3, 1024, 128, 512), (2, 1025, 128, 1024), (2, 2000, 64, 1024),     # 256 / 1024 threads
+    (257, 512, 128, 512),                                                  # one block more than 1024 threads are taken for
+])
+def test_group_amax_maximum_in_every_share(dma, n_mat, S, D, block_rows):
+    """The largest value of the tensor moves over the rows -- the first, the last, and those whose chunks fall to the
+    shares on either side of the second grid's stride and to the middle one -- so that a reduction which loses some of the
+    shares, or of the waves of a workgroup, is seen; rows never written are seen by the NaN that `out` starts from."""
+    import torch
+    gen = torch.Generator().manual_seed(S + D)
+    x = torch.randn((n_mat, S, D), generator=gen).to(torch.bfloat16)
+    rows, step = n_mat * S, block_rows or S
+    per_share = 256 * 8 // D                                               # rows that one workgroup reads per load
+    want_rows = {0, rows // 2, rows - 1} | {r for s in (255, 256, 257, 511, 512, 1023) for r in (s * per_share,) if r < rows}
+    want_rows |= {r for r in range(min(step, S) - 1, 0, -max(1, step // 17))}          # through the first block
+    flat = x.view(rows, D)
+    base = x.float().abs().amax(-1)
+    xd = x.cuda()
+    for r in sorted(want_rows):
+        old = flat[r, D // 3].clone()
+        a = base.clone()
+        a.view(-1)[r] = 40.0
+        xd.view(rows, D)[r, D // 3] = -40.0
+        if block_rows:
+            pad = torch.nn.functional.pad(a, (0, -S % step)).view(n_mat, -1, step)
+            want = pad.amax(-1, keepdim=True).expand(-1, -1, step).reshape(n_mat, -1)[:, :S]
+        else:
+            want = a.max().expand(n_mat, S)
+        out = torch.full((n_mat, S), float("nan"), device="cuda")
+        got = dma.dma_mx_group_amax(xd, False, dma.GRAN_BLOCK if block_rows else dma.GRAN_TENSOR, block_rows, out=out)
+        assert torch.equal(got.cpu(), want), r
+        xd.view(rows, D)[r, D // 3] = old.cuda()
+
+
 @pytest.mark.parametrize("gran", ["block", "tensor"])
 @pytest.mark.parametrize("cfg,S,causal,sink", [("tiny", 256, True, 0), ("tiny", 200, False, 0), ("prefill_8k", 512, True, 0),
                                               ("prefill_8k", 640, True, 1), ("prefill_8k", 300, False, 0)])
