@@ -263,7 +263,7 @@ int launch_group_amax(const void* x, int64_t n_mat, int64_t S, int D, int is_que
         return launch(tensor_spread_kernel, dim3((unsigned)spread), dim3(QUANT_THREADS), stream, amax, rows, parts);
     }
     if (granularity == 2 && block_rows >= FUSED_MIN && block_rows <= FUSED_MAX) {
-        const int64_t per_block = block_rows * (D / 8);
+        const int64_t per_block = (block_rows < S ? block_rows : S) * (D / 8);       // chunks of the longest block
         auto fused = [&](auto kernel, int threads) {
             return launch(kernel, dim3((unsigned)(n_mat * bpm)), dim3(threads), stream, (const v4i*)x, S, D / 8, block_rows, bpm, c, is_query, amax);
         };

@@ -561,6 +561,7 @@ def test_group_amax_routes_bit_exact(dma, n_mat, S, D, block_rows, is_query):
     (5, 120, 64, 40), (40, 1023, 64, 63), (40, 1023, 64, 33),              # ... below two rounds: few blocks / many blocks
     (2, 200, 128, 32), (3, 511, 128, 511), (3, 1024, 128, 512), (2, 1025, 128, 1024), (2, 2000, 64, 1024),     # 256 / 1024 threads
     (257, 512, 128, 512),                                                  # one block more than 1024 threads are taken for
+    (300, 20, 64, 1024), (3, 40, 64, 1000),                                # blocks longer than the matrix
 ])
 def test_group_amax_maximum_in_every_share(dma, n_mat, S, D, block_rows):
     """The largest value of the tensor moves over the rows -- the first, the last, and those whose chunks fall to the
