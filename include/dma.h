@@ -148,7 +148,7 @@ typedef struct dma_attn_opts {
  *             multiplication by log2(e)/sqrt(D) of Alg. 2 Step 1) within the row's group.
  *   granularity  DMA_GRAN_TOKEN: the row itself; DMA_GRAN_BLOCK: block_rows (> 0) consecutive rows of one [S, D] matrix,
  *             blocks starting at multiples of block_rows (the last one may be shorter); DMA_GRAN_TENSOR: all of x.
- * Two to four small kernels on `stream`; no allocation.
+ * One or two small kernels on `stream`; no allocation.
  */
 #define DMA_GRAN_TOKEN 1
 #define DMA_GRAN_BLOCK 2

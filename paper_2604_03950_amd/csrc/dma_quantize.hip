@@ -104,8 +104,9 @@ int launch_diag_copy(const void* src, void* dst, int64_t bytes, hipStream_t stre
 
 // ---------------------------------------------------------------------------------------------
 // Group maxima for Alg. 2 Step 2 at a coarser granularity than the row (Sec. 5.3 names per-block and per-tensor).
-// First the maximum magnitude of every row (queries: after the pre-scale; the product is monotone, so it is taken of
-// the row maximum), then, in place, the maximum over the block of rows or over everything.
+// One launch where a workgroup can read a whole block, two otherwise: maxima of rows or of shares into the output, then,
+// in place, the maximum over the block or over everything.  Queries: after the pre-scale; the product is monotone, so it is
+// taken of the maximum.
 // ---------------------------------------------------------------------------------------------
 template <int LPR>                                    // lanes per row: D / 8
 __global__ void __launch_bounds__(QUANT_THREADS)
