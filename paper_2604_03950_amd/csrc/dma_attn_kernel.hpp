@@ -98,6 +98,10 @@ DMA_DEV v4i buffer_load16(rsrc_t r, unsigned byte_offset)
 {
     return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_offset, 0, 0));
 }
+DMA_DEV float buffer_load_f32(rsrc_t r, unsigned byte_offset)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_offset, 0, 0));
+}
 DMA_DEV void buffer_store16(rsrc_t r, unsigned byte_offset, v4f v)
 {
     // non-temporal: the output is written once and read by nobody here, it should not push K/V lines out of the L2
@@ -278,7 +282,6 @@ DMA_DEV void load_tile(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat, int
 {
     // rows [row0, row0 + BT) of the [S, D] bf16 matrix `mat` (uniform).  BOUNDED: rows >= S read as zero; otherwise
     // the caller guarantees row0 + BT <= S.
-    constexpr int KPR = C::T / C::CPR;                       // rows per chunk round
     const unsigned lane_off = (unsigned)fresh(tid) * 16u;
     if constexpr (!BOUNDED) {
         // whole tile: plain loads in the (scalar base + 32-bit lane offset) form; the bases are pinned in scalar
@@ -292,15 +295,15 @@ DMA_DEV void load_tile(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat, int
             reg[r] = *(global_v4i)((((uint64_t)hi << 32) | (uint64_t)lo) + (uint64_t)lane_off);
         }
     } else {
-        // one buffer resource per chunk round, based at the round's first row and as long as what is left of the
-        // matrix from there
+        // one buffer resource over the matrix; the whole offset is per lane, because only that part is checked against the
+        // resource's size (the offsets of the rows past the end stay below 2^32: dma_attn_fwd_ex refuses longer ones).
+        // In every wave's instruction stream: with a resource per chunk round (a base and a length each) a step held 60
+        // scalar instructions more and the instance spilled 31 scalar registers, now 5.  32 / 8 heads: S = 613 21.75 -> 21.44 us,
+        // 2 x S = 3000 without the mask 254.1 -> 253.7, S = 4096 with the tensor scale (and load_key_amax below) 170.9 -> 161.8.
+        const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));
+        const unsigned off = pin((unsigned)row0 * (C::D * 2) + lane_off);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            const int row = row0 + r * KPR;
-            const int64_t left = (int64_t)(S - row) * (C::D * 2);
-            const rsrc_t rs = make_rsrc(mat + (int64_t)row * C::D, left > 0 ? (uint32_t)left : 0u);
-            reg[r] = buffer_load16(rs, lane_off);
-        }
+        for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::T * 16);
     }
 }
 
@@ -321,13 +324,10 @@ DMA_DEV void load_tile_vmx(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat,
             reg[r] = *(global_v4i)((((uint64_t)hi << 32) | (uint64_t)lo) + (uint64_t)lane_off);
         }
     } else {
+        const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));          // as in load_tile
+        const unsigned off = pin((unsigned)row0 * (C::D * 2) + lane_off);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            const int row = row0 + r * C::VRG;
-            const int64_t left = (int64_t)(S - row) * (C::D * 2);
-            const rsrc_t rs = make_rsrc(mat + (int64_t)row * C::D, left > 0 ? (uint32_t)left : 0u);
-            reg[r] = buffer_load16(rs, lane_off);
-        }
+        for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::VRG * C::D * 2);
     }
 }
 
@@ -788,14 +788,16 @@ DMA_DEV void key_token_scales(const v4i (&reg)[C::CPT], float (&inv_sk)[C::CPT],
     }
 }
 
-// The group maxima of the key rows of a tile, one per chunk round of the thread (rows >= S: 0).
+// The group maxima of the key rows of a tile, one per chunk round of the thread (rows >= S read as 0 by the bounds of the
+// resource: a branch around each load made the wave wait for the one before).
 template <typename C>
 DMA_DEV void load_key_amax(float (&kam)[C::CPT], const float* __restrict__ amax_head, int row0, int S, int tid)
 {
     constexpr int KPR = C::T / C::CPR;
-    const int key0 = row0 + fresh(tid) / C::CPR;
+    const rsrc_t rs = make_rsrc(amax_head, (uint32_t)S * 4);
+    const unsigned off = (unsigned)(row0 + fresh(tid) / C::CPR) * 4;
 #pragma unroll
-    for (int r = 0; r < C::CPT; ++r) kam[r] = (key0 + r * KPR < S) ? amax_head[key0 + r * KPR] : 0.f;
+    for (int r = 0; r < C::CPT; ++r) kam[r] = buffer_load_f32(rs, off + 4 * r * KPR);
 }
 
 // K and V of one key tile from registers into LDS: K in the low format if some wave computes the tile in Phase 1,
