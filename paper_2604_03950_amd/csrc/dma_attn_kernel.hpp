@@ -345,15 +345,38 @@ DMA_DEV void stage_k(const v4i (&reg)[C::CPT], unsigned kdst, unsigned ksdst, un
     constexpr int STRIDE = C::template kstride<FMT>();
     const unsigned ka = pin(kdst + k_lane);
     const unsigned sa = pin(ksdst + s_lane);                  // every lane stores its block's scale: no divergence
+    if constexpr (FMT == FMT_E2M1 && !PT) {
+        // Keys are not pre-scaled: block maximum and converts work on the packed bf16 directly.  The thread's chunks go
+        // through every step side by side: one after the other each is a chain of dependent instructions with wait states
+        // between them (DPP sources, converts that fill one dword byte by byte: 19 s_nop per tile, now 1).  Bound by that chain
+        // where a wave has nothing beside it, by power at the large sizes: 4 / 1 heads, S = 8192 177.5 -> 174.8 us; 32 / 8,
+        // S = 2500 68.3 -> 67.5; S = 8192 at D = 64 303.1 -> 298.3; S = 32768 5967 -> 5937.
+        unsigned am[C::CPT], w4[C::CPT];
+        int code[C::CPT];
+        float sc[C::CPT];
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) am[r] = amax8_bf16_bits(reg[r]);
+        quad_max_u32(am);
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) {
+            code[r] = max((int)(am[r] >> 7) - 2, 0);
+            sc[r] = cvt_scale_operand(code[r]);
+        }
+        static_for<4>([&](auto T) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < C::CPT; ++r) put_e2m1_bf16<decltype(T)::value>(w4[r], reg[r][(int)T], sc[r]);
+        });
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) {
+            lds_write<int>(ka + r * KPR * STRIDE, (int)w4[r]);
+            lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code[r]);
+        }
+        return;
+    }
 #pragma unroll
     for (int r = 0; r < C::CPT; ++r) {
         if constexpr (FMT == FMT_BF16) {
             lds_write<v4i>(ka + r * KPR * STRIDE, reg[r]);
-        } else if constexpr (FMT == FMT_E2M1 && !PT) {
-            // keys are not pre-scaled: block maximum and converts work on the packed bf16 directly
-            const int code = max((int)(quad_max_u32(amax8_bf16_bits(reg[r])) >> 7) - 2, 0);
-            lds_write<int>(ka + r * KPR * STRIDE, encode8_e2m1_bf16(reg[r], code));
-            lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code);
         } else if constexpr (FMT == FMT_E2M1) {
             float x[8];
             unpack8<false>(reg[r], 1.f, x);

@@ -101,12 +101,14 @@ DMA_DEV void token_scale(float amax, float& s_q, float& inv_s_q)
     inv_s_q = ok ? __fdiv_rn(2688.0f, amax) : 1.0f;
 }
 
-DMA_DEV unsigned quad_max_u32(unsigned a)
+// quad_max for N unsigned values per lane, side by side (a DPP source needs two wait states after its last write).
+template <int N>
+DMA_DEV void quad_max_u32(unsigned (&a)[N])
 {
-    unsigned b = (unsigned)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true);
-    a = max(a, b);
-    b = (unsigned)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true);
-    return max(a, b);
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = max(a[i], (unsigned)__builtin_amdgcn_mov_dpp((int)a[i], 0xB1, 0xF, 0xF, true));
+#pragma unroll
+    for (int i = 0; i < N; ++i) a[i] = max(a[i], (unsigned)__builtin_amdgcn_mov_dpp((int)a[i], 0x4E, 0xF, 0xF, true));
 }
 
 // Largest magnitude among eight packed bf16, returned as its 15-bit pattern (sign cleared); the
@@ -147,21 +149,20 @@ DMA_DEV int encode8_e2m1(const float (&x)[8], int code)
     return (int)r;
 }
 
-// The same from eight packed bf16 (no pre-scale): the convert reads the bf16 pairs directly.
-// The four converts are written as instructions rather than through the builtin: with the elements of the 128-bit
-// vector named in the builtin this compiler emits the FIRST register of the source tuple for all four converts (wrong
+// Byte BYTE of a dword of codes from two packed bf16 (no pre-scale): the convert reads the bf16 pair directly.  Byte 0 starts
+// the dword (the other bytes are unspecified until they are written).
+// The converts are written as instructions rather than through the builtin: with the elements of a 128-bit vector
+// named in the builtin this compiler emits the FIRST register of the source tuple for all four converts (wrong
 // codes), and pinning each element into a register of its own costs a move per element; an instruction operand taken
 // from a vector element is allocated as the sub-register it is.
-// tests/test_isa.py checks the generated code of every instance for four distinct source registers per group.
-DMA_DEV int encode8_e2m1_bf16(const v4i& w, int code)
+// tests/test_isa.py checks the generated code of every instance for four distinct source registers per dword.
+template <int BYTE>
+DMA_DEV void put_e2m1_bf16(unsigned& r, int w, float sc)
 {
-    const float sc = cvt_scale_operand(code);
-    unsigned r = 0;
-    asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2" : "+v"(r) : "v"(w[0]), "v"(sc));
-    asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2 op_sel:[0,0,1,0]" : "+v"(r) : "v"(w[1]), "v"(sc));
-    asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2 op_sel:[0,0,0,1]" : "+v"(r) : "v"(w[2]), "v"(sc));
-    asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2 op_sel:[0,0,1,1]" : "+v"(r) : "v"(w[3]), "v"(sc));
-    return (int)r;
+    if constexpr (BYTE == 0) asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2" : "=v"(r) : "v"(w), "v"(sc));
+    else if constexpr (BYTE == 1) asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2 op_sel:[0,0,1,0]" : "+v"(r) : "v"(w), "v"(sc));
+    else if constexpr (BYTE == 2) asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2 op_sel:[0,0,0,1]" : "+v"(r) : "v"(w), "v"(sc));
+    else asm("v_cvt_scalef32_pk_fp4_bf16 %0, %1, %2 op_sel:[0,0,1,1]" : "+v"(r) : "v"(w), "v"(sc));
 }
 
 // Eight binary32 values -> eight E4M3 bytes (two dwords).  The hardware convert yields the NaN
@@ -299,7 +300,7 @@ DMA_DEV unsigned pk_max_u16(unsigned a, unsigned b)
 
 // Maximum over the lanes that share lane % CW (CW = 4, 8 or 16), of two packed 16-bit magnitudes: rotations inside
 // the 16-lane rows, then the rows pairwise (v_permlane16_swap), then the two half-waves (v_permlane32_swap).
-// (One dword at a time, in a scalar variable of its own: see encode8_e2m1_bf16 for why no vector element is named in
+// (One dword at a time, in a scalar variable of its own: see put_e2m1_bf16 for why no vector element is named in
 // a builtin here.)
 template <int CW>
 DMA_DEV unsigned strided_lane_max_u16(unsigned a)
