@@ -33,13 +33,15 @@ namespace dma {
 template <int A, int B>
 constexpr int cmax() { return A > B ? A : B; }
 
-template <int D_, int BT_, int TPW_>
+// KS: waves that share 32 query rows, each computing 1 / KS of the keys of every tile (dma_attn_split.hpp); 1 in this file.
+template <int D_, int BT_, int TPW_, int KS_ = 1>
 struct Cfg {
-    static constexpr int D = D_, BT = BT_, TPW = TPW_;
+    static constexpr int D = D_, BT = BT_, TPW = TPW_, KS = KS_;
     static constexpr int WPT = BT / 32;          // waves per logical query tile (32 rows each)
-    static constexpr int NW = WPT * TPW;         // waves per workgroup
+    static constexpr int NW = KS == 1 ? WPT * TPW : 2 * WPT;     // waves per workgroup
     static constexpr int T = NW * 64;            // threads per workgroup
     static constexpr int NKB = BT / 32;          // 32-key blocks per key tile
+    static constexpr int NB = NKB / KS;          // ... of which one wave computes this many
     static constexpr int NDB = D / 32;           // 32-wide blocks of the head dimension (output)
     static constexpr int NH = D / 64;            // k=64 scaled MFMAs per score block
     static constexpr int NKK = D / 16;           // k=16 bf16 MFMAs per score block
@@ -63,7 +65,7 @@ struct Cfg {
     static constexpr int V8BYTES = V8CODES + NKB * D;
     static constexpr int VCW = CPR / TPW;        // 16-byte chunks (of 8 columns) per row of lanes
     static constexpr int VRG = 64 / VCW;         // keys per chunk round of a wave
-    static_assert(NW == NKB * TPW && VRG * CPT == 32, "one 32-key block per wave (and column half)");
+    static_assert(KS > 1 || (NW == NKB * TPW && VRG * CPT == 32), "one 32-key block per wave (and column half)");
     // V rows sit densely in LDS; so that the transpose reads of four consecutive keys do not hit the same banks,
     // chunk c of key k is stored at chunk c ^ (4 * v_swizzle(k)).
     static constexpr int v_swizzle(int key) { return D == 128 ? (key & 3) : ((key >> 1) & 1); }
@@ -461,7 +463,7 @@ DMA_DEV void stage_v_mx(const v4i (&reg)[C::CPT], unsigned vdst, int tid)
 // MX-format P V, E4M3 codes of 64 keys per group with the lane's scale byte.
 template <typename C, bool PVMX>
 struct PTile {
-    v8bf b[2 * C::NKB];
+    v8bf b[2 * C::NB];
 };
 template <typename C>
 struct PTile<C, true> {
@@ -486,23 +488,16 @@ DMA_DEV v8i widen(const v4i& lo, const v4i& hi) { return v8i{lo[0], lo[1], lo[2]
 // First half of a key tile for one wave (all of its VALU work): scores S^T, causal mask, new running maximum,
 // rescale of l and O by 2^(m_old - m_new), probabilities P = 2^(S - m) summed into l and rounded to bf16.
 // The result is P^T packed as the B operands of the value part: pb[grp] holds keys 16 grp .. 16 grp + 15.
-// ksrc / kssrc: LDS addresses of the tile's K codes / scale bytes.
-// MAYBE_DIAG = false compiles the mask away (tiles strictly below the diagonal).
-// after_mfma() runs between the matrix part and the softmax part (the caller's global loads go there).
+// Three steps: score_products, mask_scores and softmax_part (score_max, move_max, probabilities); score_part is all of them
+// for waves that compute every key of the tile.
+
+// S - m of the wave's keys.  ksrc / kssrc: LDS addresses of the first of their K codes / scale bytes.
 // PT (per-token scale, Alg. 2 Step 2): the product of the codes is multiplied by S_q of the query row (q_sq) and S_q of
 // the key (one float per key at ktssrc) before the maximum is taken.
-// PVMX (MX-format P V): the probabilities leave as MXFP8-E4M3 blocks of 32 keys.  The lane holds 16 keys of every
-// 32-key block of its query (the other half-wave holds the other 16): keys 8 v + 4 g + b of block kb are byte b of
-// VGPR v (block 2c) or 4 + v (block 2c + 1) of the operand of key group c, which is the order the V^T operand is read
-// in (value_vmx_lane).  The block's scale comes from its largest probability 2^max(S - m): floor of that exponent.
-template <typename C, int FMT, bool MAYBE_DIAG, bool PT, bool PVMX, int QR, typename F>
-DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned kssrc, unsigned k_lane, unsigned s_lane,
-                        unsigned ktssrc, float q_sq, bool diagonal, int key_limit, int qrow_in_tile, int lane, float c,
-                        float& m, float& mfloor, float& l, v16f (&o)[C::NDB], PTile<C, PVMX>& pt, F&& after_mfma)
+template <typename C, int FMT, bool PT, int QR>
+DMA_DEV void score_products(v16f (&s)[C::NB], const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned kssrc, unsigned k_lane,
+                            unsigned s_lane, unsigned ktssrc, float q_sq, int g, float c, float m)
 {
-    lane = fresh(lane);
-    const int j = lane & 31, g = lane >> 5;
-    v16f s[C::NKB];
     constexpr int STRIDE = C::template kstride<FMT>();
     const unsigned ka = pin(ksrc + k_lane);                       // the lane's key row of 32-key block 0 (score_k_lane)
     // The accumulators start at -m (the running maximum so far), so the products arrive as S - m and the
@@ -518,13 +513,14 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
         // which go h-major so that the two MFMAs into one accumulator are not adjacent
         // scale of MX block 2h + g of the lane's key: byte 0 of the dword at chunk 4 (2h + g) of the key's scale row
         const unsigned sa = pin(kssrc + s_lane);
-        static_assert(C::NKB % 2 == 0, "key tile must hold an even number of 32-key blocks");
-        v4i a[2][2][C::NH];
-        int ksc[2][2][C::NH];
+        constexpr int U = C::NB < 2 ? C::NB : 2;
+        static_assert(C::NB % U == 0, "one 32-key block or an even number of them");
+        v4i a[2][U][C::NH];
+        int ksc[2][U][C::NH];
         auto fetch = [&](int pair) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int kb = 2 * pair + u;
+            for (int u = 0; u < U; ++u) {
+                const int kb = U * pair + u;
 #pragma unroll
                 for (int h = 0; h < C::NH; ++h) {
                     ksc[pair & 1][u][h] = lds_read<int>(sa + kb * 32 * C::CPR + 8 * h);
@@ -534,21 +530,21 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
         };
         fetch(0);
 #pragma unroll
-        for (int pair = 0; pair < C::NKB / 2; ++pair) {
-            if (pair + 1 < C::NKB / 2) fetch(pair + 1);
+        for (int pair = 0; pair < C::NB / U; ++pair) {
+            if (pair + 1 < C::NB / U) fetch(pair + 1);
             static_for<C::NH>([&](auto H) {
                 constexpr int h = H;
                 const v8i b = widen(qr[h]);
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    s[2 * pair + u] = mfma_mx<FMT, h>(widen(a[pair & 1][u][h]), b, h == 0 ? sinit : s[2 * pair + u], ksc[pair & 1][u][h], qscale);
+                for (int u = 0; u < U; ++u)
+                    s[U * pair + u] = mfma_mx<FMT, h>(widen(a[pair & 1][u][h]), b, h == 0 ? sinit : s[U * pair + u], ksc[pair & 1][u][h], qscale);
             });
             __builtin_amdgcn_sched_barrier(0);
         }
     } else if constexpr (FMT == FMT_E4M3) {
         const unsigned sa = pin(kssrc + s_lane);
 #pragma unroll
-        for (int kb = 0; kb < C::NKB; ++kb) {
+        for (int kb = 0; kb < C::NB; ++kb) {
             static_for<C::NH>([&](auto H) {
                 constexpr int h = H;
                 const int ksc = lds_read<int>(sa + kb * 32 * C::CPR + 8 * h);
@@ -561,7 +557,7 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
         // bf16 MFMA (unquantized, or MXFP8 decoded exactly): NKK k=16 steps per 32-key block, in units of UK steps;
         // the next unit's operands are in flight while the current unit multiplies.  Step kk = 4h + t multiplies the
         // lane's chunk t of MX block 2h + g (see load_q_raw): byte 128 h + 64 g + 16 t of the key's bf16 row.
-        constexpr int UK = 4, UPB = C::NKK / UK, NU = C::NKB * UPB;
+        constexpr int UK = 4, UPB = C::NKK / UK, NU = C::NB * UPB;
         static_assert(C::NKK % UK == 0, "head dimension must be a multiple of 64");
         v4i a[2][UK];
         auto fetch = [&](int u) {
@@ -583,7 +579,7 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
         }
         if constexpr (FMT == FMT_BF16) {                 // unquantized operands: the softmax factor multiplies the score
 #pragma unroll
-            for (int kb = 0; kb < C::NKB; ++kb)
+            for (int kb = 0; kb < C::NB; ++kb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) s[kb][r] = __builtin_fmaf(s[kb][r], c, -m);
         }
@@ -593,7 +589,7 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
         // register r of 32-key block kb is key 32 kb + 8 (r / 4) + 4 g + r % 4: four consecutive scales per read
         const unsigned ta = pin(ktssrc + 16 * g);
 #pragma unroll
-        for (int kb = 0; kb < C::NKB; ++kb)
+        for (int kb = 0; kb < C::NB; ++kb)
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 const v4f sk = lds_read<v4f>(ta + 4 * (32 * kb + 8 * r4));
@@ -601,77 +597,107 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
                 for (int e = 0; e < 4; ++e) s[kb][4 * r4 + e] = __builtin_fmaf(s[kb][4 * r4 + e], q_sq * sk[e], -m);
             }
     }
-    after_mfma();
+}
 
-    // ---- causal mask on the tile that straddles the diagonal (key > query -> -inf) and / or the keys of a partial
-    // last tile that lie past the end of the sequence (key >= key_limit -> -inf)
-    if constexpr (MAYBE_DIAG) {
-        if (diagonal || key_limit < C::BT) {
-            const int last_key = min(diagonal ? qrow_in_tile + j : C::BT - 1, key_limit - 1);
+// The causal mask on the tile that straddles the diagonal (key > query -> -inf) and / or the keys of a partial last tile
+// that lie past the end of the sequence (key >= key_limit -> -inf).  key0: the wave's first key in the tile.
+template <typename C>
+DMA_DEV void mask_scores(v16f (&s)[C::NB], bool diagonal, int key_limit, int qrow_in_tile, int key0, int j, int g)
+{
+    if (diagonal || key_limit < C::BT) {
+        const int last_key = min(diagonal ? qrow_in_tile + j : C::BT - 1, key_limit - 1) - key0;
 #pragma unroll
-            for (int kb = 0; kb < C::NKB; ++kb)
+        for (int kb = 0; kb < C::NB; ++kb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int kj = kb * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (kj > last_key) s[kb][r] = -INFINITY;
-                }
-        }
+            for (int r = 0; r < 16; ++r) {
+                const int kj = kb * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
+                s[kb][r] = kj > last_key ? -INFINITY : s[kb][r];
+            }
     }
+}
 
-    // ---- online softmax in base 2.  s holds S - m.  delta = how far the row maximum moves (>= 0; on the first tile
-    // of a row, where m is only the arbitrary start value 0, any sign: mfloor is -inf there and 0 afterwards).
+// Row maximum of the wave's scores.
+template <typename C>
+DMA_DEV float score_max(const v16f (&s)[C::NB])
+{
     float mx = -INFINITY;
-    float bmax[C::NKB];                                   // MX-format P V: maxima per 32-key block
-    if constexpr (PVMX) {
 #pragma unroll
-        for (int kb = 0; kb < C::NKB; ++kb) {
-            bmax[kb] = -INFINITY;
+    for (int kb = 0; kb < C::NB; ++kb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) bmax[kb] = fmaxf(bmax[kb], s[kb][r]);
-            bmax[kb] = cross_half_max(bmax[kb]);
-            mx = fmaxf(mx, bmax[kb]);
-        }
-    } else {
-#pragma unroll
-        for (int kb = 0; kb < C::NKB; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-        mx = cross_half_max(mx);
-    }
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+    return cross_half_max(mx);
+}
+
+// Online softmax in base 2: the running maximum moves by the returned delta, O and the scores (S - m) with it; alpha is
+// the factor for l.  delta >= 0; on the first tile of a row, where m is only the arbitrary start value 0, any sign: mfloor
+// is -inf there and 0 afterwards.
+template <typename C>
+DMA_DEV float move_max(v16f (&s)[C::NB], v16f (&o)[C::NDB], float mx, float& m, float& mfloor, float& alpha)
+{
     const float delta = fmaxf(mx, mfloor);
     const float mnew = m + delta;
-    const float alpha = __builtin_amdgcn_exp2f(fminf(m - mnew, 0.f));     // first tile: l and O are 0, any finite factor does
+    alpha = __builtin_amdgcn_exp2f(fminf(m - mnew, 0.f));     // first tile: l and O are 0, any finite factor does
     m = mnew;
     mfloor = 0.f;
     if (__builtin_amdgcn_ballot_w64(delta != 0.0f) != 0) {      // skipped when no row of the wave moved its maximum
 #pragma unroll
         for (int db = 0; db < C::NDB; ++db) o[db] *= alpha;
 #pragma unroll
-        for (int kb = 0; kb < C::NKB; ++kb) s[kb] -= delta;
+        for (int kb = 0; kb < C::NB; ++kb) s[kb] -= delta;
     }
+    return delta;
+}
 
-    // ---- P = 2^(S - m): row sums from the binary32 values; for the P V product bf16 (round to nearest even), or ...
+// P = 2^(S - m): for the P V product bf16 (round to nearest even); returns the row sum of the binary32 values.
+template <typename C>
+DMA_DEV float probabilities(const v16f (&s)[C::NB], PTile<C, false>& pt)
+{
     float psum[2] = {0.f, 0.f};
-    if constexpr (!PVMX) {
 #pragma unroll
-        for (int grp = 0; grp < 2 * C::NKB; ++grp) {
+    for (int grp = 0; grp < 2 * C::NB; ++grp) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float p0 = __builtin_amdgcn_exp2f(s[grp >> 1][8 * (grp & 1) + 2 * t]);
-                const float p1 = __builtin_amdgcn_exp2f(s[grp >> 1][8 * (grp & 1) + 2 * t + 1]);
-                psum[0] += p0;
-                psum[1] += p1;
-                const v2bf h2 = __builtin_convertvector(v2f{p0, p1}, v2bf);
-                pt.b[grp][2 * t] = h2[0];
-                pt.b[grp][2 * t + 1] = h2[1];
-            }
+        for (int t = 0; t < 4; ++t) {
+            const float p0 = __builtin_amdgcn_exp2f(s[grp >> 1][8 * (grp & 1) + 2 * t]);
+            const float p1 = __builtin_amdgcn_exp2f(s[grp >> 1][8 * (grp & 1) + 2 * t + 1]);
+            psum[0] += p0;
+            psum[1] += p1;
+            const v2bf h2 = __builtin_convertvector(v2f{p0, p1}, v2bf);
+            pt.b[grp][2 * t] = h2[0];
+            pt.b[grp][2 * t + 1] = h2[1];
         }
+    }
+    return psum[0] + psum[1];
+}
+
+// From S - m to the probabilities.
+// PVMX (MX-format P V): the probabilities leave as MXFP8-E4M3 blocks of 32 keys.  The lane holds 16 keys of every
+// 32-key block of its query (the other half-wave holds the other 16): keys 8 v + 4 g + b of block kb are byte b of
+// VGPR v (block 2c) or 4 + v (block 2c + 1) of the operand of key group c, which is the order the V^T operand is read
+// in (value_vmx_lane).  The block's scale comes from its largest probability 2^max(S - m): floor of that exponent.
+template <typename C, bool PVMX>
+DMA_DEV void softmax_part(v16f (&s)[C::NB], float& m, float& mfloor, float& l, v16f (&o)[C::NDB], PTile<C, PVMX>& pt, int g)
+{
+    float alpha;
+    if constexpr (!PVMX) {
+        move_max<C>(s, o, score_max<C>(s), m, mfloor, alpha);
+        l = l * alpha + probabilities<C>(s, pt);
     } else {
-        // ... MXFP8-E4M3 blocks of 32 keys.  The block maximum of S - m after the rescale is bmax - delta (rounding is
+        float mx = -INFINITY, bmax[C::NB];                   // maxima per 32-key block
+#pragma unroll
+        for (int kb = 0; kb < C::NB; ++kb) {
+            bmax[kb] = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) bmax[kb] = fmaxf(bmax[kb], s[kb][r]);
+            bmax[kb] = cross_half_max(bmax[kb]);
+            mx = fmaxf(mx, bmax[kb]);
+        }
+        const float delta = move_max<C>(s, o, mx, m, mfloor, alpha);
+        float psum[2] = {0.f, 0.f};
+        // The block maximum of S - m after the rescale is bmax - delta (rounding is
         // monotone); the largest probability of the block is 2^that, so its biased exponent is 127 + floor(that) and the
         // scale byte max(127 + floor - 8, 0).  A block with every key masked has maximum -inf and scale byte 0.
 #pragma unroll
-        for (int cgrp = 0; cgrp < C::NKB / 2; ++cgrp) {
+        for (int cgrp = 0; cgrp < C::NB / 2; ++cgrp) {
             int code[2];
             int packed[8];
 #pragma unroll
@@ -695,8 +721,24 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
             pt.q[cgrp] = v8i{packed[0], packed[1], packed[2], packed[3], packed[4], packed[5], packed[6], packed[7]};
             pt.sc[cgrp] = g ? code[1] : code[0];
         }
+        l = l * alpha + (psum[0] + psum[1]);
     }
-    l = l * alpha + (psum[0] + psum[1]);
+}
+
+// MAYBE_DIAG = false compiles the mask away (tiles strictly below the diagonal).
+// after_mfma() runs between the matrix part and the softmax part (the caller's global loads go there).
+template <typename C, int FMT, bool MAYBE_DIAG, bool PT, bool PVMX, int QR, typename F>
+DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned kssrc, unsigned k_lane, unsigned s_lane,
+                        unsigned ktssrc, float q_sq, bool diagonal, int key_limit, int qrow_in_tile, int lane, float c,
+                        float& m, float& mfloor, float& l, v16f (&o)[C::NDB], PTile<C, PVMX>& pt, F&& after_mfma)
+{
+    lane = fresh(lane);
+    const int j = lane & 31, g = lane >> 5;
+    v16f s[C::NB];
+    score_products<C, FMT, PT>(s, qr, qscale, ksrc, kssrc, k_lane, s_lane, ktssrc, q_sq, g, c, m);
+    after_mfma();
+    if constexpr (MAYBE_DIAG) mask_scores<C>(s, diagonal, key_limit, qrow_in_tile, 0, j, g);
+    softmax_part<C, PVMX>(s, m, mfloor, l, o, pt, g);
 }
 
 // Second half (all matrix work): O^T += V^T . P^T in groups of 16 keys; the V^T operands of the next group are in
@@ -704,7 +746,7 @@ DMA_DEV void score_part(const v4i (&qr)[QR], int qscale, unsigned ksrc, unsigned
 template <typename C>
 DMA_DEV void value_part(unsigned vsrc, const unsigned (&v_lane)[C::NDB], v16f (&o)[C::NDB], const PTile<C, false>& pt)
 {
-    const v8bf (&pb)[2 * C::NKB] = pt.b;
+    const v8bf (&pb)[2 * C::NB] = pt.b;
     // va[db]: the lane's address for d-block db in the tile's first patch (value_v_lane); other patches are constant offsets
     unsigned va[C::NDB];
 #pragma unroll
@@ -718,7 +760,7 @@ DMA_DEV void value_part(unsigned vsrc, const unsigned (&v_lane)[C::NDB], v16f (&
             a[db] = v8s{a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
         }
     };
-    constexpr int NG = 2 * C::NKB;
+    constexpr int NG = 2 * C::NB;
     v8s vt[3][C::NDB];                       // operands of groups grp, grp+1 and grp+2 in rotation
     read_vt(vt[0], 0);
     if (NG > 1) read_vt(vt[1], 1);
@@ -1200,42 +1242,62 @@ inline int compute_units()
     return n;
 }
 
+// The static schedule as the kernels see it: `blocks` workgroups; items ranked in blocks of head_block heads (see the kernel)
+// of heads_x query heads, dealt to `workers` workgroups (those of one XCD when each keeps its own units).
+struct Schedule {
+    int64_t blocks;
+    int workers, heads_x, head_block;
+};
+// items: B * Hq * NG, NG groups of query rows per head; slots: the workgroups the chip holds at once.
+inline Schedule make_schedule(const AttnArgs& a, int NG, int64_t slots)
+{
+    Schedule s;
+    const int64_t items = (int64_t)a.B * a.Hq * NG;
+    s.blocks = items < slots ? items : slots;
+    // ranking blocks: the fewest heads that fill an even number of rounds, in whole
+    // groups of query heads that share a kv head: the workers of a round then walk the SAME K/V stream with items of nearly
+    // equal length (on the 32k GQA workload 17 % fewer bytes fetched than with single heads, 0.6 % less time)
+    const int units = a.B * a.Hkv, group = a.Hq / a.Hkv;
+    const bool by_xcd = (units % 8 == 0) && (s.blocks % 8 == 0);
+    s.workers = (int)(by_xcd ? s.blocks / 8 : s.blocks);
+    s.heads_x = by_xcd ? (units / 8) * group : a.B * a.Hq;
+    s.head_block = s.heads_x;
+    for (int hb = group; hb < s.heads_x; hb += group)
+        if (s.heads_x % hb == 0 && ((int64_t)hb * NG) % (2 * s.workers) == 0) { s.head_block = hb; break; }
+    return s;
+}
+
+// Launch a forward kernel whose items are one of NG groups of query rows of one head, on as many workgroups as the chip
+// holds at once (one per CU for the D = 128 instances), each walking its share of the work items.  resident_cache: the
+// kernel's resident workgroups per CU, the same on every device of one kind; kept once a query has succeeded (a failed query
+// is repeated by the next call); every writer stores the same value, so several host threads may launch at once.
+template <typename... P>
+static int launch_resident(void (*kernel)(P...), int threads, int NG, std::atomic<int>& resident_cache, const AttnArgs& a, hipStream_t stream)
+{
+    const int64_t items = (int64_t)a.B * a.Hq * NG;
+    if (items <= 0 || items > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED_;
+    const int cus = compute_units();
+    if (cus <= 0) return DMA_ERR_HIP_;
+    int resident = resident_cache.load(std::memory_order_relaxed);
+    if (resident == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, kernel, threads, 0) != hipSuccess || resident <= 0) return DMA_ERR_HIP_;
+        resident_cache.store(resident, std::memory_order_relaxed);
+    }
+    const Schedule s = make_schedule(a, NG, (int64_t)cus * resident);
+    const float c = (float)(1.4426950408889634074 / sqrt((double)a.D));
+    return launch(kernel, dim3((unsigned)s.blocks), dim3(threads), stream,
+                  (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, a.out, a.B, a.Hq, a.Hkv,
+                  a.S, a.band, a.sink, a.causal, c, s.head_block, a.q_amax, a.k_amax);
+}
+
 template <int D, int BT, int TPW, int LO, int HI, bool GENERAL, bool PT, bool PVMX = false>
 static int launch_variant(const AttnArgs& a, hipStream_t stream)
 {
     using C = Cfg<D, BT, TPW>;
     const int N = (a.S + BT - 1) / BT;
-    const int64_t items = (int64_t)a.B * a.Hq * ((N + TPW - 1) / TPW);
-    if ((!GENERAL && N % TPW != 0) || items <= 0 || items > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED_;
-    const int cus = compute_units();
-    if (cus <= 0) return DMA_ERR_HIP_;
-    // as many workgroups as the chip holds at once (one per CU for the D = 128 instances), each walking its share
-    // of the work items
-    // per instance, the same on every device of one kind; kept once a query has succeeded (a failed query is repeated by
-    // the next call); every writer stores the same value, so several host threads may launch at once
+    if (!GENERAL && N % TPW != 0) return DMA_ERR_UNSUPPORTED_;
     static std::atomic<int> resident_cache{0};
-    int resident = resident_cache.load(std::memory_order_relaxed);
-    if (resident == 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, C::T, 0) != hipSuccess || resident <= 0)
-            return DMA_ERR_HIP_;
-        resident_cache.store(resident, std::memory_order_relaxed);
-    }
-    const int64_t slots = (int64_t)cus * resident;
-    const int64_t blocks = items < slots ? items : slots;
-    const float c = (float)(1.4426950408889634074 / sqrt((double)D));
-    // ranking blocks: the fewest heads that fill an even number of rounds (mirrors the kernel's view of the grid), in whole
-    // groups of query heads that share a kv head: the workers of a round then walk the SAME K/V stream with items of nearly
-    // equal length (on the 32k GQA workload 17 % fewer bytes fetched than with single heads, 0.6 % less time)
-    const int units = a.B * a.Hkv, group = a.Hq / a.Hkv, NG = (N + TPW - 1) / TPW;
-    const bool by_xcd = (units % 8 == 0) && (blocks % 8 == 0);
-    const int workers = (int)(by_xcd ? blocks / 8 : blocks);
-    const int heads_x = by_xcd ? (units / 8) * group : a.B * a.Hq;
-    int head_block = heads_x;
-    for (int hb = group; hb < heads_x; hb += group)
-        if (heads_x % hb == 0 && ((int64_t)hb * NG) % (2 * workers) == 0) { head_block = hb; break; }
-    return launch(dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, dim3((unsigned)blocks), dim3(C::T), stream,
-                  (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, a.out, a.B, a.Hq, a.Hkv,
-                  a.S, a.band, a.sink, a.causal, c, head_block, a.q_amax, a.k_amax);
+    return launch_resident(dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, C::T, (N + TPW - 1) / TPW, resident_cache, a, stream);
 }
 
 // Alg. 1 as printed (causal, no sink window, sequence a whole number of tile groups) runs the straight-line instance, whose

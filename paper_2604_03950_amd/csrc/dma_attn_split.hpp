@@ -1,0 +1,354 @@
+// The forward of dma_attn_kernel.hpp for problems with few work items: the keys of a tile are split over waves.
+//
+// Work split.  A work item is 32 * NW / KS query rows of one logical tile (a whole tile or half of one); KS waves share 32
+// query rows, and each computes the scores, probabilities and P V of 1 / KS of the keys of EVERY key tile, with its own
+// partial O and l.  The row maximum of a tile is exchanged through LDS before the exponentials, so every wave uses the
+// running maximum of the whole tile, as Alg. 1 does: the probabilities (and their rounding to bf16) are the ones the
+// unsplit kernel forms; only the binary32 sums over the keys are taken in another order.  The partial sums meet in LDS at
+// the end of the item.  Nothing but the output goes to memory.
+//
+// Pipeline.  One barrier per tile, in the middle of the step: before it K of tile jt + 1 is staged, the scores of tile jt
+// are formed and each wave publishes its row maxima; behind it V of tile jt + 1 is staged, the maxima are read, and the
+// exponentials and P V of tile jt follow.  K of buffer b is read before the barrier of a step only and V of buffer b
+// behind it only, so the buffers of the step before are free at either place.
+#pragma once
+
+#include "dma_attn_kernel.hpp"
+
+namespace dma {
+
+// Sink window, non-causal variant and ragged lengths are all handled by this one instance (loads bounded by buffer
+// resources, precision and mask decided per tile).
+template <int D, int BT, int KS, int LO, int HI, bool PT>
+__global__ void __launch_bounds__((BT / 32) * 2 * 64, 2)
+dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                      const uint16_t* __restrict__ v, float* __restrict__ out,
+                      int B, int Hq, int Hkv, int S, int band, int sink, int causal, float c, int head_block,
+                      const float* __restrict__ q_amax, const float* __restrict__ k_amax)
+{
+    using C = Cfg<D, BT, 1, KS>;
+    constexpr bool TWO = (LO != HI);
+    constexpr int RG = C::NW / KS;                       // groups of 32 query rows
+    constexpr int ROWS = 32 * RG;                        // query rows of an item
+    static_assert(BT % ROWS == 0, "an item lies inside one logical tile");
+    constexpr int KLO = C::template kbytes<LO>();
+    constexpr int KHI = TWO ? C::template kbytes<HI>() : 0;
+    constexpr int QRLO = C::template qregs<LO>();
+    constexpr int QRHI = TWO ? C::template qregs<HI>() : 1;
+    // LDS map (bytes): the row maxima of the waves' shares (double-buffered), then V and K as in the unsplit kernel, all
+    // double-buffered.  The partial sums of the epilogue reuse V and K.
+    constexpr int MAXIMA = C::NW * 32 * 4;
+    constexpr int OFF_V = 2 * MAXIMA;
+    constexpr int OFF_KLO = OFF_V + 2 * C::VBYTES;
+    constexpr int OFF_KSLO = OFF_KLO + 2 * KLO;
+    constexpr int OFF_KHI = OFF_KSLO + 2 * C::KSC;
+    constexpr bool HI_SCALES = TWO && !uses_bf16_mfma(HI);
+    constexpr int OFF_KSHI = OFF_KHI + 2 * KHI;
+    constexpr int OFF_KTS = OFF_KSHI + (HI_SCALES ? 2 * C::KSC : 0);
+    constexpr int EPI_STRIDE = D * 4 + 16;               // bytes per row of a wave's partial O (padded against bank conflicts)
+    constexpr int EPI_WAVE = 32 * EPI_STRIDE;
+    constexpr int OFF_EPI = OFF_V;
+    constexpr int LDS_TOTAL = cmax<OFF_KTS + (PT ? 2 * BT * 4 : 0), OFF_EPI + C::NW * EPI_WAVE>();
+    static_assert(LDS_TOTAL <= 160 * 1024, "LDS budget of one CU");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_TOTAL];
+    const unsigned lds0 = (unsigned)(uintptr_t)(DMA_LDS uint8_t*)lds;
+    auto v_at = [&](int buf) { return lds0 + OFF_V + buf * C::VBYTES; };
+    auto klo_at = [&](int buf) { return lds0 + OFF_KLO + buf * KLO; };
+    auto kslo_at = [&](int buf) { return lds0 + OFF_KSLO + buf * C::KSC; };
+    auto khi_at = [&](int buf) { return lds0 + OFF_KHI + buf * KHI; };
+    auto kshi_at = [&](int buf) { return lds0 + OFF_KSHI + (HI_SCALES ? buf * C::KSC : 0); };
+    auto kts_at = [&](int buf) { return lds0 + OFF_KTS + (PT ? buf * BT * 4 : 0); };
+
+    const bool amax_given = PT && q_amax != nullptr;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int rg = wave % RG, kh = wave / RG;            // the wave's query rows and its share of the keys
+    const int key0 = kh * C::NB * 32;
+    LaneOffsets<C, LO> lofs;
+    lofs.init(tid, lane);
+    const unsigned mx_slot = pin((kh * RG + rg) * 128 + 4 * (lane & 31));      // the wave's maxima; the others' are a xor away
+
+    // ---- static schedule: as in the unsplit kernel, with items of ROWS query rows
+    const int N = (S + BT - 1) / BT;
+    const int NG = (S + ROWS - 1) / ROWS;
+    const int group = Hq / Hkv;
+    const int units = B * Hkv;
+    const bool by_xcd = (units % 8 == 0) && (gridDim.x % 8 == 0);
+    const int xcd = by_xcd ? (int)(blockIdx.x & 7) : 0;
+    const int slot = by_xcd ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    const int workers = by_xcd ? (int)(gridDim.x >> 3) : (int)gridDim.x;
+    const int heads_x = by_xcd ? (units / 8) * group : B * Hq;
+    const int items = heads_x * NG;
+
+    for (int round = 0;; ++round) {
+        const int pos = round * workers + ((round & 1) ? workers - 1 - slot : slot);
+        if (pos >= items) break;
+        const int blk = pos / (head_block * NG), within = pos % (head_block * NG);
+        const int grp = NG - 1 - within / head_block;
+        const int hx = blk * head_block + within % head_block;
+        const int unit = by_xcd ? (hx / group) * 8 + xcd : hx / group;
+        const int b = unit / Hkv;
+        const int hkv = unit % Hkv;
+        const int hq = hkv * group + hx % group;
+        const uint16_t* qhead = q + ((int64_t)b * Hq + hq) * S * D;
+        const uint16_t* khead = k + ((int64_t)b * Hkv + hkv) * S * D;
+        const uint16_t* vhead = v + ((int64_t)b * Hkv + hkv) * S * D;
+        float* ohead = out + ((int64_t)b * Hq + hq) * S * D;
+        const float* qam_head = amax_given ? q_amax + ((int64_t)b * Hq + hq) * S : nullptr;
+        const float* kam_head = amax_given ? k_amax + ((int64_t)b * Hkv + hkv) * S : nullptr;
+
+        const int row0 = grp * ROWS, it = row0 / BT;
+        const int qrow = row0 + rg * 32, qrow_in_tile = qrow - it * BT;
+        const int nt = causal ? it + 1 : N;
+        auto tile_hi = [&](int jt) __attribute__((always_inline)) {
+            if (!TWO) return false;
+            if (jt < sink) return true;
+            const int dist = (causal || it >= jt) ? it - jt : jt - it;
+            return dist < band;
+        };
+        // main tiles (low format, unmasked) and band tiles [0, s1), [w0, w1) and a partial last tile without the causal mask
+        int w0, w1, s1 = TWO ? min(sink, nt) : 0;
+        if (causal) {
+            w0 = (TWO && band > 0) ? max(0, it + 1 - band) : it;
+            w1 = nt;
+        } else if (TWO && band > 0) {
+            w0 = max(0, it + 1 - band);
+            w1 = min(N, it + band);
+        } else {
+            w0 = w1 = nt;
+        }
+        const bool ragged_tail = !causal && S % BT != 0;
+        if (ragged_tail) w0 = min(w0, nt - 1);
+        if (s1 > w0) { w1 = max(w1, s1); w0 = 0; s1 = 0; }
+
+        float m = 0.f, mfloor = -INFINITY, l = 0.f;
+        v16f o[C::NDB];
+#pragma unroll
+        for (int db = 0; db < C::NDB; ++db) o[db] = v16f{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+
+        v4i kreg[C::CPT], vreg[C::CPT];
+        float kam[C::CPT];
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) kam[r] = 0.f;
+        auto load_k = [&](int jt) __attribute__((always_inline)) {
+            load_tile<C, true>(kreg, khead, jt * BT, S, tid);
+            if constexpr (PT) {
+                if (amax_given) load_key_amax<C>(kam, kam_head, jt * BT, S, tid);
+            }
+        };
+        auto load_v = [&](int jt) __attribute__((always_inline)) { load_tile<C, true>(vreg, vhead, jt * BT, S, tid); };
+        auto stage_key = [&](int jt, bool lo_known) __attribute__((always_inline)) {                 // K tile jt from the registers into LDS
+            const int buf = jt & 1;
+            float inv_sk[C::CPT], bam[C::CPT];
+#pragma unroll
+            for (int r = 0; r < C::CPT; ++r) inv_sk[r] = 1.f, bam[r] = 0.f;
+            if constexpr (PT) key_token_scales<C>(kreg, inv_sk, bam, kts_at(buf), tid, kam, amax_given);
+            const bool h = !lo_known && tile_hi(jt);
+            if (!h) stage_k<C, LO, PT>(kreg, klo_at(buf), kslo_at(buf), lofs.stage_k, lofs.stage_s, inv_sk, bam);
+            if constexpr (TWO) {
+                if (h) stage_k<C, HI, PT>(kreg, khi_at(buf), kshi_at(buf), stage_k_lane<C, HI>(fresh(tid)), lofs.stage_s, inv_sk, bam);
+            }
+        };
+
+        // ---- prologue: key tile 0 and the query operands, tile 0 into LDS buffer 0, tile 1 requested
+        PTile<C, false> pb;
+        v4i qr_lo[QRLO], qr_hi[QRHI];
+        int qs_lo = 0, qs_hi = 0;
+        float q_sq = 1.f;
+        {
+            v4i qraw[C::NKK];
+            load_q_raw<C>(qraw, make_rsrc(qhead, (uint32_t)S * (D * 2)), qrow, fresh(lane) & 31, fresh(lane) >> 5);
+            load_k(0);
+            load_v(0);
+            __builtin_amdgcn_sched_barrier(0);
+            float inv_sq = 1.f;
+            if constexpr (PT) {
+                float amax;
+                if (amax_given) {
+                    const int row = qrow + (fresh(lane) & 31);
+                    amax = row < S ? qam_head[row] : 0.f;
+                } else {
+                    amax = q_row_amax<C>(qraw, c);
+                }
+                token_scale(amax, q_sq, inv_sq);
+            }
+            make_q<C, LO, PT>(qr_lo, qs_lo, qraw, c, inv_sq);
+            if constexpr (TWO) {
+                if (band > 0 || sink > 0) make_q<C, HI, PT>(qr_hi, qs_hi, qraw, c, inv_sq);
+            }
+        }
+        stage_key(0, false);
+        stage_v<C>(vreg, v_at(0), lofs.stage_v);
+        load_k(1 < nt ? 1 : N);
+        load_v(1 < nt ? 1 : N);
+        __syncthreads();
+
+        // ---- tile loop.  MAIN: a main tile followed by another one, so that nothing of the step depends on jt.
+        auto step = [&](int jt, auto MAIN) __attribute__((always_inline)) {
+            constexpr bool main = decltype(MAIN)::value != 0;
+            const int buf = jt & 1, ln = fresh(lane), g = ln >> 5;
+            const unsigned kts = kts_at(buf) + 4 * key0;
+            v16f s[C::NB];
+            if (main || !tile_hi(jt)) {
+                score_products<C, LO, PT>(s, qr_lo, qs_lo, klo_at(buf) + key0 * C::template kstride<LO>(), kslo_at(buf) + key0 * C::CPR, lofs.score_k, lofs.score_s, kts, q_sq, g, c, m);
+            } else if constexpr (TWO) {
+                score_products<C, HI, PT>(s, qr_hi, qs_hi, khi_at(buf) + key0 * C::template kstride<HI>(), kshi_at(buf) + key0 * C::CPR, score_k_lane<C, HI>(fresh(lane)), lofs.score_s, kts, q_sq, g, c, m);
+            }
+            if (!main) mask_scores<C>(s, causal && jt == it, causal ? BT : min(BT, S - jt * BT), qrow_in_tile, key0, ln & 31, g);
+            float mx = score_max<C>(s);
+            const unsigned maxima = lds0 + buf * MAXIMA;
+            lds_write<float>(maxima + mx_slot, mx);
+            if (main || jt + 1 < nt) stage_key(jt + 1, main);
+            const int ahead = main || jt + 2 < nt ? jt + 2 : N;
+            load_k(ahead);
+            __syncthreads();
+            float other[KS - 1];
+#pragma unroll
+            for (int i = 1; i < KS; ++i) other[i - 1] = lds_read<float>(maxima + (mx_slot ^ (i * RG * 128)));
+            if (main || jt + 1 < nt) stage_v<C>(vreg, v_at(buf ^ 1), lofs.stage_v);
+            load_v(ahead);
+#pragma unroll
+            for (int i = 1; i < KS; ++i) mx = fmaxf(mx, other[i - 1]);
+            float alpha;
+            move_max<C>(s, o, mx, m, mfloor, alpha);
+            l = l * alpha + probabilities<C>(s, pb);
+            value_part<C>(v_at(buf) + key0 * C::VS, lofs.value_v, o, pb);
+        };
+        const int mend = ragged_tail ? max(w1, nt - 1) : nt;
+        for (int jt = 0; jt < nt; ++jt) {
+            const int stop = jt < s1 ? jt : jt < w0 ? w0 - 1 : jt < w1 ? jt : mend - 1;      // main tiles up to here
+            for (; jt < stop; ++jt) step(jt, IC<1>{});
+            step(jt, IC<0>{});
+        }
+
+        // ---- epilogue: every wave parks its partial O row-major in LDS and its partial l beside the maxima; then the KS
+        // waves of 32 query rows take 32 / KS of the rows each, add the partial sums in the order of the keys and store
+        // whole rows.
+        __syncthreads();
+        {
+            const int ln = fresh(lane);
+            const int j = ln & 31, g = ln >> 5;
+            lds_write<float>(lds0 + mx_slot, cross_half_sum(l));
+            const unsigned wr = pin(lds0 + OFF_EPI + wave * EPI_WAVE + j * EPI_STRIDE + 16 * g);
+#pragma unroll
+            for (int db = 0; db < C::NDB; ++db)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
+                    lds_write<v4f>(wr + 128 * db + 32 * r4, v4f{o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]});
+        }
+        __syncthreads();
+        {
+            constexpr int LPR = D / 4;                   // lanes per row, 16 bytes each
+            constexpr int RPI = 64 / LPR;                // rows per store
+            const int ln = fresh(lane);
+            const int rsub = ln / LPR, piece = ln % LPR;
+            const int first = kh * (32 / KS) + rsub;     // the lane's first row of the group
+            const rsrc_t omat = make_rsrc(ohead, (uint32_t)S * (D * 4));
+            const unsigned obase = (unsigned)(qrow + first) * (D * 4) + 16 * piece;
+            const unsigned rd = pin(lds0 + OFF_EPI + rg * EPI_WAVE + first * EPI_STRIDE + 16 * piece);
+            const unsigned rl = pin(lds0 + rg * 128 + 4 * first);
+#pragma unroll
+            for (int i = 0; i < 32 / KS / RPI; ++i) {
+                v4f sum = lds_read<v4f>(rd + i * RPI * EPI_STRIDE);
+                float lsum = lds_read<float>(rl + 4 * i * RPI);
+#pragma unroll
+                for (int p = 1; p < KS; ++p) {
+                    sum += lds_read<v4f>(rd + i * RPI * EPI_STRIDE + p * RG * EPI_WAVE);
+                    lsum += lds_read<float>(rl + 4 * i * RPI + p * RG * 128);
+                }
+                const float inv = 1.0f / lsum;
+                buffer_store16(omat, obase + i * RPI * (D * 4), sum * inv);
+            }
+        }
+        __syncthreads();                  // the next item's staging overwrites the partial sums
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Host side: pick the number of waves that share a tile's keys
+// ---------------------------------------------------------------------------------------------
+// The longest list of items any workgroup is dealt, in steps of the unsplit kernel: `step` per key tile and `item` per item
+// (prologue, epilogue, band tiles).  The heaviest lists are those of the first and the last worker: the first starts with
+// the longest item, the last has two neighbours of the middle.
+inline float longest_list(const AttnArgs& a, int rows, int64_t slots, float step, float item)
+{
+    const int N = (a.S + a.tile - 1) / a.tile, NG = (a.S + rows - 1) / rows;
+    const Schedule s = make_schedule(a, NG, slots);
+    const int64_t items = (int64_t)s.heads_x * NG, block = (int64_t)s.head_block * NG;
+    float longest = 0.f;
+    for (int w = 0; w < s.workers; w += s.workers > 1 ? s.workers - 1 : 1) {
+        float sum = 0.f;
+        int64_t pos = w;
+        for (int round = 0; pos < items; ++round, pos = (int64_t)round * s.workers + ((round & 1) ? s.workers - 1 - w : w)) {
+            const int grp = NG - 1 - (int)(pos % block) / s.head_block;
+            const int last_tile = (int)(((int64_t)(grp + 1) * rows - 1) / a.tile);           // of the item's rows
+            sum += item + step * (a.causal ? (last_tile + 1 < N ? last_tile + 1 : N) : N);
+        }
+        longest = sum > longest ? sum : longest;
+    }
+    return longest;
+}
+
+// Waves per 32 query rows.  A split item takes the same number of steps for half (2) or a quarter (4) of the query rows, and
+// a step does not get shorter in proportion, because every step still quantizes and stages a whole key tile: so the split
+// pays exactly where the chip would otherwise wait for the longest list of items.  One step, in steps of the unsplit
+// kernel, where nothing else limits it (4 heads, S = 900 to 3700; us per step of the unsplit, 2-way and 4-way kernel):
+//   D = 128  MXFP4 tiles 2.72, 1.66, 1.27; unquantized 2.92, 1.89, 1.33; staging-heavy paths: all MXFP8 3.19, 2.33, 1.82,
+//            Step-2 scale 3.46, 2.38, 1.92
+//   D = 64   MXFP4 tiles 0.96, 0.60; all MXFP8 1.07, 0.78; Step-2 scale 1.36, 0.90
+// and an item costs 2 to 2.5 steps (D = 128), 3.7 (D = 64, where two workgroups share a CU).  Measured with the choice that
+// is made (us, 1 / 2 / 4 waves): 4 / 1 heads S = 8192 176 / 114 / 98; S = 16384 338 / 261 / 360; 8 / 2 heads S = 5200
+// 123 / 78 / 99; 32 / 8 heads S = 640 21.3 / 18.3 / 18.7, S = 1800 51 / 45 / 67, S = 2600 69 / 80 / 112.  On the sizes 200 .. 16384
+// with 4 to 32 heads the choice costs at most 3.4 % against the best of the three.
+inline int key_split(const AttnArgs& a, bool staging_heavy)
+{
+    const int64_t cus = compute_units();
+    if (cus <= 0 || a.S <= a.tile) return 1;
+    const bool d64 = a.D == 64;
+    const int64_t slots = d64 ? 2 * cus : cus;
+    const int64_t items = (int64_t)a.B * a.Hq * ((a.S + 2 * a.tile - 1) / (2 * a.tile));
+    if (items > 4 * slots) return 1;                     // the lists are balanced: splitting only costs
+    const float whole = longest_list(a, 2 * a.tile, slots, 1.f, d64 ? 3.7f : 2.5f);
+    const float two = longest_list(a, a.tile, slots, d64 ? (staging_heavy ? 0.70f : 0.63f) : staging_heavy ? 0.72f : 0.63f, d64 ? 3.7f : 2.1f);
+    if (d64) return two < whole ? 2 : 1;
+    const float four = longest_list(a, a.tile / 2, slots, staging_heavy ? 0.57f : 0.47f, 1.9f);
+    return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
+}
+
+template <int D, int BT, int KS, int LO, int HI, bool PT>
+static int launch_split(const AttnArgs& a, hipStream_t stream)
+{
+    using C = Cfg<D, BT, 1, KS>;
+    constexpr int ROWS = 32 * C::NW / KS;
+    static std::atomic<int> resident_cache{0};
+    return launch_resident(dma_attn_split_kernel<D, BT, KS, LO, HI, PT>, C::T, (a.S + ROWS - 1) / ROWS, resident_cache, a, stream);
+}
+template <int D, int BT, int KS, int LO, int HI>
+static int launch_split(const AttnArgs& a, hipStream_t stream)
+{
+    if constexpr (LO != FMT_BF16) {                      // unquantized operands have no per-token scale
+        if (a.per_token) return launch_split<D, BT, KS, LO, HI, true>(a, stream);
+    }
+    return launch_split<D, BT, KS, LO, HI, false>(a, stream);
+}
+
+// Split, or the instance of the unsplit kernel with two logical tiles per workgroup (one for a single-tile sequence).
+template <int D, int BT, int LO, int HI>
+static int launch_tile(const AttnArgs& a, hipStream_t stream)
+{
+    if (!a.pv_mx) {
+        const bool staging_heavy = LO != FMT_BF16 && (a.per_token || LO != FMT_E2M1);
+        const int ks = key_split(a, staging_heavy);
+        if (ks == 2) return launch_split<D, BT, 2, LO, HI>(a, stream);
+        if constexpr (D == 128) {
+            if (ks == 4) return launch_split<D, BT, 4, LO, HI>(a, stream);
+        }
+    }
+    // two logical tiles per workgroup (256 query rows share each K/V tile); with an odd number of tiles the last
+    // pair is filled up with a tile past the end of the sequence.  One tile per workgroup only for a single tile.
+    if (a.S > BT) return launch_instance<D, BT, 2, LO, HI>(a, stream);
+    return launch_instance<D, BT, 1, LO, HI>(a, stream);
+}
+
+}  // namespace dma
