@@ -279,58 +279,33 @@ struct LaneOffsets {
 };
 
 // Chunk r of thread tid is 16-byte chunk r * T + tid of the dense tile: key r * (T / CPR) + tid / CPR.
-template <typename C, bool BOUNDED>
+template <typename C>
 DMA_DEV void load_tile(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat, int row0, int S, int tid)
 {
-    // rows [row0, row0 + BT) of the [S, D] bf16 matrix `mat` (uniform).  BOUNDED: rows >= S read as zero; otherwise
-    // the caller guarantees row0 + BT <= S.
-    const unsigned lane_off = (unsigned)fresh(tid) * 16u;
-    if constexpr (!BOUNDED) {
-        // whole tile: plain loads in the (scalar base + 32-bit lane offset) form; the bases are pinned in scalar
-        // registers so that no vector address arithmetic is generated
-        typedef const __attribute__((address_space(1))) v4i* global_v4i;
+    // rows [row0, row0 + BT) of the [S, D] bf16 matrix `mat` (uniform); rows >= S read as zero.
+    // One buffer resource over the matrix; the whole offset is per lane, because only that part is checked against the
+    // resource's size (the offsets of the rows past the end stay below 2^32: dma_attn_fwd_ex refuses longer ones).
+    // In every wave's instruction stream: with a resource per chunk round (a base and a length each) a step held 60
+    // scalar instructions more and the instance spilled 31 scalar registers.  32 / 8 heads: S = 613 21.75 -> 21.44 us,
+    // S = 4096 with the tensor scale (and load_key_amax below) 170.9 -> 161.8.  Loads from a scalar base per chunk
+    // round, unbounded, for whole tiles are no faster (S = 8192 410 us, the bounded ones 408).
+    const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));
+    const unsigned off = pin((unsigned)row0 * (C::D * 2) + (unsigned)fresh(tid) * 16u);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            const uint64_t t64 = (uint64_t)(mat + (int64_t)row0 * C::D) + (uint64_t)r * C::T * 16;
-            uint32_t lo = (uint32_t)t64, hi = (uint32_t)(t64 >> 32);
-            asm volatile("" : "+s"(lo), "+s"(hi));
-            reg[r] = *(global_v4i)((((uint64_t)hi << 32) | (uint64_t)lo) + (uint64_t)lane_off);
-        }
-    } else {
-        // one buffer resource over the matrix; the whole offset is per lane, because only that part is checked against the
-        // resource's size (the offsets of the rows past the end stay below 2^32: dma_attn_fwd_ex refuses longer ones).
-        // In every wave's instruction stream: with a resource per chunk round (a base and a length each) a step held 60
-        // scalar instructions more and the instance spilled 31 scalar registers, now 5.  32 / 8 heads: S = 613 21.75 -> 21.44 us,
-        // 2 x S = 3000 without the mask 254.1 -> 253.7, S = 4096 with the tensor scale (and load_key_amax below) 170.9 -> 161.8.
-        const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));
-        const unsigned off = pin((unsigned)row0 * (C::D * 2) + lane_off);
-#pragma unroll
-        for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::T * 16);
-    }
+    for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::T * 16);
 }
 
 // V tile in the thread mapping of the MX-format P V (vmx_thread).
-template <typename C, bool BOUNDED>
+template <typename C>
 DMA_DEV void load_tile_vmx(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat, int row0, int S, int tid)
 {
     int kb, key, chunk;
     vmx_thread<C>(fresh(tid), kb, key, chunk);
     const unsigned lane_off = (unsigned)((32 * kb + key) * C::CPR + chunk) * 16u;     // < BT * D * 2: inside the tile
-    if constexpr (!BOUNDED) {
-        typedef const __attribute__((address_space(1))) v4i* global_v4i;
+    const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));          // as in load_tile
+    const unsigned off = pin((unsigned)row0 * (C::D * 2) + lane_off);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            const uint64_t t64 = (uint64_t)(mat + (int64_t)(row0 + r * C::VRG) * C::D);
-            uint32_t lo = (uint32_t)t64, hi = (uint32_t)(t64 >> 32);
-            asm volatile("" : "+s"(lo), "+s"(hi));
-            reg[r] = *(global_v4i)((((uint64_t)hi << 32) | (uint64_t)lo) + (uint64_t)lane_off);
-        }
-    } else {
-        const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));          // as in load_tile
-        const unsigned off = pin((unsigned)row0 * (C::D * 2) + lane_off);
-#pragma unroll
-        for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::VRG * C::D * 2);
-    }
+    for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::VRG * C::D * 2);
 }
 
 // K tile from registers into LDS in format FMT.  kdst / ksdst: LDS addresses of the codes and of the scale bytes.
@@ -865,12 +840,11 @@ DMA_DEV void load_key_amax(float (&kam)[C::CPT], const float* __restrict__ amax_
     for (int r = 0; r < C::CPT; ++r) kam[r] = buffer_load_f32(rs, off + 4 * r * KPR);
 }
 
-// K and V of one key tile from registers into LDS: K in the low format if some wave computes the tile in Phase 1,
-// in the high format if some wave computes it in Phase 2.
-template <typename C, int LO, int HI, bool PT, bool PVMX>
-DMA_DEV void stage_tile(const v4i (&kreg)[C::CPT], const v4i (&vreg)[C::CPT], bool any_lo, bool any_hi,
-                        unsigned klo, unsigned kslo, unsigned khi, unsigned kshi, unsigned kts, unsigned vdst,
-                        const LaneOffsets<C, LO>& lo, int tid, const float (&kam)[C::CPT], bool kam_given)
+// K of one key tile from registers into LDS: in the low format if some wave computes the tile in Phase 1, in the high format
+// if some wave computes it in Phase 2.
+template <typename C, int LO, int HI, bool PT>
+DMA_DEV void stage_key(const v4i (&kreg)[C::CPT], bool any_lo, bool any_hi, unsigned klo, unsigned kslo, unsigned khi, unsigned kshi,
+                       unsigned kts, const LaneOffsets<C, LO>& lo, int tid, const float (&kam)[C::CPT], bool kam_given)
 {
     float inv_sk[C::CPT], bam[C::CPT];
 #pragma unroll
@@ -880,12 +854,11 @@ DMA_DEV void stage_tile(const v4i (&kreg)[C::CPT], const v4i (&vreg)[C::CPT], bo
     if constexpr (LO != HI) {
         if (any_hi) stage_k<C, HI, PT>(kreg, khi, kshi, stage_k_lane<C, HI>(fresh(tid)), lo.stage_s, inv_sk, bam);
     }
-    if constexpr (PVMX) stage_v_mx<C>(vreg, vdst, tid);
-    else stage_v<C>(vreg, vdst, lo.stage_v);
 }
 
-// GENERAL = false: Alg. 1 as printed (causal, no sink window; sink_arg / causal_arg are ignored): main tiles then band
-// tiles, two loops in a row.  GENERAL = true: sink window and / or no causal mask: runs of main and band tiles alternate.
+// GENERAL = false: Alg. 1 as printed (causal, no sink window; sink_arg / causal_arg are ignored), any length: main tiles then
+// band tiles.  GENERAL = true: sink window and / or no causal mask: runs of main and band tiles alternate.  (The general
+// instance on the causal mask: 64 x 32 / 8 heads, S = 300 209.3 us against 204.9; no difference from S = 2600 on.)
 // PT: per-token scale of Alg. 2 Step 2 on queries and keys (built with GENERAL only).
 // PVMX: the P V product in MXFP8-E4M3 with blocks of 32 keys (an extension beyond Alg. 1, which keeps P and V in 16 bit).
 template <int D, int BT, int TPW, int LO, int HI, bool GENERAL, bool PT, bool PVMX>
@@ -931,8 +904,8 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     auto kshi_at = [&](int buf) { return lds0 + OFF_KSHI + (HI_SCALES ? buf * C::KSC : 0); };
     auto kts_at = [&](int buf) { return lds0 + OFF_KTS + (PT ? buf * BT * 4 : 0); };
     auto load_v = [&](v4i (&reg)[C::CPT], const uint16_t* mat, int row0, int S_, int tid_) __attribute__((always_inline)) {
-        if constexpr (PVMX) load_tile_vmx<C, GENERAL>(reg, mat, row0, S_, tid_);
-        else load_tile<C, GENERAL>(reg, mat, row0, S_, tid_);
+        if constexpr (PVMX) load_tile_vmx<C>(reg, mat, row0, S_, tid_);
+        else load_tile<C>(reg, mat, row0, S_, tid_);
     };
     auto pv = [&](unsigned vsrc, const LaneOffsets<C, LO>& lo_, int lane_, v16f (&o_)[C::NDB], const PTile<C, PVMX>& p_) __attribute__((always_inline)) {
         if constexpr (PVMX) value_part<C>(vsrc, lane_, o_, p_);
@@ -953,8 +926,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     // everything), so the workers move from block to block together and share few K/V streams at a time.  When the
     // (batch, kv head) units divide over the 8 XCDs (workgroup i runs on XCD i % 8), each XCD keeps its own units, so
     // the K/V stream of a unit stays in one L2.
-    // Logical tiles per sequence; the last one may be partial.  When N is not a multiple of TPW (GENERAL instances only)
-    // the last group is filled up with query tiles that lie wholly past the end of the sequence: their rows load as
+    // Logical tiles per sequence; the last one may be partial.  When N is not a multiple of TPW the last group is filled up with query tiles that lie wholly past the end of the sequence: their rows load as
     // zeros, their waves compute zeros on main tiles and nothing on band tiles, and their stores are dropped by the bounds
     // of the output's buffer resource.
     const int N = (S + BT - 1) / BT;
@@ -1001,7 +973,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // flag of its own and a second test in `needs`: 5 VGPRs and up to 36 spilled SGPRs more; S = 2500: 67.9 us before
         // there was any of this, 68.3 with the flag, 68.05 with the bound).
         const int nt = causal ? min(last + 1, N) : N;
-        const int jlast = (GENERAL && TPW > 1 && it >= N) ? -1 : causal ? it : N;
+        const int jlast = (TPW > 1 && it >= N) ? -1 : causal ? it : N;
         auto tile_hi = [&](int qt, int jt) __attribute__((always_inline)) {             // does query tile qt compute key tile jt in the high format?
             if (!TWO) return false;
             if (jt < sink) return true;
@@ -1057,14 +1029,11 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         float kam[C::CPT];                               // group maxima of the key rows in kreg (when given)
 #pragma unroll
         for (int r = 0; r < C::CPT; ++r) kam[r] = 0.f;
-        auto load_kam = [&](int jt) __attribute__((always_inline)) {                 // the group maxima of K tile jt, when given
+        auto load_k = [&](int jt) __attribute__((always_inline)) {                   // K tile jt (and its group maxima) into the registers
+            load_tile<C>(kreg, khead, jt * BT, S, tid);
             if constexpr (PT) {
                 if (amax_given) load_key_amax<C>(kam, kam_head, jt * BT, S, tid);
             }
-        };
-        auto load_k = [&](int jt) __attribute__((always_inline)) {                   // K tile jt (and its group maxima) into the registers
-            load_tile<C, GENERAL>(kreg, khead, jt * BT, S, tid);
-            load_kam(jt);
         };
         PTile<C, PVMX> pb;
         v4i qr_lo[QRLO], qr_hi[QRHI];
@@ -1092,66 +1061,50 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 if (band > 0 || sink > 0) make_q<C, HI, PT>(qr_hi, qs_hi, qraw, c, inv_sq);
             }
         }
+        auto stage_value = [&](int buf) __attribute__((always_inline)) {                 // V of the registers into LDS buffer buf
+            if constexpr (PVMX) stage_v_mx<C>(vreg, v_at(buf), tid);
+            else stage_v<C>(vreg, v_at(buf), lofs.stage_v);
+        };
         auto stage_next = [&](int jt, int buf) __attribute__((always_inline)) {         // tile jt from the K/V registers into LDS buffer buf
             bool any_lo, any_hi;
             needs(jt, any_lo, any_hi);
-            stage_tile<C, LO, HI, PT, PVMX>(kreg, vreg, any_lo, any_hi, klo_at(buf), kslo_at(buf), khi_at(buf), kshi_at(buf), kts_at(buf),
-                                      v_at(buf), lofs, tid, kam, amax_given);
+            stage_key<C, LO, HI, PT>(kreg, any_lo, any_hi, klo_at(buf), kslo_at(buf), khi_at(buf), kshi_at(buf), kts_at(buf), lofs, tid, kam, amax_given);
+            stage_value(buf);
         };
+        // K and V tile jt into the registers; past the item's last tile from a tile of which no row exists (zeros, no memory
+        // access), so that the number of loads in flight is the same on every path and a wait for K does not wait for V too.
+        // (An item of a single-tile sequence never has a next tile.)
+        auto tile_or_none = [&](int jt) __attribute__((always_inline)) { return jt < nt ? jt : N; };
         stage_next(0, 0);
-        if (1 < nt) {
-            load_k(1);
-            load_v(vreg, vhead, BT, S, tid);
+        if (TPW > 1 || 1 < nt) {
+            load_k(tile_or_none(1));
+            load_v(vreg, vhead, tile_or_none(1) * BT, S, tid);
         }
         __syncthreads();
 
-        // ---- tile loop.  Tile jt lives in LDS buffer jt & 1; one barrier per tile.  At the top of step jt the K and
-        // V tiles jt+1 (loaded into registers during step jt-1) go into the other buffer (K quantized on the way) and
-        // the loads of tile jt+2 start; then the wave computes tile jt.
+        // ---- tile loop.  Tile jt lives in LDS buffer jt & 1; one barrier per tile.  During step jt the K and V tiles jt+1
+        // (loaded into registers during step jt-1) go into the other buffer (K quantized on the way) and the loads of
+        // tile jt+2 start.
         // (Direct global-to-LDS loads are not used for V: generated from the builtin, the compiler orders every later LDS
         // access behind them with a full vmcnt(0) wait, which exposes the memory latency; issued from inline assembly
         // they work, but the forward was measured 8 % slower than with V going through registers.)
-        // On main tiles K of tile jt+2 is requested in the middle of the score part (after its MFMAs), V after it:
-        // the two bursts of requests (every wave of the workgroup issues them at about the same point) are half as
-        // long, and the matrix part of the score has 32 registers more.  With the Step-2 scale (PT) the softmax part holds
-        // the key scales as well, and K requested in the middle of it spilled 113 registers at D = 128: there K is
-        // requested after it, and nothing spills but 50 registers of the FP8-MFMA pair (tensor scale at S = 4096, 32 / 8
-        // heads, with the group maxima: 199.3 -> 172.5 us).  At D = 64 a thread holds two 16-byte chunks each of K and V and
-        // nothing ever spilled: both are requested as soon as the last ones are staged, which covers the
-        // latency where a CU holds few workgroups, and the group maxima after the scores, where their bounds check and
-        // branch stand in nobody's way.  S = 2500 / 4096, 32 / 8 heads, per token: 60.1 / 122.3 us in the middle, 61.3 / 121.3
-        // after it, 60.1 / 120.2 as it is; tensor scale: 74.3 / 139.8, 74.7 / 135.9, 73.5 / 136.7.
-        constexpr bool KV_AT_ONCE = PT && D == 64;
+        // A main step is a main tile followed by another one: the next tile is staged in the low format and the one after
+        // it exists or is past the end of the matrix, so that nothing here branches but the rescale, and the compiler
+        // schedules the step as one block.  K is staged and then requested (behind the score MFMAs; with the Step-2 scale
+        // behind the softmax, where the key scales no longer need registers), V is staged behind the softmax, right before
+        // its registers are requested again.  Against steps that ask per tile which formats it needs, with K and V staged
+        // together (32 / 8 heads unless stated): S = 2500 67.0 -> 62.2 us, S = 32768 5634 -> 5534, 2 x S = 3000 without the mask
+        // 246.0 -> 236.4, S = 8192 per token 513 -> 496, D = 64 S = 5200 134.9 -> 129.9; 8k prefill 407.5 -> 397.5, with the MX-format
+        // P V 577 -> 524.  V staged with K at the top costs 0.6 % at S = 32768, both of them behind the score MFMAs 1.8 %, in half
+        // of the waves 2 %.  Bound by vector issue, and by power at the full sizes (2.2 GHz of 2.4 at S = 32768).
         auto main_step = [&](int jt) __attribute__((always_inline)) {
-            const int buf = jt & 1;
-            if constexpr (!GENERAL && !PT && !PVMX) {
-                // Alg. 1 as printed: a main tile is followed by at least two more tiles, so nothing here needs a
-                // condition on jt.  The two waves of a SIMD (w and w + 4) take the staging of the next tile and their
-                // score MFMAs in opposite order: the matrix pipe serves one wave at a time, the lower-numbered one
-                // first, so wave w multiplies while wave w + 4 quantizes and stages, then the other way round, instead
-                // of both staging and then one waiting for the other's MFMAs (measured -0.8 % on the 32k workload,
-                // -0.5 % on the 8k prefill; the opposite assignment gains nothing).
-                const bool mfma_first = C::NW == 8 && __builtin_amdgcn_readfirstlane(tid) < 256;
-                if (!mfma_first) stage_next(jt + 1, buf ^ 1);
-                score_part<C, LO, false, PT, PVMX>(qr_lo, qs_lo, klo_at(buf), kslo_at(buf), lofs.score_k, lofs.score_s, kts_at(buf), q_sq, false, BT, qrow_in_tile, lane, c, m, mfloor, l, o, pb,
-                                         [&]() __attribute__((always_inline)) {
-                                             if (mfma_first) stage_next(jt + 1, buf ^ 1);
-                                             __builtin_amdgcn_sched_barrier(0);
-                                             load_k(jt + 2);
-                                         });
-                load_v(vreg, vhead, (jt + 2) * BT, S, tid);
-            } else {
-                if (jt + 1 < nt) stage_next(jt + 1, buf ^ 1);
-                if (KV_AT_ONCE && jt + 2 < nt) {
-                    load_tile<C, GENERAL>(kreg, khead, (jt + 2) * BT, S, tid);
-                    load_v(vreg, vhead, (jt + 2) * BT, S, tid);
-                }
-                score_part<C, LO, false, PT, PVMX>(qr_lo, qs_lo, klo_at(buf), kslo_at(buf), lofs.score_k, lofs.score_s, kts_at(buf), q_sq, false, BT, qrow_in_tile, lane, c, m, mfloor, l, o, pb,
-                                         [&]() __attribute__((always_inline)) { if (!PT && jt + 2 < nt) load_k(jt + 2); });
-                if (PT && !KV_AT_ONCE && jt + 2 < nt) load_k(jt + 2);
-                if (KV_AT_ONCE && jt + 2 < nt) load_kam(jt + 2);
-                if (!KV_AT_ONCE && jt + 2 < nt) load_v(vreg, vhead, (jt + 2) * BT, S, tid);
-            }
+            const int buf = jt & 1, nxt = buf ^ 1;
+            stage_key<C, LO, HI, PT>(kreg, true, false, klo_at(nxt), kslo_at(nxt), khi_at(nxt), kshi_at(nxt), kts_at(nxt), lofs, tid, kam, amax_given);
+            score_part<C, LO, false, PT, PVMX>(qr_lo, qs_lo, klo_at(buf), kslo_at(buf), lofs.score_k, lofs.score_s, kts_at(buf), q_sq, false, BT, qrow_in_tile, lane, c, m, mfloor, l, o, pb,
+                                     [&]() __attribute__((always_inline)) { if (!PT) load_k(jt + 2); });
+            if (PT) load_k(jt + 2);
+            stage_value(nxt);
+            load_v(vreg, vhead, (jt + 2) * BT, S, tid);
             pv(v_at(buf), lofs, lane, o, pb);
             __syncthreads();
         };
@@ -1169,26 +1122,21 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     score_part<C, HI, true, PT, PVMX>(qr_hi, qs_hi, khi_at(buf), kshi_at(buf), score_k_lane<C, HI>(fresh(lane)), lofs.score_s, kts_at(buf), q_sq, diagonal, key_limit, qrow_in_tile, lane, c, m, mfloor, l, o, pb, [] {});
                 }
             }
-            if (jt + 2 < nt) {
-                load_k(jt + 2);
-                load_v(vreg, vhead, (jt + 2) * BT, S, tid);
+            if (TPW > 1 || jt + 2 < nt) {
+                load_k(tile_or_none(jt + 2));
+                load_v(vreg, vhead, tile_or_none(jt + 2) * BT, S, tid);
             }
             if (active) pv(v_at(buf), lofs, lane, o, pb);
             __syncthreads();
         };
-        if constexpr (!GENERAL) {
-            for (int jt = 0; jt < w0; ++jt) main_step(jt);
-            for (int jt = w0; jt < nt; ++jt) band_step(jt);
-        } else {
-            // four runs in a row (each may be empty): sink band tiles, main tiles, band tiles around the diagonal, and
-            // (without the causal mask) the main tiles above the window
-            // ... and a partial last tile, whose missing keys a band step masks
-            const int mend = ragged_tail ? max(w1, nt - 1) : nt;
-            for (int jt = 0; jt < s1; ++jt) band_step(jt);
-            for (int jt = s1; jt < w0; ++jt) main_step(jt);
-            for (int jt = w0; jt < w1; ++jt) band_step(jt);
-            for (int jt = w1; jt < mend; ++jt) main_step(jt);
-            for (int jt = mend; jt < nt; ++jt) band_step(jt);
+        // Runs of main tiles, [s1, w0) and, without the causal mask, [w1, mend) (a partial last tile, whose missing keys are
+        // masked, is a band tile), up to the one before their last; every other tile is a band step.  (One copy of either step:
+        // with a loop per run the code is three times as long and the registers of one run are parked across another.)
+        const int mend = ragged_tail ? max(w1, nt - 1) : nt;
+        for (int jt = 0; jt < nt; ++jt) {
+            const int stop = GENERAL ? (jt < s1 ? jt : jt < w0 ? w0 - 1 : jt < w1 ? jt : mend - 1) : w0 - 1;
+            for (; jt < stop; ++jt) main_step(jt);
+            band_step(jt);
         }
 
         // ---- O / l, transposed through LDS (free after the barrier above) so that every output row leaves as whole
@@ -1295,14 +1243,12 @@ static int launch_variant(const AttnArgs& a, hipStream_t stream)
 {
     using C = Cfg<D, BT, TPW>;
     const int N = (a.S + BT - 1) / BT;
-    if (!GENERAL && N % TPW != 0) return DMA_ERR_UNSUPPORTED_;
     static std::atomic<int> resident_cache{0};
     return launch_resident(dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, C::T, (N + TPW - 1) / TPW, resident_cache, a, stream);
 }
 
-// Alg. 1 as printed (causal, no sink window, sequence a whole number of tile groups) runs the straight-line instance, whose
-// tile loads are unbounded; the sink window, the non-causal variant, the per-token scale and a partial last tile run
-// the general one, whose loads are bounded by buffer resources (unquantized operands have no per-token scale).
+// Alg. 1 as printed (causal, no sink window) runs the simpler instance; the sink window, the non-causal variant and the
+// per-token scale run the general one (unquantized operands have no per-token scale).
 template <int D, int BT, int TPW, int LO, int HI>
 static int launch_instance(const AttnArgs& a, hipStream_t stream)
 {
@@ -1310,7 +1256,7 @@ static int launch_instance(const AttnArgs& a, hipStream_t stream)
         // the MX-format P V is built for the default pair only, without the per-token scale
         if constexpr (LO == FMT_E2M1 && HI == FMT_E4M3_X) {
             if (a.per_token) return DMA_ERR_UNSUPPORTED_;
-            if (a.causal && a.sink == 0 && a.S % (BT * TPW) == 0) return launch_variant<D, BT, TPW, LO, HI, false, false, true>(a, stream);
+            if (a.causal && a.sink == 0) return launch_variant<D, BT, TPW, LO, HI, false, false, true>(a, stream);
             return launch_variant<D, BT, TPW, LO, HI, true, false, true>(a, stream);
         } else {
             return DMA_ERR_UNSUPPORTED_;
@@ -1319,7 +1265,7 @@ static int launch_instance(const AttnArgs& a, hipStream_t stream)
     if constexpr (LO != FMT_BF16) {
         if (a.per_token) return launch_variant<D, BT, TPW, LO, HI, true, true>(a, stream);
     }
-    if (a.causal && a.sink == 0 && a.S % (BT * TPW) == 0) return launch_variant<D, BT, TPW, LO, HI, false, false>(a, stream);
+    if (a.causal && a.sink == 0) return launch_variant<D, BT, TPW, LO, HI, false, false>(a, stream);
     return launch_variant<D, BT, TPW, LO, HI, true, false>(a, stream);
 }
 

@@ -132,12 +132,12 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 #pragma unroll
         for (int r = 0; r < C::CPT; ++r) kam[r] = 0.f;
         auto load_k = [&](int jt) __attribute__((always_inline)) {
-            load_tile<C, true>(kreg, khead, jt * BT, S, tid);
+            load_tile<C>(kreg, khead, jt * BT, S, tid);
             if constexpr (PT) {
                 if (amax_given) load_key_amax<C>(kam, kam_head, jt * BT, S, tid);
             }
         };
-        auto load_v = [&](int jt) __attribute__((always_inline)) { load_tile<C, true>(vreg, vhead, jt * BT, S, tid); };
+        auto load_v = [&](int jt) __attribute__((always_inline)) { load_tile<C>(vreg, vhead, jt * BT, S, tid); };
         auto stage_key = [&](int jt, bool lo_known) __attribute__((always_inline)) {                 // K tile jt from the registers into LDS
             const int buf = jt & 1;
             float inv_sk[C::CPT], bam[C::CPT];
