@@ -292,16 +292,16 @@ inline float longest_list(const AttnArgs& a, int rows, int64_t slots, float step
 
 // Waves per 32 query rows.  A split item takes the same number of steps for half (2) or a quarter (4) of the query rows, and
 // a step does not get shorter in proportion, because every step still quantizes and stages a whole key tile: so the split
-// pays exactly where the chip would otherwise wait for the longest list of items.  One step, in steps of the unsplit
-// kernel, where nothing else limits it (4 heads, S = 900 to 3700; us per step of the unsplit, 2-way and 4-way kernel):
-//   D = 128  MXFP4 tiles 2.72, 1.66, 1.27; unquantized 2.92, 1.89, 1.33; staging-heavy paths: all MXFP8 3.19, 2.33, 1.82,
-//            Step-2 scale 3.46, 2.38, 1.92
-//   D = 64   MXFP4 tiles 0.96, 0.60; all MXFP8 1.07, 0.78; Step-2 scale 1.36, 0.90
-// and an item costs 2 to 2.5 steps (D = 128), 3.7 (D = 64, where two workgroups share a CU).  Measured with the choice that
-// is made (us, 1 / 2 / 4 waves): 4 / 1 heads S = 8192 176 / 114 / 98; S = 16384 338 / 261 / 360; 8 / 2 heads S = 5200
-// 123 / 78 / 99; 32 / 8 heads S = 640 21.3 / 18.3 / 18.7, S = 1800 51 / 45 / 67, S = 2600 69 / 80 / 112.  On the sizes 200 .. 16384
-// with 4 to 32 heads the choice costs at most 3.4 % against the best of the three.
-inline int key_split(const AttnArgs& a, bool staging_heavy)
+// pays exactly where the chip would otherwise wait for the longest list of items.  us per step of the unsplit, 2-way and
+// 4-way kernel where nothing else limits it (4 heads, S = 900 to 3700):
+//   D = 128  MXFP4 tiles 2.40, 1.72, 1.27; all MXFP8 2.94, 2.14, 1.60; unquantized 2.85, 1.89, 1.32; with the Step-2 scale
+//            MXFP4 3.27, 2.39, 1.91, MXFP8 3.81, 2.82, 2.23
+//   D = 64   MXFP4 tiles 0.83, 0.59; all MXFP8 0.96, 0.71; unquantized 0.84, 0.61; Step-2 scale 1.23, 0.90
+// and an item costs 2 to 2.5 unsplit steps (D = 128), 3.7 (D = 64, where two workgroups share a CU).  The choice and what it
+// was made from (us with 1 / 2 / 4 waves): 4 / 1 heads S = 3700 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500
+// 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7,
+// S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads, S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
+inline int key_split(const AttnArgs& a)
 {
     const int64_t cus = compute_units();
     if (cus <= 0 || a.S <= a.tile) return 1;
@@ -310,9 +310,9 @@ inline int key_split(const AttnArgs& a, bool staging_heavy)
     const int64_t items = (int64_t)a.B * a.Hq * ((a.S + 2 * a.tile - 1) / (2 * a.tile));
     if (items > 4 * slots) return 1;                     // the lists are balanced: splitting only costs
     const float whole = longest_list(a, 2 * a.tile, slots, 1.f, d64 ? 3.7f : 2.5f);
-    const float two = longest_list(a, a.tile, slots, d64 ? (staging_heavy ? 0.70f : 0.63f) : staging_heavy ? 0.72f : 0.63f, d64 ? 3.7f : 2.1f);
+    const float two = longest_list(a, a.tile, slots, 0.72f, d64 ? 3.7f : 2.1f);
     if (d64) return two < whole ? 2 : 1;
-    const float four = longest_list(a, a.tile / 2, slots, staging_heavy ? 0.57f : 0.47f, 1.9f);
+    const float four = longest_list(a, a.tile / 2, slots, a.per_token ? 0.58f : 0.53f, 1.9f);
     return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
 }
 
@@ -338,8 +338,7 @@ template <int D, int BT, int LO, int HI>
 static int launch_tile(const AttnArgs& a, hipStream_t stream)
 {
     if (!a.pv_mx) {
-        const bool staging_heavy = LO != FMT_BF16 && (a.per_token || LO != FMT_E2M1);
-        const int ks = key_split(a, staging_heavy);
+        const int ks = key_split(a);
         if (ks == 2) return launch_split<D, BT, 2, LO, HI>(a, stream);
         if constexpr (D == 128) {
             if (ks == 4) return launch_split<D, BT, 4, LO, HI>(a, stream);

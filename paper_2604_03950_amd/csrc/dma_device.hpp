@@ -243,6 +243,33 @@ DMA_DEV v4i quant_dequant8(const float (&x)[8], int code)
     else return quant_dequant8_e4m3(x, code);
 }
 
+// The same from packed bf16 magnitudes and signs (no pre-scale), one dword (two elements) at a time, without a detour
+// through binary32: clamp on the bit patterns (the limit 1.75 * 2^(code + e_max - 127) is a bf16, and patterns of
+// magnitudes order like unsigned integers; lim holds it twice), convert, decode.  mag: the dword without its signs; sc: the
+// scale 2^(code - 127) as mx8_scale gives it, which both converts take.
+DMA_DEV float mx8_scale(int code) { return __int_as_float(max(code << 23, 0x00400000)); }
+template <int FMT>
+DMA_DEV unsigned mx8_limit(int code)
+{
+    const unsigned lim = ((unsigned)code << 7) + ((FMT == FMT_E5M2_X ? 15u : 8u) << 7 | 0x60u);
+    return lim << 16 | lim;
+}
+template <int FMT>
+DMA_DEV int quant_dequant2_bf16(int w, unsigned mag, unsigned lim, float sc)
+{
+    typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+    const unsigned m = __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(v2us, mag), __builtin_bit_cast(v2us, lim)));
+    const v2bf x = __builtin_bit_cast(v2bf, m | ((unsigned)w & 0x80008000u));
+    v2s q = __builtin_bit_cast(v2s, x);                   // the convert fills the lower half, the upper one is not used
+    if constexpr (FMT == FMT_E5M2_X) {
+        q = __builtin_amdgcn_cvt_scalef32_pk_bf8_bf16(q, x, sc, false);
+        return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8((unsigned)__builtin_bit_cast(int, q), sc, false));
+    } else {
+        q = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(q, x, sc, false);
+        return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)__builtin_bit_cast(int, q), sc, false));
+    }
+}
+
 // Unpack a 16-byte chunk of eight bf16 into binary32, optionally pre-scaled (one multiply each).
 template <bool PRESCALE>
 DMA_DEV void unpack8(const v4i& w, float c, float (&x)[8])
