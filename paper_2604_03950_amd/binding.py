@@ -87,7 +87,9 @@ def version() -> int:
 
 
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    """The current HIP stream of the current device.  (torch.cuda.current_stream() builds a Stream object for it: 2.8 us of
+    a call whose kernel may take less, against 0.2.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t: torch.Tensor, dtype, what: str, shape=None) -> int:
@@ -103,16 +105,21 @@ def _dev(t: torch.Tensor, dtype, what: str, shape=None) -> int:
 def dma_mx_quantize(x: torch.Tensor, fmt: int, is_query: bool, codes: torch.Tensor | None = None,
                     scales: torch.Tensor | None = None):
     """x: [..., D] bf16 -> (codes uint8 [..., D] or [..., D/2], scales uint8 [..., D/32])."""
-    D = x.shape[-1]
-    rows = x.numel() // D
+    *lead, D = x.shape
     cb = D // 2 if fmt == FMT_MXFP4_E2M1 else D
+    # x is checked first: what is allocated here needs no check
+    px = _dev(x, torch.bfloat16, "x")
     if codes is None:
-        codes = torch.empty(x.shape[:-1] + (cb,), dtype=torch.uint8, device=x.device)
+        codes = torch.empty((*lead, cb), dtype=torch.uint8, device=x.device)
+        pc = codes.data_ptr()
+    else:
+        pc = _dev(codes, torch.uint8, "codes", (*lead, cb))
     if scales is None:
-        scales = torch.empty(x.shape[:-1] + (D // 32,), dtype=torch.uint8, device=x.device)
-    rc = load().dma_mx_quantize(_dev(x, torch.bfloat16, "x"), rows, D, fmt, int(bool(is_query)),
-                                _dev(codes, torch.uint8, "codes", x.shape[:-1] + (cb,)),
-                                _dev(scales, torch.uint8, "scales", x.shape[:-1] + (D // 32,)), _stream())
+        scales = torch.empty((*lead, D // 32), dtype=torch.uint8, device=x.device)
+        ps = scales.data_ptr()
+    else:
+        ps = _dev(scales, torch.uint8, "scales", (*lead, D // 32))
+    rc = load().dma_mx_quantize(px, x.numel() // D, D, fmt, int(bool(is_query)), pc, ps, _stream())
     if rc:
         raise DmaError(rc, "dma_mx_quantize")
     return codes, scales
@@ -120,15 +127,14 @@ def dma_mx_quantize(x: torch.Tensor, fmt: int, is_query: bool, codes: torch.Tens
 
 def dma_mx_quantize_token(x: torch.Tensor, fmt: int, is_query: bool):
     """dma_mx_quantize with the per-token scale of Alg. 2 Step 2: returns (codes, scales, token_scales float32 [...])."""
-    D = x.shape[-1]
-    rows = x.numel() // D
+    *lead, D = x.shape
     cb = D // 2 if fmt == FMT_MXFP4_E2M1 else D
-    codes = torch.empty(x.shape[:-1] + (cb,), dtype=torch.uint8, device=x.device)
-    scales = torch.empty(x.shape[:-1] + (D // 32,), dtype=torch.uint8, device=x.device)
-    ts = torch.empty(x.shape[:-1], dtype=torch.float32, device=x.device)
-    rc = load().dma_mx_quantize_token(_dev(x, torch.bfloat16, "x"), rows, D, fmt, int(bool(is_query)),
-                                      _dev(codes, torch.uint8, "codes"), _dev(scales, torch.uint8, "scales"),
-                                      _dev(ts, torch.float32, "token_scales"), _stream())
+    px = _dev(x, torch.bfloat16, "x")
+    codes = torch.empty((*lead, cb), dtype=torch.uint8, device=x.device)
+    scales = torch.empty((*lead, D // 32), dtype=torch.uint8, device=x.device)
+    ts = torch.empty(lead, dtype=torch.float32, device=x.device)
+    rc = load().dma_mx_quantize_token(px, x.numel() // D, D, fmt, int(bool(is_query)), codes.data_ptr(), scales.data_ptr(),
+                                      ts.data_ptr(), _stream())
     if rc:
         raise DmaError(rc, "dma_mx_quantize_token")
     return codes, scales, ts
@@ -141,12 +147,16 @@ def dma_mx_group_amax(x: torch.Tensor, is_query: bool, granularity: int, block_r
                       out: torch.Tensor | None = None) -> torch.Tensor:
     """x [..., S, D] bf16 -> float32 [..., S]: for every row the largest magnitude (queries: after the Step-1 pre-scale) of
     the group that shares its Step-2 scale: the row, block_rows rows of its [S, D] matrix, or all of x."""
-    S, D = x.shape[-2], x.shape[-1]
+    shape = x.shape
+    S, D = shape[-2], shape[-1]
     n_mat = x.numel() // (S * D)
+    px = _dev(x, torch.bfloat16, "x")
     if out is None:
-        out = torch.empty(x.shape[:-1], dtype=torch.float32, device=x.device)
-    rc = load().dma_mx_group_amax(_dev(x, torch.bfloat16, "x"), n_mat, S, D, int(bool(is_query)), int(granularity),
-                                  int(block_rows), _dev(out, torch.float32, "amax", x.shape[:-1]), _stream())
+        out = torch.empty(shape[:-1], dtype=torch.float32, device=x.device)
+        po = out.data_ptr()
+    else:
+        po = _dev(out, torch.float32, "amax", shape[:-1])
+    rc = load().dma_mx_group_amax(px, n_mat, S, D, int(bool(is_query)), int(granularity), int(block_rows), po, _stream())
     if rc:
         raise DmaError(rc, "dma_mx_group_amax")
     return out
@@ -154,17 +164,17 @@ def dma_mx_group_amax(x: torch.Tensor, is_query: bool, granularity: int, block_r
 
 def dma_mx_quantize_dual(x: torch.Tensor, is_query: bool, out=None):
     """One read of x -> (codes_lo, scales_lo, codes_hi, scales_hi): MXFP4 E2M1 and MXFP8 E4M3 copies."""
-    D = x.shape[-1]
-    rows = x.numel() // D
+    *lead, D = x.shape
+    px = _dev(x, torch.bfloat16, "x")
     if out is None:
-        mk = lambda n: torch.empty(x.shape[:-1] + (n,), dtype=torch.uint8, device=x.device)
+        mk = lambda n: torch.empty((*lead, n), dtype=torch.uint8, device=x.device)
         out = (mk(D // 2), mk(D // 32), mk(D), mk(D // 32))
-    c4, s4, c8, s8 = out
-    rc = load().dma_mx_quantize_dual(_dev(x, torch.bfloat16, "x"), rows, D, int(bool(is_query)),
-                                     _dev(c4, torch.uint8, "codes_lo", x.shape[:-1] + (D // 2,)),
-                                     _dev(s4, torch.uint8, "scales_lo", x.shape[:-1] + (D // 32,)),
-                                     _dev(c8, torch.uint8, "codes_hi", x.shape[:-1] + (D,)),
-                                     _dev(s8, torch.uint8, "scales_hi", x.shape[:-1] + (D // 32,)), _stream())
+        ptrs = [t.data_ptr() for t in out]
+    else:
+        c4, s4, c8, s8 = out
+        ptrs = [_dev(c4, torch.uint8, "codes_lo", (*lead, D // 2)), _dev(s4, torch.uint8, "scales_lo", (*lead, D // 32)),
+                _dev(c8, torch.uint8, "codes_hi", (*lead, D)), _dev(s8, torch.uint8, "scales_hi", (*lead, D // 32))]
+    rc = load().dma_mx_quantize_dual(px, x.numel() // D, D, int(bool(is_query)), *ptrs, _stream())
     if rc:
         raise DmaError(rc, "dma_mx_quantize_dual")
     return out
@@ -180,14 +190,17 @@ def dma_attn_fwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, *, diag_band
     group_amax: (q_amax [B,Hq,S], k_amax [B,Hkv,S]) float32 from dma_mx_group_amax: with per_token_scale, the Step-2 scale
     of a row comes from its group's maximum instead of its own."""
     B, Hq, S, D = q.shape
-    Hkv = k.shape[1]
-    if k.shape != (B, Hkv, S, D) or v.shape != k.shape:
+    k_shape = k.shape
+    Hkv = k_shape[1]
+    if k_shape != (B, Hkv, S, D) or v.shape != k_shape:
         raise ValueError("k and v must be [B, Hkv, S, D] matching q")
+    pq, pk, pv = _dev(q, torch.bfloat16, "q"), _dev(k, torch.bfloat16, "k"), _dev(v, torch.bfloat16, "v")
     if out is None:
         out = torch.empty((B, Hq, S, D), dtype=torch.float32, device=q.device)
-    args = [_dev(q, torch.bfloat16, "q"), _dev(k, torch.bfloat16, "k"), _dev(v, torch.bfloat16, "v"),
-            _dev(out, torch.float32, "out", (B, Hq, S, D)), B, Hq, Hkv, S, D, int(bool(causal)), int(diag_band_tiles),
-            int(hi_fmt), int(lo_fmt)]
+        po = out.data_ptr()
+    else:
+        po = _dev(out, torch.float32, "out", (B, Hq, S, D))
+    args = [pq, pk, pv, po, B, Hq, Hkv, S, D, int(bool(causal)), int(diag_band_tiles), int(hi_fmt), int(lo_fmt)]
     if tile is None and not fp8_mfma and not sink_tiles and not per_token_scale and not pv_mx and group_amax is None:
         rc = load().dma_attn_fwd(*args, _stream())
     else:
