@@ -350,6 +350,32 @@ DMA_DEV void stage_k(const v4i (&reg)[C::CPT], unsigned kdst, unsigned ksdst, un
         }
         return;
     }
+    if constexpr (FMT == FMT_E2M1 && PT) {
+        // Scaled keys, side by side too; the chunks' elements are unpacked pair by pair, right before their convert.  With
+        // the block maxima on packed bf16 (key_token_scales), 32 / 8 heads, S = 4096 with the tensor scale, its maxima
+        // included, 157.0 -> 153.2 us, S = 8192 526 -> 513, per token 500 -> 499.
+        unsigned w4[C::CPT];
+        int code[C::CPT];
+        float sc[C::CPT];
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) {
+            code[r] = e8m0_code<FMT_E2M1>(__fmul_rn(bam[r], inv_sk[r]));
+            sc[r] = cvt_scale_operand(code[r]);
+            w4[r] = 0;
+        }
+        static_for<4>([&](auto T) __attribute__((always_inline)) {
+            constexpr int t = decltype(T)::value;
+#pragma unroll
+            for (int r = 0; r < C::CPT; ++r)
+                w4[r] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w4[r], __fmul_rn(bf16_lo(reg[r][t]), inv_sk[r]), __fmul_rn(bf16_hi(reg[r][t]), inv_sk[r]), sc[r], t);
+        });
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) {
+            lds_write<int>(ka + r * KPR * STRIDE, (int)w4[r]);
+            lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code[r]);
+        }
+        return;
+    }
     if constexpr ((FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) && !PT) {
         // The same way to the decoded 8-bit formats: 140 vector instructions per tile instead of 208 with a detour through
         // binary32.  S = 16384, 40 / 8 heads, all MXFP8 2481 -> 2427 us; 4 / 1 heads S = 3700 58.6 -> 52.4; D = 64 S = 4096
@@ -379,14 +405,6 @@ DMA_DEV void stage_k(const v4i (&reg)[C::CPT], unsigned kdst, unsigned ksdst, un
     for (int r = 0; r < C::CPT; ++r) {
         if constexpr (FMT == FMT_BF16) {
             lds_write<v4i>(ka + r * KPR * STRIDE, reg[r]);
-        } else if constexpr (FMT == FMT_E2M1) {
-            float x[8];
-            unpack8<false>(reg[r], 1.f, x);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = __fmul_rn(x[e], inv_sk[r]);
-            const int code = e8m0_code<FMT_E2M1>(__fmul_rn(bam[r], inv_sk[r]));
-            lds_write<int>(ka + r * KPR * STRIDE, encode8_e2m1(x, code));
-            lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code);
         } else {
             float x[8];
             unpack8<false>(reg[r], 1.f, x);
@@ -824,16 +842,25 @@ DMA_DEV void key_token_scales(const v4i (&reg)[C::CPT], float (&inv_sk)[C::CPT],
     static_assert(C::CPR % 4 == 0, "a quad of lanes lies inside one key row");
     tid = fresh(tid);
     const int key0 = tid / C::CPR, dc = tid % C::CPR, ql = tid & 3;
+    unsigned bits[C::CPT];
     float am[C::CPT];
 #pragma unroll
-    for (int r = 0; r < C::CPT; ++r) {
-        float x[8];
-        unpack8<false>(reg[r], 1.f, x);
-        bam[r] = quad_max(amax8(x));                     // the lane's MX block (a quad of lanes), for stage_k
-        float row = bam[r];                              // ... and on to the whole row: group_max's remaining steps
-        if constexpr (C::CPR >= 8) row = fmaxf(row, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(row), 0x141, 0xF, 0xF, true)));
-        if constexpr (C::CPR >= 16) row = fmaxf(row, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(row), 0x140, 0xF, 0xF, true)));
-        am[r] = given ? kam[r] : row;
+    for (int r = 0; r < C::CPT; ++r) bits[r] = amax8_bf16_bits(reg[r]);
+    quad_max_u32(bits);                                  // the lane's MX block (a quad of lanes), for stage_k
+#pragma unroll
+    for (int r = 0; r < C::CPT; ++r) bam[r] = am[r] = __int_as_float((int)(bits[r] << 16));
+    if (given) {
+#pragma unroll
+        for (int r = 0; r < C::CPT; ++r) am[r] = kam[r];
+    } else {                                             // ... and on to the whole row: group_max's remaining steps
+        if constexpr (C::CPR >= 8) {
+#pragma unroll
+            for (int r = 0; r < C::CPT; ++r) am[r] = fmaxf(am[r], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(am[r]), 0x141, 0xF, 0xF, true)));
+        }
+        if constexpr (C::CPR >= 16) {
+#pragma unroll
+            for (int r = 0; r < C::CPT; ++r) am[r] = fmaxf(am[r], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(am[r]), 0x140, 0xF, 0xF, true)));
+        }
     }
 #pragma unroll
     for (int base = 0; base < C::CPT; base += 4) {
