@@ -918,7 +918,7 @@ __global__ void __launch_bounds__((BT / 32) * TPW * 64, 2)
 dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, float* __restrict__ out,
                     int B, int Hq, int Hkv, int S, int band, int sink_arg, int causal_arg, float c, int head_block,
-                    const float* __restrict__ q_amax, const float* __restrict__ k_amax)
+                    const float* __restrict__ q_amax, const float* __restrict__ k_amax, int pair_arg)
 {
     // q_amax / k_amax (PT only, both or neither): group maxima per query row [B, Hq, S] / key row [B, Hkv, S] that replace
     // the rows' own maxima in Alg. 2 Step 2 (a coarser granularity of the scale); null: per-token.
@@ -971,25 +971,30 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     lofs.init(tid, lane);
 
     // ---- static schedule.  The grid is one workgroup per CU; a work item is (batch, query head, group of TPW query
-    // tiles) and costs about 2 * grp + 2 key-tile steps.  Items are ranked heaviest first within blocks of
-    // `head_block` query heads and dealt to the workgroups in boustrophedon order (round 0: worker 0, 1, ..., W-1;
+    // tiles), or (pair) (batch, two query heads that share a kv head, query tile): the two logical tiles of the workgroup
+    // are then the same tile of both heads, end on the same key tile and need the same format of every key tile, no half of
+    // the workgroup waits for the other on the last one, and an odd number of tiles needs no filling up.
+    // Items are ranked heaviest first within blocks of
+    // `head_block` query heads (or pairs of them) and dealt to the workgroups in boustrophedon order (round 0: worker 0, 1, ..., W-1;
     // round 1: W-1, ..., 0; ...), which gives every worker the same load to within the lightest items, without
     // atomics and whatever order the hardware starts workgroups in; a block is an even number of rounds (or
     // everything), so the workers move from block to block together and share few K/V streams at a time.  When the
     // (batch, kv head) units divide over the 8 XCDs (workgroup i runs on XCD i % 8), each XCD keeps its own units, so
     // the K/V stream of a unit stays in one L2.
-    // Logical tiles per sequence; the last one may be partial.  When N is not a multiple of TPW the last group is filled up with query tiles that lie wholly past the end of the sequence: their rows load as
-    // zeros, their waves compute zeros on main tiles and nothing on band tiles, and their stores are dropped by the bounds
+    // Logical tiles per sequence; the last one may be partial.  When N is not a multiple of TPW (and heads are not paired) the
+    // last group is filled up with query tiles that lie wholly past the end of the sequence: their rows load as zeros, their waves compute zeros on main tiles and nothing on band tiles, and their stores are dropped by the bounds
     // of the output's buffer resource.
     const int N = (S + BT - 1) / BT;
-    const int NG = (N + TPW - 1) / TPW;  // tile groups
+    const bool pair = TPW == 2 && pair_arg != 0;
+    const int heads_item = pair ? 2 : 1, tstep = pair ? 0 : 1;       // query heads of an item; from one of its tiles to the next
+    const int NG = pair ? N : (N + TPW - 1) / TPW;                     // items per query head or pair
     const int group = Hq / Hkv;
     const int units = B * Hkv;
     const bool by_xcd = (units % 8 == 0) && (gridDim.x % 8 == 0);
     const int xcd = by_xcd ? (int)(blockIdx.x & 7) : 0;
     const int slot = by_xcd ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     const int workers = by_xcd ? (int)(gridDim.x >> 3) : (int)gridDim.x;
-    const int heads_x = by_xcd ? (units / 8) * group : B * Hq;       // query heads ranked together
+    const int heads_x = (by_xcd ? (units / 8) * group : B * Hq) / heads_item;       // query heads or pairs ranked together
     const int items = heads_x * NG;
 
     for (int round = 0;; ++round) {
@@ -997,11 +1002,11 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         if (pos >= items) break;
         const int blk = pos / (head_block * NG), within = pos % (head_block * NG);
         const int grp = NG - 1 - within / head_block;
-        const int hx = blk * head_block + within % head_block;
+        const int hx = (blk * head_block + within % head_block) * heads_item;
         const int unit = by_xcd ? (hx / group) * 8 + xcd : hx / group;
         const int b = unit / Hkv;
         const int hkv = unit % Hkv;
-        const int hq = hkv * group + hx % group;
+        const int hq = hkv * group + hx % group + (pair ? wave / C::WPT : 0);       // of this wave
         const uint16_t* qhead = q + ((int64_t)b * Hq + hq) * S * D;
         const uint16_t* khead = k + ((int64_t)b * Hkv + hkv) * S * D;
         const uint16_t* vhead = v + ((int64_t)b * Hkv + hkv) * S * D;
@@ -1013,8 +1018,8 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // precision iff it lies in the diagonal window, it - jt < band; extensions: the first `sink` key tiles are high
         // precision for every query tile, and without the causal mask every key tile is visited and the window is
         // |it - jt| < band).  Key tiles are visited in ascending order.
-        const int it0 = grp * TPW, last = it0 + TPW - 1;
-        const int it = it0 + wave / C::WPT;
+        const int it0 = pair ? grp : grp * TPW, last = it0 + (TPW - 1) * tstep;
+        const int it = it0 + wave / C::WPT * tstep;
         const int qrow_in_tile = (wave % C::WPT) * 32;
         const int qrow = it * BT + qrow_in_tile;
         // this item visits key tiles [0, nt).  A filled-up tile of the last group (it >= N) has no rows: it asks for no
@@ -1059,8 +1064,9 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     // a filled-up tile needs nothing.  Tested only with the Step-2 scale, where staging a format for its sake
                     // is dear (S = 613, 32 / 8 heads, per token: 25.5 us with the test, 26.2 without); without the scale S = 613
                     // takes 21.8 us as it is, 22.0 with this test and a flag for it
-                    if ((causal && jt > it0 + w) || (PT && it0 + w >= N)) continue;
-                    const bool h = tile_hi(it0 + w, jt);
+                    const int qt = it0 + w * tstep;
+                    if ((causal && jt > qt) || (PT && qt >= N)) continue;
+                    const bool h = tile_hi(qt, jt);
                     any_hi |= h;
                     any_lo |= !h;
                 }
@@ -1248,19 +1254,19 @@ struct Schedule {
     int64_t blocks;
     int workers, heads_x, head_block;
 };
-// items: B * Hq * NG, NG groups of query rows per head; slots: the workgroups the chip holds at once.
-inline Schedule make_schedule(const AttnArgs& a, int NG, int64_t slots)
+// NG items per query head or per heads_item query heads that share a kv head; slots: the workgroups the chip holds at once.
+inline Schedule make_schedule(const AttnArgs& a, int NG, int heads_item, int64_t slots)
 {
     Schedule s;
-    const int64_t items = (int64_t)a.B * a.Hq * NG;
+    const int64_t items = (int64_t)a.B * (a.Hq / heads_item) * NG;
     s.blocks = items < slots ? items : slots;
     // ranking blocks: the fewest heads that fill an even number of rounds, in whole
     // groups of query heads that share a kv head: the workers of a round then walk the SAME K/V stream with items of nearly
     // equal length (on the 32k GQA workload 17 % fewer bytes fetched than with single heads, 0.6 % less time)
-    const int units = a.B * a.Hkv, group = a.Hq / a.Hkv;
+    const int units = a.B * a.Hkv, group = a.Hq / a.Hkv / heads_item;
     const bool by_xcd = (units % 8 == 0) && (s.blocks % 8 == 0);
     s.workers = (int)(by_xcd ? s.blocks / 8 : s.blocks);
-    s.heads_x = by_xcd ? (units / 8) * group : a.B * a.Hq;
+    s.heads_x = (by_xcd ? units / 8 : units) * group;
     s.head_block = s.heads_x;
     for (int hb = group; hb < s.heads_x; hb += group)
         if (s.heads_x % hb == 0 && ((int64_t)hb * NG) % (2 * s.workers) == 0) { s.head_block = hb; break; }
@@ -1271,10 +1277,11 @@ inline Schedule make_schedule(const AttnArgs& a, int NG, int64_t slots)
 // holds at once (one per CU for the D = 128 instances), each walking its share of the work items.  resident_cache: the
 // kernel's resident workgroups per CU, the same on every device of one kind; kept once a query has succeeded (a failed query
 // is repeated by the next call); every writer stores the same value, so several host threads may launch at once.
-template <typename... P>
-static int launch_resident(void (*kernel)(P...), int threads, int NG, std::atomic<int>& resident_cache, const AttnArgs& a, hipStream_t stream)
+template <typename... P, typename... X>
+static int launch_resident(void (*kernel)(P...), int threads, int NG, int heads_item, std::atomic<int>& resident_cache, const AttnArgs& a,
+                           hipStream_t stream, X... extra)
 {
-    const int64_t items = (int64_t)a.B * a.Hq * NG;
+    const int64_t items = (int64_t)a.B * (a.Hq / heads_item) * NG;
     if (items <= 0 || items > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED_;
     const int cus = compute_units();
     if (cus <= 0) return DMA_ERR_HIP_;
@@ -1283,12 +1290,18 @@ static int launch_resident(void (*kernel)(P...), int threads, int NG, std::atomi
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, kernel, threads, 0) != hipSuccess || resident <= 0) return DMA_ERR_HIP_;
         resident_cache.store(resident, std::memory_order_relaxed);
     }
-    const Schedule s = make_schedule(a, NG, (int64_t)cus * resident);
+    const Schedule s = make_schedule(a, NG, heads_item, (int64_t)cus * resident);
     const float c = (float)(1.4426950408889634074 / sqrt((double)a.D));
     return launch(kernel, dim3((unsigned)s.blocks), dim3(threads), stream,
                   (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, a.out, a.B, a.Hq, a.Hkv,
-                  a.S, a.band, a.sink, a.causal, c, s.head_block, a.q_amax, a.k_amax);
+                  a.S, a.band, a.sink, a.causal, c, s.head_block, a.q_amax, a.k_amax, extra...);
 }
+
+// Do the two logical tiles of a workgroup come from two query heads?  Wherever the heads of a kv head divide into pairs: two
+// tiles of one head leave half of the workgroup without work on the item's last key tile and an odd tile count half empty.
+// 32 / 8 heads, us with two tiles of a head and with a tile of two heads: 64 x S = 100 67.0, 47.0; 64 x S = 300 199, 167;
+// 16 x S = 1100 248, 222; S = 2500 61.9, 60.6; S = 8191 415, 407; S = 32768 5807, 5753; D = 64 64 x S = 700 281, 247.
+inline bool pair_heads(const AttnArgs& a) { return (a.Hq / a.Hkv) % 2 == 0; }
 
 template <int D, int BT, int TPW, int LO, int HI, bool GENERAL, bool PT, bool PVMX = false>
 static int launch_variant(const AttnArgs& a, hipStream_t stream)
@@ -1296,7 +1309,9 @@ static int launch_variant(const AttnArgs& a, hipStream_t stream)
     using C = Cfg<D, BT, TPW>;
     const int N = (a.S + BT - 1) / BT;
     static std::atomic<int> resident_cache{0};
-    return launch_resident(dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, C::T, (N + TPW - 1) / TPW, resident_cache, a, stream);
+    const bool pair = TPW == 2 && pair_heads(a);
+    return launch_resident(dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, C::T, pair ? N : (N + TPW - 1) / TPW, pair ? 2 : 1,
+                           resident_cache, a, stream, (int)pair);
 }
 
 // Alg. 1 as printed (causal, no sink window) runs the simpler instance; the sink window, the non-causal variant and the

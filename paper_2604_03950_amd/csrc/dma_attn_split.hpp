@@ -271,10 +271,10 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 // The longest list of items any workgroup is dealt, in steps of the unsplit kernel: `step` per key tile and `item` per item
 // (prologue, epilogue, band tiles).  The heaviest lists are those of the first and the last worker: the first starts with
 // the longest item, the last has two neighbours of the middle.
-inline float longest_list(const AttnArgs& a, int rows, int64_t slots, float step, float item)
+inline float longest_list(const AttnArgs& a, int rows, int heads_item, int64_t slots, float step, float item)
 {
     const int N = (a.S + a.tile - 1) / a.tile, NG = (a.S + rows - 1) / rows;
-    const Schedule s = make_schedule(a, NG, slots);
+    const Schedule s = make_schedule(a, NG, heads_item, slots);
     const int64_t items = (int64_t)s.heads_x * NG, block = (int64_t)s.head_block * NG;
     float longest = 0.f;
     for (int w = 0; w < s.workers; w += s.workers > 1 ? s.workers - 1 : 1) {
@@ -309,10 +309,11 @@ inline int key_split(const AttnArgs& a)
     const int64_t slots = d64 ? 2 * cus : cus;
     const int64_t items = (int64_t)a.B * a.Hq * ((a.S + 2 * a.tile - 1) / (2 * a.tile));
     if (items > 4 * slots) return 1;                     // the lists are balanced: splitting only costs
-    const float whole = longest_list(a, 2 * a.tile, slots, 1.f, d64 ? 3.7f : 2.5f);
-    const float two = longest_list(a, a.tile, slots, 0.72f, d64 ? 3.7f : 2.1f);
+    const bool pair = pair_heads(a);
+    const float whole = longest_list(a, pair ? a.tile : 2 * a.tile, pair ? 2 : 1, slots, 1.f, d64 ? 3.7f : 2.5f);
+    const float two = longest_list(a, a.tile, 1, slots, 0.72f, d64 ? 3.7f : 2.1f);
     if (d64) return two < whole ? 2 : 1;
-    const float four = longest_list(a, a.tile / 2, slots, a.per_token ? 0.58f : 0.53f, 1.9f);
+    const float four = longest_list(a, a.tile / 2, 1, slots, a.per_token ? 0.58f : 0.53f, 1.9f);
     return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
 }
 
@@ -322,7 +323,7 @@ static int launch_split(const AttnArgs& a, hipStream_t stream)
     using C = Cfg<D, BT, 1, KS>;
     constexpr int ROWS = 32 * C::NW / KS;
     static std::atomic<int> resident_cache{0};
-    return launch_resident(dma_attn_split_kernel<D, BT, KS, LO, HI, PT>, C::T, (a.S + ROWS - 1) / ROWS, resident_cache, a, stream);
+    return launch_resident(dma_attn_split_kernel<D, BT, KS, LO, HI, PT>, C::T, (a.S + ROWS - 1) / ROWS, 1, resident_cache, a, stream);
 }
 template <int D, int BT, int KS, int LO, int HI>
 static int launch_split(const AttnArgs& a, hipStream_t stream)
@@ -344,9 +345,10 @@ static int launch_tile(const AttnArgs& a, hipStream_t stream)
             if (ks == 4) return launch_split<D, BT, 4, LO, HI>(a, stream);
         }
     }
-    // two logical tiles per workgroup (256 query rows share each K/V tile); with an odd number of tiles the last
-    // pair is filled up with a tile past the end of the sequence.  One tile per workgroup only for a single tile.
-    if (a.S > BT) return launch_instance<D, BT, 2, LO, HI>(a, stream);
+    // two logical tiles per workgroup (256 query rows share each K/V tile); without a second head to take it from and with
+    // an odd number of tiles the last pair is filled up with a tile past the end of the sequence.  One tile per workgroup
+    // only for a single tile of a single head.
+    if (a.S > BT || pair_heads(a)) return launch_instance<D, BT, 2, LO, HI>(a, stream);
     return launch_instance<D, BT, 1, LO, HI>(a, stream);
 }
 
