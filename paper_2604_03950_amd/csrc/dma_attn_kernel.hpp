@@ -855,11 +855,11 @@ DMA_DEV void key_token_scales(const v4i (&reg)[C::CPT], float (&inv_sk)[C::CPT],
     } else {                                             // ... and on to the whole row: group_max's remaining steps
         if constexpr (C::CPR >= 8) {
 #pragma unroll
-            for (int r = 0; r < C::CPT; ++r) am[r] = fmaxf(am[r], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(am[r]), 0x141, 0xF, 0xF, true)));
+            for (int r = 0; r < C::CPT; ++r) am[r] = half_row_max(am[r]);
         }
         if constexpr (C::CPR >= 16) {
 #pragma unroll
-            for (int r = 0; r < C::CPT; ++r) am[r] = fmaxf(am[r], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(am[r]), 0x140, 0xF, 0xF, true)));
+            for (int r = 0; r < C::CPT; ++r) am[r] = full_row_max(am[r]);
         }
     }
 #pragma unroll

@@ -78,17 +78,24 @@ DMA_DEV float quad_max(float a)
     return fmaxf(a, b);
 }
 
-// max over a group of LANES consecutive lanes (LANES = 4, 8 or 16, group aligned to LANES): quad permutes, then the
-// DPP mirrors of half a row (8 lanes) and of a row (16 lanes).
+// From maxima over 4 lanes to 8 and from 8 to 16: the DPP mirrors of half a row (8 lanes) and of a row (16 lanes); from 16
+// lanes to 32: the rows of a half-wave trade places (v_permlane16_swap).
+DMA_DEV float half_row_max(float a) { return fmaxf(a, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a), 0x141, 0xF, 0xF, true))); }
+DMA_DEV float full_row_max(float a) { return fmaxf(a, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a), 0x140, 0xF, 0xF, true))); }
+DMA_DEV float row_pair_max(float a)
+{
+    const v2u r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// max over a group of LANES consecutive lanes (LANES = 4, 8 or 16, group aligned to LANES).
 template <int LANES>
 DMA_DEV float group_max(float a)
 {
     static_assert(LANES == 4 || LANES == 8 || LANES == 16, "group of 4, 8 or 16 lanes");
     a = quad_max(a);
-    if constexpr (LANES >= 8)
-        a = fmaxf(a, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a), 0x141, 0xF, 0xF, true)));   // row_half_mirror
-    if constexpr (LANES >= 16)
-        a = fmaxf(a, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a), 0x140, 0xF, 0xF, true)));   // row_mirror
+    if constexpr (LANES >= 8) a = half_row_max(a);
+    if constexpr (LANES >= 16) a = full_row_max(a);
     return a;
 }
 

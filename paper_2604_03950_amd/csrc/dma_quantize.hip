@@ -14,14 +14,17 @@ constexpr int QUANT_THREADS = 256;
 constexpr int QUANT_UNROLL = 4;     // chunks per thread
 
 // MODE: 1 = E4M3 only, 2 = E2M1 only, 3 = both (low copy E2M1 + high copy E4M3), 4 = E5M2 only.
-// PER_TOKEN: Alg. 2 Step 2: the row (lanes_per_row = D / 8 consecutive lanes, a power of two <= 64) is multiplied by
-// 2688 / rowmax before the shared scales are formed, and rowmax / 2688 goes to token_scales[row].
+// PER_TOKEN: Alg. 2 Step 2: the row (2^row_shift = D / 8 consecutive lanes, 4 .. 64) is multiplied by 2688 / rowmax before
+// the shared scales are formed, and rowmax / 2688 goes to token_scales[row].  Bound by the same read and writes, and by
+// vector work: the row maximum goes through DPP and lane swaps, the lanes of a quad share the divisions (lane q those of
+// chunk round q), the block maximum is taken before the scaling, and rows are counted with a shift.  32 heads of
+// 8192 x 128 to MXFP4 19.3 -> 13.8 us, to MXFP8 20.0 -> 16.7 (without the token scale 13.9 and 16.7).
 template <int MODE, bool IS_QUERY, bool PER_TOKEN>
 __global__ void __launch_bounds__(QUANT_THREADS)
 mx_quantize_kernel(const v4i* __restrict__ x, int64_t n_chunks, float c,
                    int* __restrict__ codes4, uint8_t* __restrict__ scales4,
                    v2i* __restrict__ codes8, uint8_t* __restrict__ scales8,
-                   float* __restrict__ token_scales, int lanes_per_row)
+                   float* __restrict__ token_scales, int row_shift)
 {
     const int64_t base = ((int64_t)blockIdx.x * QUANT_UNROLL) * QUANT_THREADS + threadIdx.x;
     v4i w[QUANT_UNROLL];
@@ -30,22 +33,59 @@ mx_quantize_kernel(const v4i* __restrict__ x, int64_t n_chunks, float c,
         const int64_t ch = base + (int64_t)u * QUANT_THREADS;
         w[u] = (ch < n_chunks) ? __builtin_nontemporal_load(x + ch) : v4i{0, 0, 0, 0};
     }
+    float bmax[QUANT_UNROLL], inv[QUANT_UNROLL];
+    if constexpr (PER_TOKEN) {
+        static_assert(QUANT_UNROLL == 4, "one chunk round per lane of a quad");
+        float rmax[QUANT_UNROLL];
+#pragma unroll
+        for (int u = 0; u < QUANT_UNROLL; ++u) {
+            float v[8];
+            unpack8<IS_QUERY>(w[u], c, v);
+            bmax[u] = rmax[u] = quad_max(amax8(v));
+        }
+        // row maximum: from the quad to the 8, 16, 32 or 64 lanes of the row (rows never straddle a wave)
+        if (row_shift >= 3) {
+#pragma unroll
+            for (int u = 0; u < QUANT_UNROLL; ++u) rmax[u] = half_row_max(rmax[u]);
+        }
+        if (row_shift >= 4) {
+#pragma unroll
+            for (int u = 0; u < QUANT_UNROLL; ++u) rmax[u] = full_row_max(rmax[u]);
+        }
+        if (row_shift >= 5) {
+#pragma unroll
+            for (int u = 0; u < QUANT_UNROLL; ++u) rmax[u] = row_pair_max(rmax[u]);
+        }
+        if (row_shift >= 6) {
+#pragma unroll
+            for (int u = 0; u < QUANT_UNROLL; ++u) rmax[u] = cross_half_max(rmax[u]);
+        }
+        const int q = threadIdx.x & 3;
+        float s_q, mine;
+        token_scale(q == 0 ? rmax[0] : q == 1 ? rmax[1] : q == 2 ? rmax[2] : rmax[3], s_q, mine);
+        const int m = __float_as_int(mine);
+        inv[0] = __int_as_float(__builtin_amdgcn_mov_dpp(m, 0x00, 0xF, 0xF, true));
+        inv[1] = __int_as_float(__builtin_amdgcn_mov_dpp(m, 0x55, 0xF, 0xF, true));
+        inv[2] = __int_as_float(__builtin_amdgcn_mov_dpp(m, 0xAA, 0xF, 0xF, true));
+        inv[3] = __int_as_float(__builtin_amdgcn_mov_dpp(m, 0xFF, 0xF, 0xF, true));
+        const int64_t mine_ch = base + (int64_t)q * QUANT_THREADS;          // the lane's own chunk of round q
+        if ((threadIdx.x & ((1 << row_shift) - 1)) < 4 && mine_ch < n_chunks) token_scales[mine_ch >> row_shift] = s_q;
+    }
 #pragma unroll
     for (int u = 0; u < QUANT_UNROLL; ++u) {
         const int64_t ch = base + (int64_t)u * QUANT_THREADS;
         float v[8];
         unpack8<IS_QUERY>(w[u], c, v);
+        float amax;
         if constexpr (PER_TOKEN) {
-            // row maximum: quad, then butterfly over the remaining lanes of the row (rows never straddle a wave)
-            float rmax = quad_max(amax8(v));
-            for (int off = 4; off < lanes_per_row; off <<= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off, 64));
-            float s_q, inv;
-            token_scale(rmax, s_q, inv);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) v[t] = __fmul_rn(v[t], inv);
-            if (ch < n_chunks && (ch % lanes_per_row) == 0) token_scales[ch / lanes_per_row] = s_q;
+            for (int t = 0; t < 8; ++t) v[t] = __fmul_rn(v[t], inv[u]);
+            // rounding is monotone: the maximum of the scaled block is the scaled maximum (a factor of 0, of a row with an
+            // infinity, makes every finite element 0)
+            amax = inv[u] == 0.f ? 0.f : __fmul_rn(bmax[u], inv[u]);
+        } else {
+            amax = quad_max(amax8(v));              // every lane of the wave executes the DPP
         }
-        const float amax = quad_max(amax8(v));      // every lane of the wave executes the DPP
         if (ch >= n_chunks) continue;
         const bool writes_scale = (threadIdx.x & 3) == 0;
         if (MODE & 2) {
@@ -78,11 +118,12 @@ static int launch_mode(const void* x, int64_t rows, int D, int is_query, void* c
     const float c = (float)(1.4426950408889634074 / sqrt((double)D));
     const int lpr = D / 8;
     if (PER_TOKEN && (lpr > 64 || (lpr & (lpr - 1)) != 0)) return DMA_ERR_UNSUPPORTED_;
+    const int row_shift = __builtin_ctz((unsigned)lpr);
     if (is_query)
         return launch(mx_quantize_kernel<MODE, true, PER_TOKEN>, dim3((unsigned)blocks), dim3(QUANT_THREADS), stream,
-                      (const v4i*)x, n_chunks, c, (int*)c4, (uint8_t*)s4, (v2i*)c8, (uint8_t*)s8, ts, lpr);
+                      (const v4i*)x, n_chunks, c, (int*)c4, (uint8_t*)s4, (v2i*)c8, (uint8_t*)s8, ts, row_shift);
     return launch(mx_quantize_kernel<MODE, false, PER_TOKEN>, dim3((unsigned)blocks), dim3(QUANT_THREADS), stream,
-                  (const v4i*)x, n_chunks, c, (int*)c4, (uint8_t*)s4, (v2i*)c8, (uint8_t*)s8, ts, lpr);
+                  (const v4i*)x, n_chunks, c, (int*)c4, (uint8_t*)s4, (v2i*)c8, (uint8_t*)s8, ts, row_shift);
 }
 
 // Plain copy, 16 bytes per lane: the reference kernel for calibrating HBM traffic counters.
