@@ -2,9 +2,10 @@
 // online softmax of Sec. 3.2; Q/K quantization of Alg. 2 done in-kernel; options: sink window and
 // per-token scale of Sec. 5.3, non-causal variant of Sec. 4.1).
 //
-// Work split.  A work item is TPW consecutive logical query tiles (B_M = BT rows each) of one
-// (batch, query head); the workgroup that owns it walks the key tiles jt = 0, 1, ... in ascending
-// order, so one K/V tile fetched and quantized once serves TPW * BT query rows.  Each wave owns 32
+// Work split.  A work item is TPW logical query tiles (B_M = BT rows each): consecutive ones of one
+// (batch, query head), or the same one of TPW query heads that share a kv head; the workgroup that owns it walks the
+// key tiles jt = 0, 1, ... in ascending order, so one K/V tile fetched and quantized once serves TPW * BT query rows.
+// (Problems with few items run on the kernel of dma_attn_split.hpp.)  Each wave owns 32
 // query rows of one logical tile `it` and follows Alg. 1 for that tile: key tiles before the
 // diagonal band in the low format (Phase 1), the last `band` tiles up to the diagonal one in the
 // high format (Phase 2), tiles after its diagonal are skipped.  The grid is one resident workgroup
@@ -17,9 +18,10 @@
 //                                     exponentiated S^T accumulators, already in operand layout)
 // so the row maximum / sum need one cross-half exchange and the running state (m, l) is per lane.
 //
-// Pipeline.  K and V of tile jt+2 are in flight from global memory (16 B per lane, coalesced) while
-// tile jt is computed out of LDS buffer jt & 1 and tile jt+1 is quantized (block maximum over a lane
-// quad by DPP, E8M0 scale, hardware scaled converts) into buffer (jt+1) & 1: one barrier per tile.
+// Pipeline.  While tile jt is computed out of LDS buffer jt & 1, tile jt+1 goes from registers into buffer (jt+1) & 1, K
+// quantized on the way (block maximum over a lane quad by DPP, E8M0 scale, hardware scaled converts) at the top of the
+// step and V behind the softmax, and each is requested for tile jt+2 (16 B per lane, coalesced) once its registers are
+// free: one barrier per tile.
 // Two waves per SIMD (the register budget allows no more): the matrix work of one overlaps the vector
 // work of the other, and together they reach the full vector issue rate, which one wave alone does not.
 #pragma once
@@ -1024,11 +1026,9 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int qrow = it * BT + qrow_in_tile;
         // this item visits key tiles [0, nt).  A filled-up tile of the last group (it >= N) has no rows: it asks for no
         // key tile of its own, and its waves compute no band tile (jlast: the last key tile the wave computes as one), so the
-        // other wave of the SIMD has it to itself there.  S = 613, 32 / 8 heads, five tiles: 25.85 us with the step and
-        // the band tiles, 23.04 without the step, 21.79 without both; S = 300: 20.23, 17.13 and 15.74.  One bound per wave
-        // and no test in the main step, because the sizes with an even number of tiles pay for what lives through it (a
-        // flag of its own and a second test in `needs`: 5 VGPRs and up to 36 spilled SGPRs more; S = 2500: 67.9 us before
-        // there was any of this, 68.3 with the flag, 68.05 with the bound).
+        // other wave of the SIMD has it to itself there.  One bound per wave and no test in the main step, because the sizes
+        // with an even number of tiles pay for what lives through it (a flag of its own and a second test in `needs`: 5 VGPRs and
+        // up to 36 spilled SGPRs more).
         const int nt = causal ? min(last + 1, N) : N;
         const int jlast = (TPW > 1 && it >= N) ? -1 : causal ? it : N;
         auto tile_hi = [&](int qt, int jt) __attribute__((always_inline)) {             // does query tile qt compute key tile jt in the high format?
@@ -1062,8 +1062,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 #pragma unroll
                 for (int w = 0; w < TPW; ++w) {
                     // a filled-up tile needs nothing.  Tested only with the Step-2 scale, where staging a format for its sake
-                    // is dear (S = 613, 32 / 8 heads, per token: 25.5 us with the test, 26.2 without); without the scale S = 613
-                    // takes 21.8 us as it is, 22.0 with this test and a flag for it
+                    // is dear (3 % of five tiles per token)
                     const int qt = it0 + w * tstep;
                     if ((causal && jt > qt) || (PT && qt >= N)) continue;
                     const bool h = tile_hi(qt, jt);
