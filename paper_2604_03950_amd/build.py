@@ -12,7 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdma_mi355x.so")
 SOURCES = ["dma_api.hip", "dma_quantize.hip", "dma_attn_fwd.hip", "dma_diag.hip"]
-HEADERS = ["dma_device.hpp", "dma_internal.hpp", "dma_attn_kernel.hpp", "dma_attn_split.hpp", os.path.join("..", "..", "include", "dma.h")]
+HEADERS = ["dma_device.hpp", "dma_plan.hpp", "dma_internal.hpp", "dma_attn_kernel.hpp", "dma_attn_split.hpp",
+           os.path.join("..", "..", "include", "dma.h")]
 # (low, high) format pairs of the fused forward, as product-path ids of dma_device.hpp: dma_attn_inst.hip is compiled
 # once per pair (the list mirrors the declarations in dma_attn_fwd.hip)
 ATTN_PAIRS = [(2, 3), (2, 1), (2, 4), (2, 2), (3, 3), (1, 1), (4, 4), (0, 0)]

@@ -1247,31 +1247,6 @@ inline int compute_units()
     return n;
 }
 
-// The static schedule as the kernels see it: `blocks` workgroups; items ranked in blocks of head_block heads (see the kernel)
-// of heads_x query heads, dealt to `workers` workgroups (those of one XCD when each keeps its own units).
-struct Schedule {
-    int64_t blocks;
-    int workers, heads_x, head_block;
-};
-// NG items per query head or per heads_item query heads that share a kv head; slots: the workgroups the chip holds at once.
-inline Schedule make_schedule(const AttnArgs& a, int NG, int heads_item, int64_t slots)
-{
-    Schedule s;
-    const int64_t items = (int64_t)a.B * (a.Hq / heads_item) * NG;
-    s.blocks = items < slots ? items : slots;
-    // ranking blocks: the fewest heads that fill an even number of rounds, in whole
-    // groups of query heads that share a kv head: the workers of a round then walk the SAME K/V stream with items of nearly
-    // equal length (on the 32k GQA workload 17 % fewer bytes fetched than with single heads, 0.6 % less time)
-    const int units = a.B * a.Hkv, group = a.Hq / a.Hkv / heads_item;
-    const bool by_xcd = (units % 8 == 0) && (s.blocks % 8 == 0);
-    s.workers = (int)(by_xcd ? s.blocks / 8 : s.blocks);
-    s.heads_x = (by_xcd ? units / 8 : units) * group;
-    s.head_block = s.heads_x;
-    for (int hb = group; hb < s.heads_x; hb += group)
-        if (s.heads_x % hb == 0 && ((int64_t)hb * NG) % (2 * s.workers) == 0) { s.head_block = hb; break; }
-    return s;
-}
-
 // Launch a forward kernel whose items are one of NG groups of query rows of one head, on as many workgroups as the chip
 // holds at once (one per CU for the D = 128 instances), each walking its share of the work items.  resident_cache: the
 // kernel's resident workgroups per CU, the same on every device of one kind; kept once a query has succeeded (a failed query
@@ -1295,12 +1270,6 @@ static int launch_resident(void (*kernel)(P...), int threads, int NG, int heads_
                   (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, a.out, a.B, a.Hq, a.Hkv,
                   a.S, a.band, a.sink, a.causal, c, s.head_block, a.q_amax, a.k_amax, extra...);
 }
-
-// Do the two logical tiles of a workgroup come from two query heads?  Wherever the heads of a kv head divide into pairs: two
-// tiles of one head leave half of the workgroup without work on the item's last key tile and an odd tile count half empty.
-// 32 / 8 heads, us with two tiles of a head and with a tile of two heads: 64 x S = 100 67.0, 47.0; 64 x S = 300 199, 167;
-// 16 x S = 1100 248, 222; S = 2500 61.9, 60.6; S = 8191 415, 407; S = 32768 5807, 5753; D = 64 64 x S = 700 281, 247.
-inline bool pair_heads(const AttnArgs& a) { return (a.Hq / a.Hkv) % 2 == 0; }
 
 template <int D, int BT, int TPW, int LO, int HI, bool GENERAL, bool PT, bool PVMX = false>
 static int launch_variant(const AttnArgs& a, hipStream_t stream)

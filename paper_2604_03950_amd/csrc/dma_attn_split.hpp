@@ -266,57 +266,8 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 }
 
 // ---------------------------------------------------------------------------------------------
-// Host side: pick the number of waves that share a tile's keys
+// Host side: launch (the number of waves that share a tile's keys comes from dma_plan.hpp)
 // ---------------------------------------------------------------------------------------------
-// The longest list of items any workgroup is dealt, in steps of the unsplit kernel: `step` per key tile and `item` per item
-// (prologue, epilogue, band tiles).  The heaviest lists are those of the first and the last worker: the first starts with
-// the longest item, the last has two neighbours of the middle.
-inline float longest_list(const AttnArgs& a, int rows, int heads_item, int64_t slots, float step, float item)
-{
-    const int N = (a.S + a.tile - 1) / a.tile, NG = (a.S + rows - 1) / rows;
-    const Schedule s = make_schedule(a, NG, heads_item, slots);
-    const int64_t items = (int64_t)s.heads_x * NG, block = (int64_t)s.head_block * NG;
-    float longest = 0.f;
-    for (int w = 0; w < s.workers; w += s.workers > 1 ? s.workers - 1 : 1) {
-        float sum = 0.f;
-        int64_t pos = w;
-        for (int round = 0; pos < items; ++round, pos = (int64_t)round * s.workers + ((round & 1) ? s.workers - 1 - w : w)) {
-            const int grp = NG - 1 - (int)(pos % block) / s.head_block;
-            const int last_tile = (int)(((int64_t)(grp + 1) * rows - 1) / a.tile);           // of the item's rows
-            sum += item + step * (a.causal ? (last_tile + 1 < N ? last_tile + 1 : N) : N);
-        }
-        longest = sum > longest ? sum : longest;
-    }
-    return longest;
-}
-
-// Waves per 32 query rows.  A split item takes the same number of steps for half (2) or a quarter (4) of the query rows, and
-// a step does not get shorter in proportion, because every step still quantizes and stages a whole key tile: so the split
-// pays exactly where the chip would otherwise wait for the longest list of items.  us per step of the unsplit, 2-way and
-// 4-way kernel where nothing else limits it (4 heads, S = 900 to 3700):
-//   D = 128  MXFP4 tiles 2.40, 1.72, 1.27; all MXFP8 2.94, 2.14, 1.60; unquantized 2.85, 1.89, 1.32; with the Step-2 scale
-//            MXFP4 3.27, 2.39, 1.91, MXFP8 3.81, 2.82, 2.23
-//   D = 64   MXFP4 tiles 0.83, 0.59; all MXFP8 0.96, 0.71; unquantized 0.84, 0.61; Step-2 scale 1.23, 0.90
-// and an item costs 2 to 2.5 unsplit steps (D = 128), 3.7 (D = 64, where two workgroups share a CU).  The choice and what it
-// was made from (us with 1 / 2 / 4 waves): 4 / 1 heads S = 3700 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500
-// 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7,
-// S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads, S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
-inline int key_split(const AttnArgs& a)
-{
-    const int64_t cus = compute_units();
-    if (cus <= 0 || a.S <= a.tile) return 1;
-    const bool d64 = a.D == 64;
-    const int64_t slots = d64 ? 2 * cus : cus;
-    const int64_t items = (int64_t)a.B * a.Hq * ((a.S + 2 * a.tile - 1) / (2 * a.tile));
-    if (items > 4 * slots) return 1;                     // the lists are balanced: splitting only costs
-    const bool pair = pair_heads(a);
-    const float whole = longest_list(a, pair ? a.tile : 2 * a.tile, pair ? 2 : 1, slots, 1.f, d64 ? 3.7f : 2.5f);
-    const float two = longest_list(a, a.tile, 1, slots, 0.72f, d64 ? 3.7f : 2.1f);
-    if (d64) return two < whole ? 2 : 1;
-    const float four = longest_list(a, a.tile / 2, 1, slots, a.per_token ? 0.58f : 0.53f, 1.9f);
-    return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
-}
-
 template <int D, int BT, int KS, int LO, int HI, bool PT>
 static int launch_split(const AttnArgs& a, hipStream_t stream)
 {
@@ -339,7 +290,9 @@ template <int D, int BT, int LO, int HI>
 static int launch_tile(const AttnArgs& a, hipStream_t stream)
 {
     if (!a.pv_mx) {
-        const int ks = key_split(a);
+        const int cus = compute_units();
+        if (cus <= 0) return DMA_ERR_HIP_;
+        const int ks = key_split(a, cus);
         if (ks == 2) return launch_split<D, BT, 2, LO, HI>(a, stream);
         if constexpr (D == 128) {
             if (ks == 4) return launch_split<D, BT, 4, LO, HI>(a, stream);

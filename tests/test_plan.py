@@ -1,0 +1,55 @@
+"""The plan of a forward against a plain reading of the schedule the kernels walk (no GPU needed)."""
+import random
+
+import plan
+
+
+def dealt(B, Hq, Hkv, NG, heads_item, slots, cost):
+    """Sum of cost(group) over the items of every workgroup, dealt as the kernels deal them: ranked heaviest first within
+    blocks of query heads, to the workgroups (of one XCD where the kv heads divide over eight) forwards and backwards in turn."""
+    items = B * (Hq // heads_item) * NG
+    blocks = min(items, slots)
+    units, group = B * Hkv, Hq // Hkv // heads_item
+    by_xcd = units % 8 == 0 and blocks % 8 == 0
+    workers = blocks // 8 if by_xcd else blocks
+    heads = (units // 8 if by_xcd else units) * group
+    block = next((hb for hb in range(group, heads, group) if heads % hb == 0 and hb * NG % (2 * workers) == 0), heads)
+    load = [0.0] * workers
+    for pos in range(heads * NG):
+        r, at = divmod(pos, workers)
+        load[workers - 1 - at if r % 2 else at] += cost(NG - 1 - pos % (block * NG) // block)
+    return load
+
+
+def items_of(S, tile, rows, causal):
+    N = -(-S // tile)
+    tiles = lambda grp: min(((grp + 1) * rows - 1) // tile + 1, N) if causal else N
+    return -(-S // rows), tiles
+
+
+def test_longest_list_is_the_longest():
+    """... over all workgroups, not only the first and the last: those two miss it wherever the last round is partial or
+    a run of items of one length ends inside a round."""
+    rng = random.Random(1)
+    cases = [(1, 40, 8, 487, 128, True, 64, 1, 256), (2, 40, 8, 618, 128, True, 128, 1, 256), (2, 40, 8, 650, 64, True, 64, 1, 512)]
+    for _ in range(400):
+        D = rng.choice([64, 128])
+        Hkv, group = rng.choice([1, 2, 3, 5, 8, 16]), rng.choice([1, 2, 3, 4, 5])
+        pair = group % 2 == 0 and rng.random() < 0.5
+        rows = D if pair else rng.choice([D // 2, D, 2 * D])
+        cases.append((rng.choice([1, 1, 2, 8]), Hkv * group, Hkv, rng.randrange(D + 1, 3000), D, rng.random() < 0.7, rows, 2 if pair else 1,
+                      rng.choice([1, 7, 64, 256, 512, 768])))
+    ends_miss = 0
+    for B, Hq, Hkv, S, D, causal, rows, heads_item, slots in cases:
+        NG, tiles = items_of(S, D, rows, causal)
+        load = dealt(B, Hq, Hkv, NG, heads_item, slots, lambda grp: 1.5 + 0.5 * tiles(grp))        # exact in binary32
+        got = plan.library().longest_list(plan.problem(B, Hq, Hkv, S, D, causal), rows, heads_item, slots, 0.5, 1.5)
+        assert got == max(load), (B, Hq, Hkv, S, D, causal, rows, heads_item, slots)
+        ends_miss += max(load[0], load[-1]) < max(load)
+    assert ends_miss >= 10                     # the cases do hold lists that neither end has
+
+
+def test_split_by_the_longest_list():
+    """40 / 8 heads, S = 487: by the first and the last workgroup four waves looked shorter (4.86 steps) than two (4.98);
+    a workgroup in the middle has 5.39."""
+    assert plan.key_split(plan.problem(1, 40, 8, 487)) == 2
