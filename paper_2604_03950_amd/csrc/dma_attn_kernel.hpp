@@ -1247,61 +1247,78 @@ inline int compute_units()
     return n;
 }
 
+// Resident workgroups of KERNEL per CU, the same on every device of one kind; 0: the query failed.  Kept once a query has
+// succeeded (a failed query is repeated by the next call); every writer stores the same value, so several host threads may
+// launch at once.
+template <auto KERNEL>
+static int resident_workgroups(int threads)
+{
+    static std::atomic<int> cached{0};
+    int n = cached.load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, KERNEL, threads, 0) != hipSuccess || n <= 0) return 0;
+        cached.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 // Launch a forward kernel whose items are one of NG groups of query rows of one head, on as many workgroups as the chip
-// holds at once (one per CU for the D = 128 instances), each walking its share of the work items.  resident_cache: the
-// kernel's resident workgroups per CU, the same on every device of one kind; kept once a query has succeeded (a failed query
-// is repeated by the next call); every writer stores the same value, so several host threads may launch at once.
-template <typename... P, typename... X>
-static int launch_resident(void (*kernel)(P...), int threads, int NG, int heads_item, std::atomic<int>& resident_cache, const AttnArgs& a,
-                           hipStream_t stream, X... extra)
+// holds at once (one per CU for the D = 128 instances), each walking its share of the work items.
+template <auto KERNEL, typename... X>
+static int launch_resident(int threads, int NG, int heads_item, const AttnArgs& a, hipStream_t stream, X... extra)
 {
     const int64_t items = (int64_t)a.B * (a.Hq / heads_item) * NG;
     if (items <= 0 || items > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED_;
-    const int cus = compute_units();
-    if (cus <= 0) return DMA_ERR_HIP_;
-    int resident = resident_cache.load(std::memory_order_relaxed);
-    if (resident == 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, kernel, threads, 0) != hipSuccess || resident <= 0) return DMA_ERR_HIP_;
-        resident_cache.store(resident, std::memory_order_relaxed);
-    }
+    const int cus = compute_units(), resident = resident_workgroups<KERNEL>(threads);
+    if (cus <= 0 || resident <= 0) return DMA_ERR_HIP_;
     const Schedule s = make_schedule(a, NG, heads_item, (int64_t)cus * resident);
     const float c = (float)(1.4426950408889634074 / sqrt((double)a.D));
-    return launch(kernel, dim3((unsigned)s.blocks), dim3(threads), stream,
+    return launch(KERNEL, dim3((unsigned)s.blocks), dim3(threads), stream,
                   (const uint16_t*)a.q, (const uint16_t*)a.k, (const uint16_t*)a.v, a.out, a.B, a.Hq, a.Hkv,
                   a.S, a.band, a.sink, a.causal, c, s.head_block, a.q_amax, a.k_amax, extra...);
 }
 
-template <int D, int BT, int TPW, int LO, int HI, bool GENERAL, bool PT, bool PVMX = false>
-static int launch_variant(const AttnArgs& a, hipStream_t stream)
-{
-    using C = Cfg<D, BT, TPW>;
-    const int N = (a.S + BT - 1) / BT;
-    static std::atomic<int> resident_cache{0};
-    const bool pair = TPW == 2 && pair_heads(a);
-    return launch_resident(dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL, PT, PVMX>, C::T, pair ? N : (N + TPW - 1) / TPW, pair ? 2 : 1,
-                           resident_cache, a, stream, (int)pair);
-}
-
-// Alg. 1 as printed (causal, no sink window) runs the simpler instance; the sink window, the non-causal variant and the
-// per-token scale run the general one (unquantized operands have no per-token scale).
-template <int D, int BT, int TPW, int LO, int HI>
-static int launch_instance(const AttnArgs& a, hipStream_t stream)
+// f(GENERAL, PT, PVMX) for the instance that serves the call: Alg. 1 as printed (causal, no sink window) runs the simpler
+// instance; the sink window, the non-causal variant and the per-token scale run the general one (unquantized operands have no
+// per-token scale).
+template <int LO, int HI, typename F>
+static int with_instance(const AttnArgs& a, F&& f)
 {
     if (a.pv_mx) {
         // the MX-format P V is built for the default pair only, without the per-token scale
         if constexpr (LO == FMT_E2M1 && HI == FMT_E4M3_X) {
             if (a.per_token) return DMA_ERR_UNSUPPORTED_;
-            if (a.causal && a.sink == 0) return launch_variant<D, BT, TPW, LO, HI, false, false, true>(a, stream);
-            return launch_variant<D, BT, TPW, LO, HI, true, false, true>(a, stream);
+            if (a.causal && a.sink == 0) return f(IC<0>{}, IC<0>{}, IC<1>{});
+            return f(IC<1>{}, IC<0>{}, IC<1>{});
         } else {
             return DMA_ERR_UNSUPPORTED_;
         }
     }
     if constexpr (LO != FMT_BF16) {
-        if (a.per_token) return launch_variant<D, BT, TPW, LO, HI, true, true>(a, stream);
+        if (a.per_token) return f(IC<1>{}, IC<1>{}, IC<0>{});
     }
-    if (a.causal && a.sink == 0) return launch_variant<D, BT, TPW, LO, HI, false, false>(a, stream);
-    return launch_variant<D, BT, TPW, LO, HI, true, false>(a, stream);
+    if (a.causal && a.sink == 0) return f(IC<0>{}, IC<0>{}, IC<0>{});
+    return f(IC<1>{}, IC<0>{}, IC<0>{});
+}
+
+template <int D, int BT, int TPW, int LO, int HI>
+static int launch_instance(const AttnArgs& a, hipStream_t stream)
+{
+    return with_instance<LO, HI>(a, [&](auto GENERAL, auto PT, auto PVMX) {
+        const int N = (a.S + BT - 1) / BT;
+        const bool pair = TPW == 2 && pair_heads(a);
+        return launch_resident<dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL != 0, PT != 0, PVMX != 0>>(
+            Cfg<D, BT, TPW>::T, pair ? N : (N + TPW - 1) / TPW, pair ? 2 : 1, a, stream, (int)pair);
+    });
+}
+
+// Resident workgroups per CU of the instance with two tiles per workgroup that would serve the call.
+template <int D, int BT, int LO, int HI>
+static int resident_instance(const AttnArgs& a)
+{
+    return with_instance<LO, HI>(a, [&](auto GENERAL, auto PT, auto PVMX) {
+        return resident_workgroups<dma_attn_fwd_kernel<D, BT, 2, LO, HI, GENERAL != 0, PT != 0, PVMX != 0>>(Cfg<D, BT, 2>::T);
+    });
 }
 
 }  // namespace dma

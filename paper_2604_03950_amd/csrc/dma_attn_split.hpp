@@ -268,33 +268,43 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 // ---------------------------------------------------------------------------------------------
 // Host side: launch (the number of waves that share a tile's keys comes from dma_plan.hpp)
 // ---------------------------------------------------------------------------------------------
-template <int D, int BT, int KS, int LO, int HI, bool PT>
-static int launch_split(const AttnArgs& a, hipStream_t stream)
+// f(PT) for the instance that serves the call (unquantized operands have no per-token scale).
+template <int LO, typename F>
+static int with_split(const AttnArgs& a, F&& f)
 {
-    using C = Cfg<D, BT, 1, KS>;
-    constexpr int ROWS = 32 * C::NW / KS;
-    static std::atomic<int> resident_cache{0};
-    return launch_resident(dma_attn_split_kernel<D, BT, KS, LO, HI, PT>, C::T, (a.S + ROWS - 1) / ROWS, 1, resident_cache, a, stream);
+    if constexpr (LO != FMT_BF16) {
+        if (a.per_token) return f(IC<1>{});
+    }
+    return f(IC<0>{});
 }
 template <int D, int BT, int KS, int LO, int HI>
 static int launch_split(const AttnArgs& a, hipStream_t stream)
 {
-    if constexpr (LO != FMT_BF16) {                      // unquantized operands have no per-token scale
-        if (a.per_token) return launch_split<D, BT, KS, LO, HI, true>(a, stream);
-    }
-    return launch_split<D, BT, KS, LO, HI, false>(a, stream);
+    using C = Cfg<D, BT, 1, KS>;
+    constexpr int ROWS = 32 * C::NW / KS;
+    return with_split<LO>(a, [&](auto PT) {
+        return launch_resident<dma_attn_split_kernel<D, BT, KS, LO, HI, PT != 0>>(C::T, (a.S + ROWS - 1) / ROWS, 1, a, stream);
+    });
+}
+template <int D, int BT, int KS, int LO, int HI>
+static int resident_split(const AttnArgs& a)
+{
+    return with_split<LO>(a, [&](auto PT) { return resident_workgroups<dma_attn_split_kernel<D, BT, KS, LO, HI, PT != 0>>(Cfg<D, BT, 1, KS>::T); });
 }
 
 // Split, or the instance of the unsplit kernel with two logical tiles per workgroup (one for a single-tile sequence).
 template <int D, int BT, int LO, int HI>
 static int launch_tile(const AttnArgs& a, hipStream_t stream)
 {
-    if (!a.pv_mx) {
-        const int cus = compute_units();
-        if (cus <= 0) return DMA_ERR_HIP_;
-        const int ks = key_split(a, cus);
+    constexpr bool FOUR = D == 128;
+    if (!a.pv_mx && a.S > BT) {
+        const int cus = compute_units(), r1 = resident_instance<D, BT, LO, HI>(a), r2 = resident_split<D, BT, 2, LO, HI>(a);
+        int r4 = r2;
+        if constexpr (FOUR) r4 = resident_split<D, BT, 4, LO, HI>(a);
+        if (cus <= 0 || r1 <= 0 || r2 <= 0 || r4 <= 0) return DMA_ERR_HIP_;
+        const int ks = key_split(a, cus, r1, r2, r4);
         if (ks == 2) return launch_split<D, BT, 2, LO, HI>(a, stream);
-        if constexpr (D == 128) {
+        if constexpr (FOUR) {
             if (ks == 4) return launch_split<D, BT, 4, LO, HI>(a, stream);
         }
     }

@@ -54,23 +54,41 @@ inline Schedule make_schedule(const AttnArgs& a, int NG, int heads_item, int64_t
 // 16 x S = 1100 248, 222; S = 2500 61.9, 60.6; S = 8191 415, 407; S = 32768 5807, 5753; D = 64 64 x S = 700 281, 247.
 inline bool pair_heads(const AttnArgs& a) { return (a.Hq / a.Hkv) % 2 == 0; }
 
-// The longest list of items any workgroup is dealt, in steps of the unsplit kernel: `step` per key tile and `item` per item
-// (prologue, epilogue, band tiles).  Every ranking block is dealt the same way (it is an even number of rounds, or the only
-// block), so the lists of one block are added up, a run of items of one length at a time: the workers of a run inside one
-// round are consecutive, and a run costs two additions.  (Neither the first nor the last worker need have the longest list:
-// 40 / 8 heads of S = 487 in items of 64 rows, a worker in the middle has a key tile more than either.)
+// What a launch has its workgroups walk, in steps of the unsplit kernel (`step` per key tile and `item` per item: prologue,
+// epilogue, band tiles): the longest list of items any of them is dealt, and the work of a compute unit.
+struct Load {
+    float longest, cu;
+};
+// Every ranking block is dealt the same way (it is an even number of rounds, or the only block), so the lists of one block are
+// added up, a run of items of one length at a time: the workers of a run inside one round are consecutive, and a run costs
+// two additions.  (Neither the first nor the last worker need have the longest list: 40 / 8 heads of S = 487 in items of 64
+// rows, a worker in the middle has a key tile more than either.)
+// resident: the workgroups a CU holds at once, as the launch has them.
 constexpr int MAX_WORKERS = 2048;                    // 256 CUs with eight workgroups each
-inline float longest_list(const AttnArgs& a, int rows, int heads_item, int64_t slots, float step, float item)
+inline Load dealt_load(const AttnArgs& a, int rows, int heads_item, int64_t cus, int resident, float step, float item)
 {
     const int N = (a.S + a.tile - 1) / a.tile, NG = (a.S + rows - 1) / rows;
-    const Schedule s = make_schedule(a, NG, heads_item, slots);
-    if ((int64_t)s.heads_x * NG <= s.workers) return item + step * (float)N;                   // one item each
+    const Schedule s = make_schedule(a, NG, heads_item, cus * resident);
+    auto tiles_of = [&](int grp) {
+        const int last_tile = ((grp + 1) * rows - 1) / a.tile;                                    // of the item's rows
+        return a.causal ? (last_tile + 1 < N ? last_tile + 1 : N) : N;
+    };
+    Load load;
+    int64_t sum = 0;                                     // key tiles of all items of a head
+    for (int grp = 0; grp < NG; ++grp) sum += tiles_of(grp);
+    const float total = (float)((int64_t)a.B * (a.Hq / heads_item)) * (step * (float)sum + item * (float)NG);
+    // The workgroups of a CU: with the causal mask lists of all lengths meet, so a CU has its share of the whole; without it
+    // all lists are alike, and some CUs have a workgroup more than others.
+    load.cu = a.causal ? total / (float)cus : total / (float)s.blocks * (float)((s.blocks + cus - 1) / cus);
+    if ((int64_t)s.heads_x * NG <= s.workers) {                                                  // one item each
+        load.longest = item + step * (float)N;
+        return load;
+    }
     int tiles[MAX_WORKERS + 1], count[MAX_WORKERS + 1];                          // by worker: change from the worker before
     for (int w = 0; w <= s.workers; ++w) tiles[w] = count[w] = 0;
     int round = 0, at = 0;                               // of the next item
     for (int grp = NG - 1; grp >= 0; --grp) {
-        const int last_tile = ((grp + 1) * rows - 1) / a.tile;                                    // of the item's rows
-        const int n = a.causal ? (last_tile + 1 < N ? last_tile + 1 : N) : N;
+        const int n = tiles_of(grp);
         for (int left = s.head_block; left > 0;) {
             const int len = left < s.workers - at ? left : s.workers - at;
             const int first = (round & 1) ? s.workers - at - len : at;
@@ -83,10 +101,11 @@ inline float longest_list(const AttnArgs& a, int rows, int heads_item, int64_t s
     float longest = 0.f;
     for (int w = 0, t = 0, c = 0; w < s.workers; ++w) {
         t += tiles[w], c += count[w];
-        const float sum = step * (float)t + item * (float)c;
-        longest = sum > longest ? sum : longest;
+        const float of_w = step * (float)t + item * (float)c;
+        longest = of_w > longest ? of_w : longest;
     }
-    return longest * (float)(s.heads_x / s.head_block);
+    load.longest = longest * (float)(s.heads_x / s.head_block);
+    return load;
 }
 
 // Waves per 32 query rows.  A split item takes the same number of steps for half (2) or a quarter (4) of the query rows, and
@@ -96,22 +115,35 @@ inline float longest_list(const AttnArgs& a, int rows, int heads_item, int64_t s
 //   D = 128  MXFP4 tiles 2.40, 1.72, 1.27; all MXFP8 2.94, 2.14, 1.60; unquantized 2.85, 1.89, 1.32; with the Step-2 scale
 //            MXFP4 3.27, 2.39, 1.91, MXFP8 3.81, 2.82, 2.23
 //   D = 64   MXFP4 tiles 0.83, 0.59; all MXFP8 0.96, 0.71; unquantized 0.84, 0.61; Step-2 scale 1.23, 0.90
-// and an item costs 2 to 2.5 unsplit steps (D = 128), 3.7 (D = 64, where two workgroups share a CU).  The choice and what it
-// was made from (us with 1 / 2 / 4 waves): 4 / 1 heads S = 3700 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500
-// 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7,
-// S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads, S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
-inline int key_split(const AttnArgs& a, int64_t cus)
+// A CU holds one workgroup at D = 128 and three or four at D = 64 (the occupancy that the launch uses): there a step
+// takes longer the more of them share the CU, by CROWD of the work of the others.  us with 1 / 2 / 4 waves: 4 / 1 heads S = 3700
+// 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200
+// 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7, S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads,
+// S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
+// The D = 64 costs below are the ones whose choice loses least on 1220 problems timed with and without the split (six forms:
+// default, all MXFP8, all MXFP4, unquantized, per-token scale, no mask; 2 to 128 heads, S up to 8200): against the better
+// one of each problem 0.15 % on average, and no call more than 5 % slower than unsplit; a rule that counted two workgroups per
+// CU lost 0.26 % and made calls up to 13 % slower.
+constexpr float CROWD = 0.35f;
+inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident2, int resident4)
 {
     if (a.S <= a.tile) return 1;
     const bool d64 = a.D == 64;
-    const int64_t slots = d64 ? 2 * cus : cus;
     const int64_t items = (int64_t)a.B * a.Hq * ((a.S + 2 * a.tile - 1) / (2 * a.tile));
-    if (items > 4 * slots || slots > MAX_WORKERS) return 1;      // the lists are balanced: splitting only costs
+    if (items > 3 * cus) return 1;         // the lists are balanced: splitting only costs (it gained 1 % or more on 2 of 647 such problems)
+    const int most = resident1 > resident2 ? (resident1 > resident4 ? resident1 : resident4) : (resident2 > resident4 ? resident2 : resident4);
+    if (cus * most > MAX_WORKERS) return 1;
+    auto cost = [&](int rows, int heads_item, int resident, float step, float item) {
+        const Load l = dealt_load(a, rows, heads_item, cus, resident, step, item);
+        return l.longest + CROWD * (l.cu > l.longest ? l.cu - l.longest : 0.f);
+    };
     const bool pair = pair_heads(a);
-    const float whole = longest_list(a, pair ? a.tile : 2 * a.tile, pair ? 2 : 1, slots, 1.f, d64 ? 3.7f : 2.5f);
-    const float two = longest_list(a, a.tile, 1, slots, 0.72f, d64 ? 3.7f : 2.1f);
-    if (d64) return two < whole ? 2 : 1;
-    const float four = longest_list(a, a.tile / 2, 1, slots, a.per_token ? 0.58f : 0.53f, 1.9f);
+    const float whole = cost(pair ? a.tile : 2 * a.tile, pair ? 2 : 1, resident1, 1.f, 2.5f);
+    if (d64) {                                           // 1.25: of a split launch beside its lists, fitted with the other costs
+        return 1.25f + cost(a.tile, 1, resident2, 0.75f, 1.5f) < whole ? 2 : 1;
+    }
+    const float two = cost(a.tile, 1, resident2, 0.72f, 2.1f);
+    const float four = cost(a.tile / 2, 1, resident4, a.per_token ? 0.58f : 0.53f, 1.9f);
     return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
 }
 

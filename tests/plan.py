@@ -16,11 +16,13 @@ static dma::AttnArgs args(const int* p)
     a.B = p[0]; a.Hq = p[1]; a.Hkv = p[2]; a.S = p[3]; a.D = p[4]; a.tile = p[4]; a.causal = p[5]; a.lo_fmt = p[6]; a.per_token = p[7];
     return a;
 }
-extern "C" float longest_list(const int* p, int rows, int heads_item, int slots, float step, float item)
+extern "C" void dealt_load(const int* p, int rows, int heads_item, int cus, int resident, float step, float item, float* out)
 {
-    return dma::longest_list(args(p), rows, heads_item, slots, step, item);
+    const dma::Load l = dma::dealt_load(args(p), rows, heads_item, cus, resident, step, item);
+    out[0] = l.longest;
+    out[1] = l.cu;
 }
-extern "C" int key_split(const int* p, int cus) { return dma::key_split(args(p), cus); }
+extern "C" int key_split(const int* p, int cus, const int* resident) { return dma::key_split(args(p), cus, resident[0], resident[1], resident[2]); }
 """
 
 
@@ -31,8 +33,7 @@ def library():
         subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", B.CSRC, "-x", "c++", "-", "-o", so],
                        input=SHIM, text=True, check=True)
         lib = ctypes.CDLL(so)
-    lib.longest_list.restype = ctypes.c_float
-    lib.longest_list.argtypes = [ctypes.POINTER(ctypes.c_int), ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_float, ctypes.c_float]
+    lib.dealt_load.argtypes = [ctypes.POINTER(ctypes.c_int)] + 4 * [ctypes.c_int] + 2 * [ctypes.c_float] + [ctypes.POINTER(ctypes.c_float)]
     return lib
 
 
@@ -41,6 +42,23 @@ def problem(B, Hq, Hkv, S, D=128, causal=True, lo=2, per_token=False):
     return (ctypes.c_int * 8)(B, Hq, Hkv, S, D, int(causal), lo, int(per_token))
 
 
-def key_split(p, cus=256):
+def dealt_load(p, rows, heads_item, cus, resident, step, item):
+    """(longest list of a workgroup, work of a compute unit)."""
+    out = (ctypes.c_float * 2)()
+    library().dealt_load(p, rows, heads_item, cus, resident, step, item, out)
+    return tuple(out)
+
+
+def resident(D, lo, hi, per_token=False):
+    """Workgroups per CU of the unsplit kernel and of the ones that split keys over two and four waves (lo, hi: product-path
+    ids): what the launch asks the runtime for, here as the compiler reports it (test_isa.py holds it against the generated code)."""
+    if D == 128:
+        return 1, 1, 1                     # more than half of a CU's LDS each
+    if lo != hi and hi != 1:               # the decoded 8-bit keys beside the MXFP4 ones: 42 KB of LDS
+        return 3, 3, 3
+    return (3 if lo != hi or (per_token and lo > 2) else 4), 4, 4
+
+
+def key_split(p, hi=3, cus=256):
     """Waves that share 32 query rows: 1, 2 or 4."""
-    return library().key_split(p, cus)
+    return library().key_split(p, cus, (ctypes.c_int * 3)(*resident(p[4], p[6], hi, bool(p[7]))))

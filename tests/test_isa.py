@@ -6,23 +6,45 @@ tests at the time); this test pins the generated code: every group of four conve
 different source registers.  (The compiler is the image's; the check guards edits of the source.)
 The same listing must hold no packed binary32 arithmetic: the library is built with those forms switched off.
 """
+import functools
 import os
 import re
 import subprocess
+import tempfile
 
 import pytest
 
+import plan
 from paper_2604_03950_amd import build as B
 
 
-@pytest.mark.parametrize("lo,hi", [(2, 3), (2, 1), (2, 4), (2, 2)])      # every pair whose low format is MXFP4
-def test_fp4_convert_groups_read_four_registers(tmp_path, lo, hi):
-    out = tmp_path / f"inst_{lo}_{hi}.s"
+@functools.cache
+def listing(lo, hi):
+    """Generated code of one pair of formats."""
     flags = [f for f in B.HIPCC_FLAGS if f != "-fPIC"]
-    cmd = ["hipcc"] + flags + [f"-DDMA_LO={lo}", f"-DDMA_HI={hi}", "-S", "--cuda-device-only", "-o", str(out),
-                              os.path.join(B.CSRC, "dma_attn_inst.hip")]
-    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
-    text = open(out).read()
+    with tempfile.TemporaryDirectory() as d:
+        out = os.path.join(d, "inst.s")
+        subprocess.run(["hipcc"] + flags + [f"-DDMA_LO={lo}", f"-DDMA_HI={hi}", "-S", "--cuda-device-only", "-o", out,
+                                            os.path.join(B.CSRC, "dma_attn_inst.hip")],
+                       check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+        return open(out).read()
+
+
+def resources(lo, hi, kernel):
+    """What the instances of a kernel hold, by their template arguments."""
+    counts = {}
+    for block in re.split(r"(?=- \.agpr_count)", listing(lo, hi)):
+        name = re.search(rf"\.name:\s+(_ZN3dma\d+{kernel}I\S+)", block)
+        if name:
+            key = tuple(int(n) for n in re.findall(r"L[ib](\d+)E", name.group(1)))
+            counts[key] = {f: int(re.search(rf"\.{f}:\s+(\d+)", block).group(1))
+                           for f in ("vgpr_count", "vgpr_spill_count", "sgpr_spill_count", "group_segment_fixed_size", "max_flat_workgroup_size")}
+    return counts
+
+
+@pytest.mark.parametrize("lo,hi", [(2, 3), (2, 1), (2, 4), (2, 2)])      # every pair whose low format is MXFP4
+def test_fp4_convert_groups_read_four_registers(lo, hi):
+    text = listing(lo, hi)
     # the build flags keep the packed binary32 add / multiply / fused multiply-add forms out of the generated code
     assert not re.search(r"\bv_pk_(add|mul|fma)_f32\b", text)
     lines = [ln.strip() for ln in text.splitlines() if "v_cvt_scalef32_pk_fp4_bf16" in ln]
@@ -45,24 +67,13 @@ def test_fp4_convert_groups_read_four_registers(tmp_path, lo, hi):
     assert not open_groups and n_groups == len(lines) // 4
 
 
-def test_general_instances_keep_their_registers(tmp_path):
+def test_general_instances_keep_their_registers():
     """What the GENERAL instances of the default pair hold in registers.  A value that lives through the tile loops for the
     sake of a rare shape (the filled-up tile of an odd number of tiles) is paid for by every ragged length: in spilled
     scalar registers, which are moved to and from vector lanes, and in vector registers.  Each limit lies between the
     count with one bound per wave (247 VGPRs; 31, 61, 116, 15, 28 spilled SGPRs) and with a flag and a second test
     beside it (252; 36, 93, 143, 30, 35)."""
-    out = tmp_path / "inst_2_3.s"
-    flags = [f for f in B.HIPCC_FLAGS if f != "-fPIC"]
-    subprocess.run(["hipcc"] + flags + ["-DDMA_LO=2", "-DDMA_HI=3", "-S", "--cuda-device-only", "-o", str(out),
-                                        os.path.join(B.CSRC, "dma_attn_inst.hip")],
-                   check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
-    counts = {}
-    for block in re.split(r"(?=- \.agpr_count)", open(out).read()):
-        name = re.search(r"\.name:\s+(_ZN3dma19dma_attn_fwd_kernel\S+)", block)
-        if name:
-            key = tuple(int(n) for n in re.findall(r"L[ib](\d+)E", name.group(1)))
-            counts[key] = {f: int(re.search(rf"\.{f}:\s+(\d+)", block).group(1))
-                           for f in ("vgpr_count", "vgpr_spill_count", "sgpr_spill_count")}
+    counts = resources(2, 3, "dma_attn_fwd_kernel")
     # (D, tile, tiles per workgroup, low, high, general, per-token scale, MX-format P V): most spilled SGPRs
     limits = {(128, 128, 2, 2, 3, 1, 0, 0): 33, (128, 128, 2, 2, 3, 1, 0, 1): 75, (128, 128, 1, 2, 3, 1, 0, 0): 125,
               (64, 64, 2, 2, 3, 1, 0, 0): 22, (64, 64, 1, 2, 3, 1, 0, 0): 31}
@@ -72,3 +83,22 @@ def test_general_instances_keep_their_registers(tmp_path):
     # only the MX-format P V spills vector registers
     for key, c in counts.items():
         assert key[7] == 1 or c["vgpr_spill_count"] == 0, (key, c)
+
+
+@pytest.mark.parametrize("lo,hi", B.ATTN_PAIRS)
+def test_resident_workgroups(lo, hi):
+    """Workgroups of the forward kernels that share a CU (512 registers per lane and SIMD in steps of 8, 160 KB of LDS in steps
+    of 1280 bytes): the table the tests of the split rule use."""
+    def fits(c):
+        waves = c["max_flat_workgroup_size"] // 64
+        return min(512 // (-(-c["vgpr_count"] // 8) * 8) * 4 // waves, 160 * 1024 // (-(-c["group_segment_fixed_size"] // 1280) * 1280))
+
+    seen = 0
+    for (D, _, tpw, _, _, general, per_token, pv_mx), c in resources(lo, hi, "dma_attn_fwd_kernel").items():
+        if tpw == 2 and not pv_mx:
+            assert fits(c) == plan.resident(D, lo, hi, per_token)[0], (D, general, per_token, c)
+            seen += 1
+    for (D, _, ks, _, _, per_token), c in resources(lo, hi, "dma_attn_split_kernel").items():
+        assert fits(c) == plan.resident(D, lo, hi, per_token)[{2: 1, 4: 2}[ks]], (D, ks, per_token, c)
+        seen += 1
+    assert seen >= 7

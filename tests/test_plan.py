@@ -1,6 +1,8 @@
 """The plan of a forward against a plain reading of the schedule the kernels walk (no GPU needed)."""
 import random
 
+import pytest
+
 import plan
 
 
@@ -27,24 +29,29 @@ def items_of(S, tile, rows, causal):
     return -(-S // rows), tiles
 
 
-def test_longest_list_is_the_longest():
-    """... over all workgroups, not only the first and the last: those two miss it wherever the last round is partial or
-    a run of items of one length ends inside a round."""
+def test_dealt_load():
+    """The longest list is the longest over all workgroups, not only the first and the last: those two miss it wherever the last
+    round is partial or a run of items of one length ends inside a round.  The work of a CU: an even share of everything with
+    the mask, the lists of as many workgroups as the fullest CU holds without it."""
     rng = random.Random(1)
-    cases = [(1, 40, 8, 487, 128, True, 64, 1, 256), (2, 40, 8, 618, 128, True, 128, 1, 256), (2, 40, 8, 650, 64, True, 64, 1, 512)]
+    cases = [(1, 40, 8, 487, 128, True, 64, 1, 256, 1), (2, 40, 8, 618, 128, True, 128, 1, 256, 1), (2, 40, 8, 650, 64, True, 64, 1, 256, 2)]
     for _ in range(400):
         D = rng.choice([64, 128])
         Hkv, group = rng.choice([1, 2, 3, 5, 8, 16]), rng.choice([1, 2, 3, 4, 5])
         pair = group % 2 == 0 and rng.random() < 0.5
         rows = D if pair else rng.choice([D // 2, D, 2 * D])
         cases.append((rng.choice([1, 1, 2, 8]), Hkv * group, Hkv, rng.randrange(D + 1, 3000), D, rng.random() < 0.7, rows, 2 if pair else 1,
-                      rng.choice([1, 7, 64, 256, 512, 768])))
+                      rng.choice([1, 7, 64, 256]), rng.choice([1, 2, 3, 4])))
     ends_miss = 0
-    for B, Hq, Hkv, S, D, causal, rows, heads_item, slots in cases:
+    for B, Hq, Hkv, S, D, causal, rows, heads_item, cus, resident in cases:
         NG, tiles = items_of(S, D, rows, causal)
-        load = dealt(B, Hq, Hkv, NG, heads_item, slots, lambda grp: 1.5 + 0.5 * tiles(grp))        # exact in binary32
-        got = plan.library().longest_list(plan.problem(B, Hq, Hkv, S, D, causal), rows, heads_item, slots, 0.5, 1.5)
-        assert got == max(load), (B, Hq, Hkv, S, D, causal, rows, heads_item, slots)
+        load = dealt(B, Hq, Hkv, NG, heads_item, cus * resident, lambda grp: 1.5 + 0.5 * tiles(grp))        # exact in binary32
+        what = (B, Hq, Hkv, S, D, causal, rows, heads_item, cus, resident)
+        longest, cu = plan.dealt_load(plan.problem(B, Hq, Hkv, S, D, causal), rows, heads_item, cus, resident, 0.5, 1.5)
+        assert longest == max(load), what
+        total = sum(1.5 + 0.5 * tiles(grp) for grp in range(NG)) * B * (Hq // heads_item)
+        blocks = min(B * (Hq // heads_item) * NG, cus * resident)
+        assert cu == pytest.approx(total / cus if causal else total / blocks * -(-blocks // cus), rel=1e-6), what
         ends_miss += max(load[0], load[-1]) < max(load)
     assert ends_miss >= 10                     # the cases do hold lists that neither end has
 
@@ -53,3 +60,15 @@ def test_split_by_the_longest_list():
     """40 / 8 heads, S = 487: by the first and the last workgroup four waves looked shorter (4.86 steps) than two (4.98);
     a workgroup in the middle has 5.39."""
     assert plan.key_split(plan.problem(1, 40, 8, 487)) == 2
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,causal,lo,hi,split", [
+    (8, 2, 1, 4290, True, 2, 3, 1),          # 64.5 us unsplit, 72.8 split
+    (3, 5, 1, 4565, True, 3, 3, 1),          # 77.8, 87.0
+    (1, 8, 2, 2600, False, 2, 3, 1),         # 40.9, 43.0
+    (1, 4, 1, 3700, True, 2, 3, 2),
+    (1, 2, 2, 256, True, 2, 3, 2),
+])
+def test_split_at_the_occupancy_of_the_launch(B, Hq, Hkv, S, causal, lo, hi, split):
+    """D = 64: three or four workgroups share a CU.  Counted as two, the rule split calls that the split makes slower."""
+    assert plan.key_split(plan.problem(B, Hq, Hkv, S, 64, causal, lo), hi) == split
