@@ -120,10 +120,10 @@ inline Load dealt_load(const AttnArgs& a, int rows, int heads_item, int64_t cus,
 // 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200
 // 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7, S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads,
 // S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
-// The D = 64 costs below are the ones whose choice loses least on 1220 problems timed with and without the split (six forms:
-// default, all MXFP8, all MXFP4, unquantized, per-token scale, no mask; 2 to 128 heads, S up to 8200): against the better
-// one of each problem 0.15 % on average, and no call more than 5 % slower than unsplit; a rule that counted two workgroups per
-// CU lost 0.26 % and made calls up to 13 % slower.
+// The costs below are the ones whose choice loses least on 2274 problems timed with every split (six forms: default, all
+// MXFP8, all MXFP4, unquantized, per-token scale, no mask; 2 to 128 heads, S up to 8200).  Against the best split of each
+// problem: D = 128 0.07 % on average (10 % at worst; 0.13 % and 16 % with the ratios of the table, and unquantized problems on
+// their own ratios lose more, not less); D = 64 0.12 % (5 %), against 0.26 % (13 %) for a rule that counted two workgroups per CU.
 constexpr float CROWD = 0.35f;
 inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident2, int resident4)
 {
@@ -140,10 +140,11 @@ inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident
     const bool pair = pair_heads(a);
     const float whole = cost(pair ? a.tile : 2 * a.tile, pair ? 2 : 1, resident1, 1.f, 2.5f);
     if (d64) {                                           // 1.25: of a split launch beside its lists, fitted with the other costs
-        return 1.25f + cost(a.tile, 1, resident2, 0.75f, 1.5f) < whole ? 2 : 1;
+        const float step = a.lo_fmt == 0 ? 0.71f : 0.75f;                        // unquantized (FMT_BF16) keys are cheap to stage again
+        return 1.25f + cost(a.tile, 1, resident2, step, 2.f * step) < whole ? 2 : 1;
     }
-    const float two = cost(a.tile, 1, resident2, 0.72f, 2.1f);
-    const float four = cost(a.tile / 2, 1, resident4, a.per_token ? 0.58f : 0.53f, 1.9f);
+    const float two = cost(a.tile, 1, resident2, 0.70f, 2.2f);
+    const float four = cost(a.tile / 2, 1, resident4, 0.51f, 2.05f);
     return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
 }
 

@@ -72,3 +72,16 @@ def test_split_by_the_longest_list():
 def test_split_at_the_occupancy_of_the_launch(B, Hq, Hkv, S, causal, lo, hi, split):
     """D = 64: three or four workgroups share a CU.  Counted as two, the rule split calls that the split makes slower."""
     assert plan.key_split(plan.problem(B, Hq, Hkv, S, 64, causal, lo), hi) == split
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,lo,hi,split", [
+    (1, 40, 8, 400, 128, 2, 2, 2),           # us with two waves and four: 13.7, 15.9
+    (1, 40, 8, 400, 128, 3, 3, 2),           # 15.8, 17.3
+    (1, 32, 8, 822, 128, 2, 2, 2),           # 19.3, 21.5
+    (1, 32, 8, 1800, 64, 0, 0, 2),           # two waves and unsplit: 28.0, 31.6
+    (1, 4, 1, 3700, 128, 2, 3, 4),
+    (1, 32, 8, 2600, 128, 2, 3, 1),
+])
+def test_split_costs(B, Hq, Hkv, S, D, lo, hi, split):
+    """Problems close to where the choice turns, as timed."""
+    assert plan.key_split(plan.problem(B, Hq, Hkv, S, D, lo=lo), hi) == split
