@@ -123,6 +123,8 @@ int dma_attn_fwd_ex(const void* q, const void* k, const void* v, void* out, int 
     a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.S = S; a.D = D;
     a.tile = tile;
     const int n_tiles = (S + tile - 1) / tile;          // the last tile may be partial
+    // items are counted in 32 bits, and so are the query heads of the whole batch, of which an item may take two
+    if ((int64_t)B * Hq * ((n_tiles + 1) / 2) > 0x7fffffffLL) return DMA_ERR_UNSUPPORTED;
     a.band = diag_band_tiles > n_tiles ? n_tiles : diag_band_tiles;
     a.sink = sink > n_tiles ? n_tiles : sink;
     a.causal = causal != 0;

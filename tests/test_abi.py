@@ -65,6 +65,9 @@ def test_argument_checks_return_before_any_launch(lib):
     assert attn(S=1 << 23) == -2              # one head of the output would not fit a 4 GiB buffer resource
     assert attn(S=(1 << 23) - 200) == -2      # ... nor may the rows of a filled-up last tile pair wrap around its offsets
     assert attn(D=96) == -2                   # no kernel for this head dimension
+    # more than 2^31 - 1 items of two query tiles, although a work item of one tile of two heads would count half as many
+    assert attn(B=(1 << 30) - 1, Hq=4, Hkv=2, S=1) == -2
+    assert attn(B=1 << 20, Hq=1 << 12, Hkv=1 << 11, S=2) == -2
     assert attn(hi=2, lo=1) == -2             # unsupported format pair
     assert lib.dma_attn_fwd(None, fake, fake, fake, 1, 4, 2, 256, 128, 1, 1, 1, 2, None) == -1
     assert attn(hi=3, lo=1) == -2             # unsupported format pair (E5M2 over E4M3)
