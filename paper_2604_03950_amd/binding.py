@@ -86,10 +86,17 @@ def version() -> int:
     return int(load().dma_version())
 
 
+# Names of torch without a promise: where a build lacks them, the public call serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
     """The current HIP stream of the current device.  (torch.cuda.current_stream() builds a Stream object for it: 2.8 us of
     a call whose kernel may take less, against 0.2.)"""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _current_device is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
 def _dev(t: torch.Tensor, dtype, what: str, shape=None) -> int:

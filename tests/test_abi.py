@@ -1,8 +1,10 @@
 """The C-ABI library loads and exports every symbol include/dma.h declares; argument checks that
 return before any GPU work behave as documented.  No kernel is launched here."""
 import ctypes
+import importlib.util
 import os
 import re
+import types
 
 import pytest
 
@@ -101,3 +103,19 @@ def test_argument_checks_return_before_any_launch(lib):
     assert lib.dma_diag_pipes(kinds, 3, 100, ctypes.c_void_p(0x1004), None, None) == -1     # misaligned counters
     assert lib.dma_diag_pipes((ctypes.c_int * 3)(1, 7, 4), 3, 100, fake, None, None) == -1   # no such stream
     assert lib.dma_diag_pipes(None, 3, 100, fake, None, None) == -1
+
+
+@pytest.mark.parametrize("missing", [None, "_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream(monkeypatch, missing):
+    """The handle of the caller's stream, also on a torch build without the short way to it."""
+    import torch
+    spec = importlib.util.spec_from_file_location("binding_copy", binding.__file__)
+    with monkeypatch.context() as m:
+        m.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1000 + device, raising=False)
+        m.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+        m.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x2000))
+        if missing:
+            m.delattr(torch._C, missing)
+        copy = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(copy)
+        assert copy._stream() == (0x2000 if missing else 0x1003)
