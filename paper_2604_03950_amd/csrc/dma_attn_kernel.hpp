@@ -1278,9 +1278,12 @@ static int launch_resident(int threads, int NG, int heads_item, const AttnArgs& 
                   a.S, a.band, a.sink, a.causal, c, s.head_block, a.q_amax, a.k_amax, extra...);
 }
 
+// Pairs with instances for the Step-2 scale: unquantized operands have none (the option is ignored there), and the native FP8
+// MFMA refuses it (dma_attn_fwd_ex).
+constexpr bool takes_token_scale(int lo, int hi) { return lo != FMT_BF16 && hi != FMT_E4M3; }
+
 // f(GENERAL, PT, PVMX) for the instance that serves the call: Alg. 1 as printed (causal, no sink window) runs the simpler
-// instance; the sink window, the non-causal variant and the per-token scale run the general one (unquantized operands have no
-// per-token scale).
+// instance; the sink window, the non-causal variant and the per-token scale run the general one.
 template <int LO, int HI, typename F>
 static int with_instance(const AttnArgs& a, F&& f)
 {
@@ -1294,7 +1297,7 @@ static int with_instance(const AttnArgs& a, F&& f)
             return DMA_ERR_UNSUPPORTED_;
         }
     }
-    if constexpr (LO != FMT_BF16) {
+    if constexpr (takes_token_scale(LO, HI)) {
         if (a.per_token) return f(IC<1>{}, IC<1>{}, IC<0>{});
     }
     if (a.causal && a.sink == 0) return f(IC<0>{}, IC<0>{}, IC<0>{});

@@ -268,11 +268,11 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 // ---------------------------------------------------------------------------------------------
 // Host side: launch (the number of waves that share a tile's keys comes from dma_plan.hpp)
 // ---------------------------------------------------------------------------------------------
-// f(PT) for the instance that serves the call (unquantized operands have no per-token scale).
-template <int LO, typename F>
+// f(PT) for the instance that serves the call.
+template <int LO, int HI, typename F>
 static int with_split(const AttnArgs& a, F&& f)
 {
-    if constexpr (LO != FMT_BF16) {
+    if constexpr (takes_token_scale(LO, HI)) {
         if (a.per_token) return f(IC<1>{});
     }
     return f(IC<0>{});
@@ -282,14 +282,14 @@ static int launch_split(const AttnArgs& a, hipStream_t stream)
 {
     using C = Cfg<D, BT, 1, KS>;
     constexpr int ROWS = 32 * C::NW / KS;
-    return with_split<LO>(a, [&](auto PT) {
+    return with_split<LO, HI>(a, [&](auto PT) {
         return launch_resident<dma_attn_split_kernel<D, BT, KS, LO, HI, PT != 0>>(C::T, (a.S + ROWS - 1) / ROWS, 1, a, stream);
     });
 }
 template <int D, int BT, int KS, int LO, int HI>
 static int resident_split(const AttnArgs& a)
 {
-    return with_split<LO>(a, [&](auto PT) { return resident_workgroups<dma_attn_split_kernel<D, BT, KS, LO, HI, PT != 0>>(Cfg<D, BT, 1, KS>::T); });
+    return with_split<LO, HI>(a, [&](auto PT) { return resident_workgroups<dma_attn_split_kernel<D, BT, KS, LO, HI, PT != 0>>(Cfg<D, BT, 1, KS>::T); });
 }
 
 // Split, or the instance of the unsplit kernel with two logical tiles per workgroup (one for a single-tile sequence).

@@ -86,9 +86,10 @@ def test_general_instances_keep_their_registers():
 
 
 @pytest.mark.parametrize("lo,hi", B.ATTN_PAIRS)
-def test_resident_workgroups(lo, hi):
-    """Workgroups of the forward kernels that share a CU (512 registers per lane and SIMD in steps of 8, 160 KB of LDS in steps
-    of 1280 bytes): the table the tests of the split rule use."""
+def test_instances(lo, hi):
+    """What a pair is built as: the workgroups of the forward kernels that share a CU (512 registers per lane and SIMD in steps
+    of 8, 160 KB of LDS in steps of 1280 bytes), which the tests of the split rule have in a table; and no instance that no call
+    reaches."""
     def fits(c):
         waves = c["max_flat_workgroup_size"] // 64
         return min(512 // (-(-c["vgpr_count"] // 8) * 8) * 4 // waves, 160 * 1024 // (-(-c["group_segment_fixed_size"] // 1280) * 1280))
@@ -102,3 +103,6 @@ def test_resident_workgroups(lo, hi):
         assert fits(c) == plan.resident(D, lo, hi, per_token)[{2: 1, 4: 2}[ks]], (D, ks, per_token, c)
         seen += 1
     assert seen >= 7
+    # the pairs on the native FP8 MFMA refuse the Step-2 scale, unquantized operands have none: no instances for either
+    scaled = [k for k in resources(lo, hi, "dma_attn_fwd_kernel") if k[6]] + [k for k in resources(lo, hi, "dma_attn_split_kernel") if k[5]]
+    assert bool(scaled) == (lo != 0 and hi != 1), scaled
