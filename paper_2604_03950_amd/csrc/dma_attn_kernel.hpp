@@ -1027,8 +1027,8 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // this item visits key tiles [0, nt).  A filled-up tile of the last group (it >= N) has no rows: it asks for no
         // key tile of its own, and its waves compute no band tile (jlast: the last key tile the wave computes as one), so the
         // other wave of the SIMD has it to itself there.  One bound per wave and no test in the main step, because the sizes
-        // with an even number of tiles pay for what lives through it (a flag of its own and a second test in `needs`: 5 VGPRs and
-        // up to 36 spilled SGPRs more).
+        // with an even number of tiles pay for what lives through it (a flag of its own and a second test in `needs`: 1 VGPR and
+        // 7 or 8 spilled SGPRs more in the general instances).
         const int nt = causal ? min(last + 1, N) : N;
         const int jlast = (TPW > 1 && it >= N) ? -1 : causal ? it : N;
         auto tile_hi = [&](int qt, int jt) __attribute__((always_inline)) {             // does query tile qt compute key tile jt in the high format?
