@@ -298,7 +298,8 @@ def test_attn_heavy_tail_16k_modes(dma, oracle):
 
 
 def test_attn_odd_tile_count(dma, oracle):
-    """An odd number of query tiles: the last pair of tiles is filled up with a tile past the end of the sequence."""
+    """An odd number of query tiles, few enough items for the kernel that splits the keys of a tile.  (The filled-up tile of the
+    other kernel: test_gpu_unsplit.py.)"""
     w = wl.small_variant(wl.CONFIGS["prefill_8k"], S=384, Hq=3, Hkv=3)
     q, k, v = wl.generate(w)
     for band, lo, hi in ((2, "e2m1", "e4m3"), (0, "e2m1", "e2m1")):
@@ -354,7 +355,7 @@ def test_attn_sink_window(dma, oracle, band, sink):
     w = wl.small_variant(wl.CONFIGS["prefill_8k"], S=768, Hq=2, Hkv=2)
     q, k, v = wl.generate(w)
     run_case(dma, oracle, w, q, k, v, band, "e2m1", "e4m3", sink=sink)
-    w = wl.small_variant(wl.CONFIGS["gqa_32k"], S=640, Hq=8, Hkv=2)        # odd tile count: the last pair holds one real tile
+    w = wl.small_variant(wl.CONFIGS["gqa_32k"], S=640, Hq=8, Hkv=2)        # odd tile count
     q, k, v = wl.generate(w)
     run_case(dma, oracle, w, q, k, v, band, "e2m1", "e4m3", sink=sink)
     run_case(dma, oracle, w, q, k, v, band, "e2m1", "e2m1", sink=sink)      # one format: the sink changes nothing
@@ -485,7 +486,8 @@ def test_attn_pv_mx_tiny(dma, oracle, band):
 
 @pytest.mark.parametrize("S,causal,sink", [(512, True, 0), (640, True, 0), (384, True, 1), (512, False, 0), (300, True, 0), (300, False, 0)])
 def test_attn_pv_mx_d128(dma, oracle, S, causal, sink):
-    """Both tile pairings (even / odd tile counts), the general instance (sink, no mask) and a partial last tile."""
+    """Even and odd tile counts, the general instance (sink, no mask) and a partial last tile; an item is the same tile of both
+    heads (tiles in a row of one head: test_gpu_unsplit.py)."""
     w = wl.small_variant(wl.CONFIGS["prefill_8k"], S=S, Hq=2, Hkv=1)
     q, k, v = wl.generate(w)
     run_case(dma, oracle, w, q, k, v, 1, "e2m1", "e4m3", sink=sink, causal=causal, pv_mx=True,
@@ -501,13 +503,13 @@ def test_attn_pv_mx_full_size_sampled(dma, oracle):
              max_abs_bar=PV_MX_MAX_ABS, rel_bar=PV_MX_REL_L2)
 
 
-# ------------------------------------------------------------------ even tile counts at D = 128 (two query tiles per workgroup)
+# ------------------------------------------------------------------ even tile counts at D = 128
 
 @pytest.mark.parametrize("lo,hi", FMT_PAIRS)
 @pytest.mark.parametrize("S,band", [(256, 0), (256, 1), (512, 2), (1024, 0), (1024, 1), (1024, 3), (1024, 8)])
 def test_attn_d128_even_tiles_all_rows(dma, oracle, S, band, lo, hi):
-    """The instance that pairs two query tiles per workgroup and runs its two halves half a tile out of step: the
-    smallest case (one pair), and several pairs with every window width (none, inside a pair, across pairs, all)."""
+    """Whole tiles, two to eight of them, with every window width (none, one tile, a few, all): few items, so four waves share
+    the keys of a tile."""
     w = wl.small_variant(wl.CONFIGS["prefill_8k"], S=S, Hq=2, Hkv=1)
     q, k, v = wl.generate(w)
     run_case(dma, oracle, w, q, k, v, band, lo, hi, explicit_tile=False)
