@@ -101,6 +101,10 @@ int dma_mx_quantize_dual(const void* x_bf16, int64_t rows, int D, int is_query,
  *   tile, running maximum / sum in binary32, probabilities rounded to bf16 for the P V product
  *   (V stays bf16), binary32 accumulation, final division by the running sum.  No intermediate is
  *   written to device memory.
+ *
+ *   Equal calls give equal bits.  The order in which a row's binary32 sums over the keys are added follows from B, Hq, Hkv, S
+ *   and the options, though (problems with few work items split the keys of a tile over two or four waves): the same
+ *   sequence alone, in a batch, or with another number of heads may differ in the last bits (about 1e-7 of the values).
  */
 int dma_attn_fwd(const void* q, const void* k, const void* v, void* out,
                  int B, int Hq, int Hkv, int S, int D, int causal,

@@ -912,7 +912,8 @@ DMA_DEV void stage_key(const v4i (&kreg)[C::CPT], bool any_lo, bool any_hi, unsi
 
 // GENERAL = false: Alg. 1 as printed (causal, no sink window; sink_arg / causal_arg are ignored), any length: main tiles then
 // band tiles.  GENERAL = true: sink window and / or no causal mask: runs of main and band tiles alternate.  (The general
-// instance on the causal mask: 64 x 32 / 8 heads, S = 300 209.3 us against 204.9; no difference from S = 2600 on.)
+// instance on the causal mask: 64 x 32 / 8 heads, S = 300 179.2 us against 174.5; 16 x S = 1100 240.2, 238.6; no difference from
+// S = 2600 on.)
 // PT: per-token scale of Alg. 2 Step 2 on queries and keys (built with GENERAL only).
 // PVMX: the P V product in MXFP8-E4M3 with blocks of 32 keys (an extension beyond Alg. 1, which keeps P and V in 16 bit).
 template <int D, int BT, int TPW, int LO, int HI, bool GENERAL, bool PT, bool PVMX>
