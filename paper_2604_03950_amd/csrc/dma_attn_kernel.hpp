@@ -1305,14 +1305,16 @@ static int with_instance(const AttnArgs& a, F&& f)
     return f(IC<1>{}, IC<0>{}, IC<0>{});
 }
 
-template <int D, int BT, int TPW, int LO, int HI>
-static int launch_instance(const AttnArgs& a, hipStream_t stream)
+template <int D, int BT, int LO, int HI>
+static int launch_instance(Item item, const AttnArgs& a, hipStream_t stream)
 {
     return with_instance<LO, HI>(a, [&](auto GENERAL, auto PT, auto PVMX) {
         const int N = (a.S + BT - 1) / BT;
-        const bool pair = TPW == 2 && pair_heads(a);
-        return launch_resident<dma_attn_fwd_kernel<D, BT, TPW, LO, HI, GENERAL != 0, PT != 0, PVMX != 0>>(
-            Cfg<D, BT, TPW>::T, pair ? N : (N + TPW - 1) / TPW, pair ? 2 : 1, a, stream, (int)pair);
+        if (item == Item::ONE_TILE)
+            return launch_resident<dma_attn_fwd_kernel<D, BT, 1, LO, HI, GENERAL != 0, PT != 0, PVMX != 0>>(Cfg<D, BT, 1>::T, N, 1, a, stream, 0);
+        const bool pair = item == Item::TWO_HEADS;
+        return launch_resident<dma_attn_fwd_kernel<D, BT, 2, LO, HI, GENERAL != 0, PT != 0, PVMX != 0>>(
+            Cfg<D, BT, 2>::T, pair ? N : (N + 1) / 2, pair ? 2 : 1, a, stream, (int)pair);
     });
 }
 

@@ -292,27 +292,26 @@ static int resident_split(const AttnArgs& a)
     return with_split<LO, HI>(a, [&](auto PT) { return resident_workgroups<dma_attn_split_kernel<D, BT, KS, LO, HI, PT != 0>>(Cfg<D, BT, 1, KS>::T); });
 }
 
-// Split, or the instance of the unsplit kernel with two logical tiles per workgroup (one for a single-tile sequence).
+// Split, or unsplit items of one or two logical tiles per workgroup (of two, 256 query rows share each K/V tile; where two
+// in a row of a head make up an item and their number is odd, the last pair is filled up with a tile past the end).
 template <int D, int BT, int LO, int HI>
 static int launch_tile(const AttnArgs& a, hipStream_t stream)
 {
     constexpr bool FOUR = D == 128;
+    const int cus = compute_units();
+    if (cus <= 0) return DMA_ERR_HIP_;
     if (!a.pv_mx && a.S > BT) {
-        const int cus = compute_units(), r1 = resident_instance<D, BT, LO, HI>(a), r2 = resident_split<D, BT, 2, LO, HI>(a);
+        const int r1 = resident_instance<D, BT, LO, HI>(a), r2 = resident_split<D, BT, 2, LO, HI>(a);
         int r4 = r2;
         if constexpr (FOUR) r4 = resident_split<D, BT, 4, LO, HI>(a);
-        if (cus <= 0 || r1 <= 0 || r2 <= 0 || r4 <= 0) return DMA_ERR_HIP_;
+        if (r1 <= 0 || r2 <= 0 || r4 <= 0) return DMA_ERR_HIP_;
         const int ks = key_split(a, cus, r1, r2, r4);
         if (ks == 2) return launch_split<D, BT, 2, LO, HI>(a, stream);
         if constexpr (FOUR) {
             if (ks == 4) return launch_split<D, BT, 4, LO, HI>(a, stream);
         }
     }
-    // two logical tiles per workgroup (256 query rows share each K/V tile); without a second head to take it from and with
-    // an odd number of tiles the last pair is filled up with a tile past the end of the sequence.  One tile per workgroup
-    // only for a single tile of a single head.
-    if (a.S > BT || pair_heads(a)) return launch_instance<D, BT, 2, LO, HI>(a, stream);
-    return launch_instance<D, BT, 1, LO, HI>(a, stream);
+    return launch_instance<D, BT, LO, HI>(unsplit_item(a, cus), a, stream);
 }
 
 }  // namespace dma

@@ -48,11 +48,21 @@ inline Schedule make_schedule(const AttnArgs& a, int NG, int heads_item, int64_t
     return s;
 }
 
-// Do the two logical tiles of a workgroup come from two query heads?  Wherever the heads of a kv head divide into pairs: two
-// tiles of one head leave half of the workgroup without work on the item's last key tile and an odd tile count half empty.
-// 32 / 8 heads, us with two tiles of a head and with a tile of two heads: 64 x S = 100 67.0, 47.0; 64 x S = 300 199, 167;
-// 16 x S = 1100 248, 222; S = 2500 61.9, 60.6; S = 8191 415, 407; S = 32768 5807, 5753; D = 64 64 x S = 700 281, 247.
-inline bool pair_heads(const AttnArgs& a) { return (a.Hq / a.Hkv) % 2 == 0; }
+// The query rows of an unsplit item: one logical tile, two in a row of a head, or the same tile of two heads that share a kv head.
+enum class Item { ONE_TILE, TWO_TILES, TWO_HEADS };
+// Two heads wherever the heads of a kv head divide into pairs: two tiles of one head leave half of the workgroup without work on
+// the item's last key tile and an odd tile count half empty.  32 / 8 heads, us with two tiles of a head and with a tile of two
+// heads: 64 x S = 100 67.0, 47.0; 64 x S = 300 199, 167; 16 x S = 1100 248, 222; S = 2500 61.9, 60.6; S = 8191 415, 407; S = 32768 5807,
+// 5753; D = 64 64 x S = 700 281, 247.
+// A single tile goes alone while every one has a compute unit to itself: the waves of the second head would only wait for
+// the same units (time alone over time in pairs, 2000 problems of up to cus query heads: D = 128 0.78 to 0.94, D = 64 0.89 to 0.99;
+// with more heads than compute units 1.0 to 1.9 at D = 128).
+inline Item unsplit_item(const AttnArgs& a, int64_t cus)
+{
+    const bool pairs = (a.Hq / a.Hkv) % 2 == 0;
+    if (a.S <= a.tile) return pairs && (int64_t)a.B * a.Hq > cus ? Item::TWO_HEADS : Item::ONE_TILE;
+    return pairs ? Item::TWO_HEADS : Item::TWO_TILES;
+}
 
 // What a launch has its workgroups walk, in steps of the unsplit kernel (`step` per key tile and `item` per item: prologue,
 // epilogue, band tiles): the longest list of items any of them is dealt, and the work of a compute unit.
@@ -137,8 +147,8 @@ inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident
         const Load l = dealt_load(a, rows, heads_item, cus, resident, step, item);
         return l.longest + CROWD * (l.cu > l.longest ? l.cu - l.longest : 0.f);
     };
-    const bool pair = pair_heads(a);
-    const float whole = cost(pair ? a.tile : 2 * a.tile, pair ? 2 : 1, resident1, 1.f, 2.5f);
+    const bool two_heads = unsplit_item(a, cus) == Item::TWO_HEADS;
+    const float whole = cost(two_heads ? a.tile : 2 * a.tile, two_heads ? 2 : 1, resident1, 1.f, 2.5f);
     if (d64) {                                           // 1.25: of a split launch beside its lists, fitted with the other costs
         const float step = a.lo_fmt == 0 ? 0.71f : 0.75f;                        // unquantized (FMT_BF16) keys are cheap to stage again
         return 1.25f + cost(a.tile, 1, resident2, step, 2.f * step) < whole ? 2 : 1;

@@ -23,6 +23,7 @@ extern "C" void dealt_load(const int* p, int rows, int heads_item, int cus, int 
     out[1] = l.cu;
 }
 extern "C" int key_split(const int* p, int cus, const int* resident) { return dma::key_split(args(p), cus, resident[0], resident[1], resident[2]); }
+extern "C" int unsplit_item(const int* p, int cus) { return (int)dma::unsplit_item(args(p), cus); }
 """
 
 
@@ -62,3 +63,11 @@ def resident(D, lo, hi, per_token=False):
 def key_split(p, hi=3, cus=256):
     """Waves that share 32 query rows: 1, 2 or 4."""
     return library().key_split(p, cus, (ctypes.c_int * 3)(*resident(p[4], p[6], hi, bool(p[7]))))
+
+
+ONE_TILE, TWO_TILES, TWO_HEADS = range(3)
+
+
+def unsplit_item(p, cus=256):
+    """What an unsplit item holds: one logical tile, two in a row of a head, or the same tile of two heads."""
+    return library().unsplit_item(p, cus)

@@ -85,3 +85,17 @@ def test_split_at_the_occupancy_of_the_launch(B, Hq, Hkv, S, causal, lo, hi, spl
 def test_split_costs(B, Hq, Hkv, S, D, lo, hi, split):
     """Problems close to where the choice turns, as timed."""
     assert plan.key_split(plan.problem(B, Hq, Hkv, S, D, lo=lo), hi) == split
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,item", [
+    (1, 32, 8, 128, 128, plan.ONE_TILE),     # us alone and in pairs, all MXFP8: 9.6, 11.2
+    (8, 32, 8, 128, 128, plan.ONE_TILE),
+    (9, 32, 8, 128, 128, plan.TWO_HEADS),    # more heads than compute units
+    (64, 32, 8, 100, 128, plan.TWO_HEADS),   # 67.0, 47.0
+    (1, 4, 4, 1, 64, plan.ONE_TILE),
+    (100, 9, 3, 64, 64, plan.ONE_TILE),      # no pairs
+    (64, 40, 8, 300, 128, plan.TWO_TILES),
+    (64, 32, 8, 300, 128, plan.TWO_HEADS),
+])
+def test_unsplit_item(B, Hq, Hkv, S, D, item):
+    assert plan.unsplit_item(plan.problem(B, Hq, Hkv, S, D)) == item
