@@ -54,14 +54,22 @@ enum class Item { ONE_TILE, TWO_TILES, TWO_HEADS };
 // the item's last key tile and an odd tile count half empty.  32 / 8 heads, us with two tiles of a head and with a tile of two
 // heads: 64 x S = 100 67.0, 47.0; 64 x S = 300 199, 167; 16 x S = 1100 248, 222; S = 2500 61.9, 60.6; S = 8191 415, 407; S = 32768 5807,
 // 5753; D = 64 64 x S = 700 281, 247.
-// A single tile goes alone while every one has a compute unit to itself: the waves of the second head would only wait for
-// the same units (time alone over time in pairs, 2000 problems of up to cus query heads: D = 128 0.78 to 0.94, D = 64 0.89 to 0.99;
+// A single tile goes alone while every one has a compute unit to itself: a second head would only take half of the unit's
+// issue slots (time alone over time in pairs, 2000 problems of up to cus query heads: D = 128 0.78 to 0.94, D = 64 0.89 to 0.99;
 // with more heads than compute units 1.0 to 1.9 at D = 128).
+// For the same reason two tiles of one head, where their count is odd, the mask makes the last one the longest item and every
+// item has a unit: the last tile is then alone in its workgroup (D = 128, time with two tiles over two heads: 0.90 on
+// average and 1.02 at most there, 1.2 with more items than units; even counts 1.02; without the mask 1.03; D = 64 0.99).
+inline bool last_tile_alone(const AttnArgs& a, int64_t cus)
+{
+    const int N = (a.S + a.tile - 1) / a.tile;
+    return a.D == 128 && a.causal && N % 2 == 1 && (int64_t)a.B * a.Hq * ((N + 1) / 2) <= cus;
+}
 inline Item unsplit_item(const AttnArgs& a, int64_t cus)
 {
     const bool pairs = (a.Hq / a.Hkv) % 2 == 0;
     if (a.S <= a.tile) return pairs && (int64_t)a.B * a.Hq > cus ? Item::TWO_HEADS : Item::ONE_TILE;
-    return pairs ? Item::TWO_HEADS : Item::TWO_TILES;
+    return pairs && !last_tile_alone(a, cus) ? Item::TWO_HEADS : Item::TWO_TILES;
 }
 
 // What a launch has its workgroups walk, in steps of the unsplit kernel (`step` per key tile and `item` per item: prologue,
@@ -148,7 +156,8 @@ inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident
         return l.longest + CROWD * (l.cu > l.longest ? l.cu - l.longest : 0.f);
     };
     const bool two_heads = unsplit_item(a, cus) == Item::TWO_HEADS;
-    const float whole = cost(two_heads ? a.tile : 2 * a.tile, two_heads ? 2 : 1, resident1, 1.f, 2.5f);
+    float whole = cost(two_heads ? a.tile : 2 * a.tile, two_heads ? 2 : 1, resident1, 1.f, 2.5f);
+    if (last_tile_alone(a, cus)) whole *= 0.92f;
     if (d64) {                                           // 1.25: of a split launch beside its lists, fitted with the other costs
         const float step = a.lo_fmt == 0 ? 0.71f : 0.75f;                        // unquantized (FMT_BF16) keys are cheap to stage again
         return 1.25f + cost(a.tile, 1, resident2, step, 2.f * step) < whole ? 2 : 1;

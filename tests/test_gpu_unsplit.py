@@ -33,11 +33,12 @@ FORMS = [(D,) + form for D in (128, 64) for form in (
     ("e2m1", "e4m3", 2, dict(fp8_mfma=True)),
     ("e4m3", "e4m3", 0, dict(fp8_mfma=True)),
 )]
-# heads, kv heads, tiles (the last one whole or not), what an item holds.  Two tiles in a row of one head: an odd number of
-# tiles is filled up with one past the end.
-SHAPES = [(3, 3, 3, True, plan.TWO_TILES), (1, 1, 4, True, plan.TWO_TILES), (3, 1, 4, False, plan.TWO_TILES), (1, 1, 5, False, plan.TWO_TILES),
-          (4, 2, 3, False, plan.TWO_HEADS), (2, 1, 1, False, plan.TWO_HEADS), (4, 1, 4, True, plan.TWO_HEADS),
-          (4, 2, 1, True, plan.ONE_TILE), (2, 1, 1, False, plan.ONE_TILE), (3, 1, 1, False, plan.ONE_TILE)]
+# heads, kv heads, tiles (the last one whole or not), what an item holds, items at most (or as many as the split rule wants).
+# Two tiles in a row of one head: an odd number of tiles is filled up with one past the end.
+SHAPES = [(3, 3, 3, True, plan.TWO_TILES, 0), (1, 1, 4, True, plan.TWO_TILES, 0), (3, 1, 4, False, plan.TWO_TILES, 0),
+          (1, 1, 5, False, plan.TWO_TILES, 0), (4, 2, 3, False, plan.TWO_HEADS, 0), (2, 1, 1, False, plan.TWO_HEADS, 0),
+          (4, 1, 4, True, plan.TWO_HEADS, 0), (4, 2, 1, True, plan.ONE_TILE, 256), (2, 1, 1, False, plan.ONE_TILE, 256),
+          (3, 1, 1, False, plan.ONE_TILE, 256), (4, 2, 3, False, plan.TWO_TILES, 256)]
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("form", range(len(FORMS)))
@@ -52,12 +53,13 @@ def test_unsplit_against_the_oracle(oracle, form):
     scaled, causal = kw.get("per_token_scale", False), kw.get("causal", True)
     gpu_fmt = {"bf16": dma.FMT_BF16, "e4m3": dma.FMT_MXFP8_E4M3, "e2m1": dma.FMT_MXFP4_E2M1, "e5m2": dma.FMT_MXFP8_E5M2}
     ref_fmt = {"bf16": oracle.FMT_BF16, "e4m3": oracle.FMT_E4M3, "e2m1": oracle.FMT_E2M1, "e5m2": oracle.FMT_E5M2}
-    for case, (Hq, Hkv, tiles, whole, item) in enumerate(SHAPES):
+    for case, (Hq, Hkv, tiles, whole, item, few) in enumerate(SHAPES):
         S = tiles * D - (0 if whole else 37)
-        reps = 3 * 256 // (Hq * -(-tiles // 2)) + 1
-        reps += -reps % 8 if case % 2 else 0                     # with and without a share of the heads per XCD
-        if item == plan.ONE_TILE:
-            reps = 256 // Hq - case % 2
+        reps = few // (Hq * -(-tiles // 2)) or 3 * 256 // (Hq * -(-tiles // 2)) + 1
+        if case % 2:                                             # with and without a share of the heads per XCD
+            reps += -1 if few else -reps % 8
+        if few and tiles > 1 and not (D == 128 and causal):
+            continue
         path = [1 if fp8 and f == "e4m3" else PATH[f] for f in (lo, hi)]
         p = plan.problem(reps, Hq, Hkv, S, D, causal, path[0], scaled)
         assert plan.unsplit_item(p) == item and (kw.get("pv_mx") or plan.key_split(p, path[1]) == 1)

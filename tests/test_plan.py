@@ -96,6 +96,14 @@ def test_split_costs(B, Hq, Hkv, S, D, lo, hi, split):
     (100, 9, 3, 64, 64, plan.ONE_TILE),      # no pairs
     (64, 40, 8, 300, 128, plan.TWO_TILES),
     (64, 32, 8, 300, 128, plan.TWO_HEADS),
+    (1, 128, 32, 269, 128, plan.TWO_TILES),  # 16.0 us, with a tile of two heads 18.0
+    (8, 12, 3, 318, 128, plan.TWO_TILES),    # 18.9, 21.0
+    (1, 129, 43, 269, 128, plan.TWO_TILES),  # no pairs
+    (1, 132, 33, 269, 128, plan.TWO_HEADS),  # more items than compute units
+    (1, 128, 32, 256, 128, plan.TWO_HEADS),
+    (1, 128, 32, 150, 64, plan.TWO_HEADS),
 ])
 def test_unsplit_item(B, Hq, Hkv, S, D, item):
     assert plan.unsplit_item(plan.problem(B, Hq, Hkv, S, D)) == item
+    if item == plan.TWO_TILES and Hq // Hkv % 2 == 0:
+        assert plan.unsplit_item(plan.problem(B, Hq, Hkv, S, D, causal=False)) == plan.TWO_HEADS
