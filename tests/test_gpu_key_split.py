@@ -43,7 +43,7 @@ FORMS = [
 ]
 # heads, kv heads, length: 2 heads take four waves at D = 128, 32 heads two (at S = 613 four with the mask)
 SHAPES = {128: [(2, 1, 129), (2, 2, 257), (2, 1, 448), (2, 1, 1100), (32, 8, 613), (32, 8, 1100)],
-          64: [(2, 1, 65), (2, 2, 161), (4, 1, 700), (32, 8, 1600), (32, 8, 2100)]}
+          64: [(2, 1, 65), (2, 2, 161), (4, 1, 700), (32, 8, 1600)]}
 
 
 @pytest.mark.gpu
@@ -95,5 +95,5 @@ def test_split_matches_unsplit(form):
             # the two kernels add in different orders: equal bits everywhere would mean that only one of them ran
             assert not torch.equal(many[0], one[0]), (FORMS[form], Hq, S)
     assert splits == ({2, 4} if D == 128 else {2}), splits
-    if options.get("causal", True) and (D == 128 or plan.resident(64, path[lo], path[hi], scaled)[1] == 3 or lo == "bf16"):
+    if options.get("causal", True) and (D == 128 or plan.resident(64, path[lo], path[hi], scaled)[1] == 3):
         assert second_item == splits, second_item

@@ -79,6 +79,9 @@ def test_split_at_the_occupancy_of_the_launch(B, Hq, Hkv, S, causal, lo, hi, spl
     (1, 40, 8, 400, 128, 3, 3, 2),           # 15.8, 17.3
     (1, 32, 8, 822, 128, 2, 2, 2),           # 19.3, 21.5
     (1, 32, 8, 1800, 64, 0, 0, 2),           # two waves and unsplit: 28.0, 31.6
+    (45, 5, 1, 298, 64, 2, 2, 1),            # 13.8, 11.9: more than two items per compute unit
+    (16, 16, 16, 292, 64, 2, 2, 1),          # 14.7, 12.4
+    (8, 32, 8, 267, 64, 0, 0, 1),            # 14.2, 12.4
     (1, 4, 1, 3700, 128, 2, 3, 4),
     (1, 32, 8, 2600, 128, 2, 3, 1),
 ])
