@@ -1116,6 +1116,14 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             }
             make_q<C, LO, PT>(qr_lo, qs_lo, qraw, c, inv_sq);
             if constexpr (TWO) {
+                // The compiler shares the scaled elements between the two operand sets (90 vector instructions per item) and
+                // holds them in registers for it.  Not where that costs a resident workgroup: MXFP4 / native MXFP8 at D = 64 takes
+                // 132 VGPRs that way and three workgroups share a CU, 122 without and four do (20 x 60 / 12 heads, S = 132 27.9 us
+                // with four, 32.8 with three).
+                if constexpr (D == 64 && TPW == 2 && HI == FMT_E4M3) {
+#pragma unroll
+                    for (int i = 0; i < C::NKK; ++i) asm volatile("" : "+v"(qraw[i]));
+                }
                 if (band > 0 || sink > 0) make_q<C, HI, PT>(qr_hi, qs_hi, qraw, c, inv_sq);
             }
         }

@@ -57,7 +57,7 @@ def resident(D, lo, hi, per_token=False):
         return 1, 1, 1                     # more than half of a CU's LDS each
     if lo != hi and hi != 1:               # the decoded 8-bit keys beside the MXFP4 ones: 42 KB of LDS
         return 3, 3, 3
-    return (3 if lo != hi or (per_token and lo > 2) else 4), 4, 4
+    return (3 if per_token and lo > 2 else 4), 4, 4
 
 
 def key_split(p, hi=3, cus=256):
