@@ -138,18 +138,18 @@ inline Load dealt_load(const AttnArgs& a, int rows, int heads_item, int64_t cus,
 // 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200
 // 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7, S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads,
 // S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
-// The costs below are the ones whose choice loses least on problems timed with every split (six forms: default, all MXFP8,
-// all MXFP4, unquantized, per-token scale, no mask; 2 to 500 heads over the batch, S up to 8200).  From the best split of each:
-// D = 128 (2764 problems) 0.05 % on average, 10 % at worst; D = 64 (3387) 0.14 %, 12 %; by the ratios of the table, with two
-// workgroups per CU at D = 64, 0.15 %, 16 % and 0.44 %, 22 %.  Unquantized problems at D = 128 lose more, not less, by ratios of
-// their own.
+// The costs below are the ones whose choice loses least on problems timed with every split (default, all MXFP8, all MXFP4 and
+// unquantized, with and without the per-token scale and the mask; 2 to 500 heads over the batch, S up to 8200).  From the best
+// split of each: D = 128 (2764 problems) 0.05 % on average, 10 % at worst; D = 64 (6865) 0.12 %, 12 %; by the ratios of the table,
+// with two workgroups per CU at D = 64, 0.15 %, 16 % and 1.0 %, 22 %.  Unquantized problems at D = 128 lose more, not less, by
+// ratios of their own.
 constexpr float CROWD = 0.3f;
 inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident2, int resident4)
 {
     if (a.S <= a.tile) return 1;
     const bool d64 = a.D == 64;
     const int64_t items = (int64_t)a.B * a.Hq * ((a.S + 2 * a.tile - 1) / (2 * a.tile));
-    if (items > 2 * cus) return 1;         // the lists are balanced: splitting only costs (it gained 1 % or more on 20 of 1580 such problems)
+    if (items > 2 * cus) return 1;         // the lists are balanced: splitting only costs (it gained 1 % or more on 20 of 1585 such problems)
     const int most = resident1 > resident2 ? (resident1 > resident4 ? resident1 : resident4) : (resident2 > resident4 ? resident2 : resident4);
     if (cus * most > MAX_WORKERS) return 1;
     auto cost = [&](int rows, int heads_item, int resident, float step, float item) {
@@ -160,9 +160,9 @@ inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident
     float whole = cost(two_heads ? a.tile : 2 * a.tile, two_heads ? 2 : 1, resident1, 1.f, d64 ? 2.f : 2.5f);
     if (last_tile_alone(a, cus)) whole *= 0.92f;
     if (d64) {
-        // a step of the split kernel is dear where staging a key tile is most of it, least so for unquantized (FMT_BF16) keys
-        // and with the Step-2 scale (which multiplies every score); 0.5: beside the lists of a split launch
-        const float step = a.lo_fmt == 0 || a.per_token ? 0.73f : 0.79f;
+        // least for unquantized (FMT_BF16) keys and with the Step-2 scale, but not without the mask, where every list is long and
+        // two workgroups or more share a CU throughout; 0.5: beside the lists of a split launch
+        const float step = a.causal && (a.lo_fmt == 0 || a.per_token) ? 0.73f : 0.80f;
         return 0.5f + cost(a.tile, 1, resident2, step, 2.f * step) < whole ? 2 : 1;
     }
     const float two = cost(a.tile, 1, resident2, 0.70f, 2.2f);

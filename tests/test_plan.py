@@ -110,3 +110,12 @@ def test_unsplit_item(B, Hq, Hkv, S, D, item):
     assert plan.unsplit_item(plan.problem(B, Hq, Hkv, S, D)) == item
     if item == plan.TWO_TILES and Hq // Hkv % 2 == 0:
         assert plan.unsplit_item(plan.problem(B, Hq, Hkv, S, D, causal=False)) == plan.TWO_HEADS
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,lo,hi,per_token,split", [
+    (4, 48, 16, 192, 3, 3, True, 1),         # us unsplit and split: 11.3, 12.5
+    (11, 16, 2, 256, 0, 0, False, 1),        # 9.8, 10.3
+    (1, 4, 1, 3700, 2, 3, True, 2),
+])
+def test_split_without_the_mask_at_d64(B, Hq, Hkv, S, lo, hi, per_token, split):
+    assert plan.key_split(plan.problem(B, Hq, Hkv, S, 64, False, lo, per_token), hi) == split
