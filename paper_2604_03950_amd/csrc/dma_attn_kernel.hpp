@@ -19,7 +19,7 @@
 // so the row maximum / sum need one cross-half exchange and the running state (m, l) is per lane.
 //
 // Pipeline.  While tile jt is computed out of LDS buffer jt & 1, tile jt+1 goes from registers into buffer (jt+1) & 1, K
-// quantized on the way (block maximum over a lane quad by DPP, E8M0 scale, hardware scaled converts) at the top of the
+// quantized on the way (a thread has whole MX blocks: maximum, E8M0 scale, hardware scaled converts) at the top of the
 // step and V behind the softmax, and each is requested for tile jt+2 (16 B per lane, coalesced) once its registers are
 // free: one barrier per tile.
 // Two waves per SIMD (the register budget allows no more): the matrix work of one overlaps the vector
@@ -57,7 +57,12 @@ struct Cfg {
     static constexpr int KS8 = D + 16;           // E4M3 codes
     static constexpr int KSB = 2 * D + 16;       // bf16 keys
     static constexpr int VS = 2 * D;             // bf16 values: dense rows, 16-byte chunks XOR-swizzled (see v_swizzle)
-    static constexpr int KSC = BT * CPR;         // scale bytes of one tile: one per 16-byte chunk (each block's 4 chunks repeat its code)
+    // Scale bytes of one tile: those of a key lie together, first the even MX blocks, then the odd ones, so that a lane of the
+    // score part finds the NH bytes it needs (blocks 2h + g) in one read, consecutive keys in consecutive banks.  (Against a byte
+    // per 16-byte chunk, read as dwords 16 bytes apart: 32 / 8 heads S = 613 17.5 -> 17.3 us, 4 / 1 S = 8192 92.6 -> 91.6, 32 / 32
+    // S = 8192 397.5 -> 394.9, D = 64 2 x 32 / 8 S = 3000 89.0 -> 87.9.)
+    static constexpr int SPK = 2 * NH;           // scale bytes per key
+    static constexpr int KSC = BT * SPK;
     static constexpr int VBYTES = BT * VS;
     // MX-format P V: V as E4M3 codes, one byte per element in padded rows, then one scale byte per (32-key block,
     // column).  In its staging each wave owns the keys of one 32-key block (and, with two logical tiles per workgroup,
@@ -71,6 +76,18 @@ struct Cfg {
     // V rows sit densely in LDS; so that the transpose reads of four consecutive keys do not hit the same banks,
     // chunk c of key k is stored at chunk c ^ (4 * v_swizzle(k)).
     static constexpr int v_swizzle(int key) { return D == 128 ? (key & 3) : ((key >> 1) & 1); }
+    // A thread's chunks of a K tile are KR runs of KG consecutive ones (half an MX block or a whole one, as many as it has): the
+    // block maximum stays in the thread (or a pair), a block has one scale computation and its codes leave in one store.  With
+    // chunks of four different rows per thread and the maximum over a quad of lanes a D = 128 main step had 309 vector and 88 LDS
+    // instructions, now 289 and 82, and the loads, which then touch 64-byte segments per lane instead of whole rows per 16 lanes,
+    // are no slower.  (us, same box, before and after) 32 / 32 heads S = 8192 410.7 -> 404.5, 32 / 8 S = 32768 5814 -> 5682,
+    // 4 / 1 S = 8192 96.8 -> 93.5, 32 / 8 S = 4096 with the tensor scale 153.1 -> 147.9, S = 8192 per token 537 -> 515.  Runs of two
+    // chunks throughout: 32 / 32 S = 8192 0.8 % slower, the tensor scale 3 %.
+    // Unquantized keys are only copied: chunk by chunk, coalesced.
+    template <int LO>
+    static constexpr int kg() { return LO == FMT_BF16 ? 1 : CPT < 4 ? CPT : 4; }
+    template <int LO>
+    static constexpr int kr() { return CPT / kg<LO>(); }
     template <int FMT>
     static constexpr int kstride() { return FMT == FMT_E2M1 ? KS4 : FMT == FMT_E4M3 ? KS8 : KSB; }
     template <int FMT>
@@ -215,14 +232,21 @@ DMA_DEV v2i lds_read_tr8(unsigned addr) { return __builtin_amdgcn_ds_read_tr8_b6
 // The lane-dependent parts of the LDS addresses of a step never change during the kernel: the low-format ones are
 // computed once (LaneOffsets) and every step only adds the uniform buffer base; the high-format ones, used on a few
 // tiles per item, are recomputed where they are needed.
-template <typename C, int FMT>
+// (KG: Cfg::kg of the low format, in which the tile was loaded)
+template <typename C, int KG, int FMT>
 DMA_DEV unsigned stage_k_lane(int tid)           // where the thread's first chunk of a K tile goes (codes)
 {
     constexpr int CB = (FMT == FMT_E2M1) ? 4 : (FMT == FMT_E4M3) ? 8 : 16;     // bytes per chunk in LDS
-    return (tid / C::CPR) * C::template kstride<FMT>() + (tid % C::CPR) * CB;
+    constexpr int LPR = C::CPR / KG;                                           // lanes per key
+    return (tid / LPR) * C::template kstride<FMT>() + (tid % LPR) * (KG * CB);
 }
-template <typename C>
-DMA_DEV unsigned stage_s_lane(int tid) { return (tid / C::CPR) * C::CPR + tid % C::CPR; }   // ... its scale byte
+template <typename C, int KG>
+DMA_DEV unsigned stage_s_lane(int tid)           // ... its scale byte
+{
+    constexpr int LPR = C::CPR / KG;
+    const int block = tid % LPR * KG / 4;
+    return tid / LPR * C::SPK + (block & 1) * C::NH + (block >> 1);
+}
 template <typename C>
 DMA_DEV unsigned stage_v_lane(int tid)           // ... its first chunk of a V tile (swizzled, see Cfg::v_swizzle)
 {
@@ -236,7 +260,10 @@ DMA_DEV unsigned score_k_lane(int lane)          // the lane's key row of 32-key
     return (lane & 31) * C::template kstride<FMT>() + (uses_bf16_mfma(FMT) ? 64 : 16) * (lane >> 5);
 }
 template <typename C>
-DMA_DEV unsigned score_s_lane(int lane) { return (lane & 31) * C::CPR + 4 * (lane >> 5); }  // ... its scale dword
+DMA_DEV unsigned score_s_lane(int lane) { return (lane & 31) * C::SPK + (lane >> 5) * C::NH; }  // ... its scale bytes
+// The scale bytes of a lane's key for the h = 0 .. NH - 1 of mfma_mx, in the low bytes.
+template <typename C>
+DMA_DEV int read_key_scales(unsigned addr) { return C::NH == 2 ? (int)lds_read<uint16_t>(addr) : (int)lds_read<uint8_t>(addr); }
 // Transpose read of V: lane l16 of a 16-lane group points at row (l16 / 4) of a 4-key x 16-column patch; the row's
 // 16-byte chunks are swizzled by the row index (the same for every patch: patches start at multiples of 4).
 template <typename C>
@@ -268,20 +295,22 @@ DMA_DEV unsigned value_vmx_lane(int lane)
 template <typename C, int LO>
 struct LaneOffsets {
     unsigned stage_k, stage_s, stage_v, score_k, score_s, value_v[C::NDB];
-    DMA_DEV void init(int tid, int lane)
+    // k, s, v: LDS addresses of the low-format K codes, their scales and V, first buffer of each
+    DMA_DEV void init(int tid, int lane, unsigned k, unsigned s, unsigned v)
     {
-        stage_k = pin(stage_k_lane<C, LO>(tid));
-        stage_s = pin(stage_s_lane<C>(tid));
-        stage_v = pin(stage_v_lane<C>(tid));
-        score_k = pin(score_k_lane<C, LO>(lane));
-        score_s = pin(score_s_lane<C>(lane));
+        stage_k = pin(k + stage_k_lane<C, C::template kg<LO>(), LO>(tid));
+        stage_s = pin(s + stage_s_lane<C, C::template kg<LO>()>(tid));
+        stage_v = pin(v + stage_v_lane<C>(tid));
+        score_k = pin(k + score_k_lane<C, LO>(lane));
+        score_s = pin(s + score_s_lane<C>(lane));
 #pragma unroll
-        for (int db = 0; db < C::NDB; ++db) value_v[db] = pin(value_v_lane<C>(lane, db));
+        for (int db = 0; db < C::NDB; ++db) value_v[db] = pin(v + value_v_lane<C>(lane, db));
     }
 };
 
-// Chunk r of thread tid is 16-byte chunk r * T + tid of the dense tile: key r * (T / CPR) + tid / CPR.
-template <typename C>
+// Run i of thread tid is KG 16-byte chunks from chunk (i * T + tid) * KG of the dense tile on.  V: KG = 1, chunk r is of key
+// r * (T / CPR) + tid / CPR.
+template <typename C, int KG = 1>
 DMA_DEV void load_tile(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat, int row0, int S, int tid)
 {
     // rows [row0, row0 + BT) of the [S, D] bf16 matrix `mat` (uniform); rows >= S read as zero.
@@ -292,9 +321,9 @@ DMA_DEV void load_tile(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat, int
     // S = 4096 with the tensor scale (and load_key_amax below) 170.9 -> 161.8.  Loads from a scalar base per chunk
     // round, unbounded, for whole tiles are no faster (S = 8192 410 us, the bounded ones 408).
     const rsrc_t rs = make_rsrc(mat, (uint32_t)S * (C::D * 2));
-    const unsigned off = pin((unsigned)row0 * (C::D * 2) + (unsigned)fresh(tid) * 16u);
+    const unsigned off = pin((unsigned)row0 * (C::D * 2) + (unsigned)fresh(tid) * (16u * KG));
 #pragma unroll
-    for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::T * 16);
+    for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + (r / KG * C::T * KG + r % KG) * 16);
 }
 
 // V tile in the thread mapping of the MX-format P V (vmx_thread).
@@ -310,121 +339,130 @@ DMA_DEV void load_tile_vmx(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat,
     for (int r = 0; r < C::CPT; ++r) reg[r] = buffer_load16(rs, off + r * C::VRG * C::D * 2);
 }
 
-// K tile from registers into LDS in format FMT.  kdst / ksdst: LDS addresses of the codes and of the scale bytes.
-// PT: Alg. 2 Step 2: every key row is first multiplied by 2688 / rowmax; inv_sk[r] is that factor for chunk round r
+// Largest magnitude among the thread's run of KG chunks, and of the MX block it belongs to (KG = 2: the block's other half is
+// the neighbouring lane's), as 15-bit patterns (see amax8_bf16_bits).
+template <typename C, int KG, int KR>
+DMA_DEV void block_max_bits(unsigned (&am)[KR], const v4i (&reg)[C::CPT])
+{
+    static_assert(KG == 4 || KG == 2, "half an MX block or a whole one per run");
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+        unsigned a = 0;
+#pragma unroll
+        for (int t = 0; t < KG; ++t) {
+            const unsigned b = amax8_bf16_packed(reg[i * KG + t]);
+            a = t == 0 ? b : pk_max_u16(a, b);
+        }
+        am[i] = max(a & 0xffffu, a >> 16);
+    }
+    if constexpr (KG == 2) {
+#pragma unroll
+        for (int i = 0; i < KR; ++i) am[i] = max(am[i], (unsigned)__builtin_amdgcn_mov_dpp((int)am[i], 0xB1, 0xF, 0xF, true));
+    }
+}
+
+// K tile from registers (loaded in runs of KG chunks) into LDS in format FMT.  kdst / ksdst: LDS addresses of the codes and
+// of the scale bytes.
+// PT: Alg. 2 Step 2: every key row is first multiplied by 2688 / rowmax; inv_sk[i] is that factor for run i
 // (the caller computes it once per tile for both formats, see key_token_scales).
 // k_lane / s_lane: stage_k_lane / stage_s_lane of the thread.
-template <typename C, int FMT, bool PT>
+template <typename C, int KG, int FMT, bool PT>
 DMA_DEV void stage_k(const v4i (&reg)[C::CPT], unsigned kdst, unsigned ksdst, unsigned k_lane, unsigned s_lane,
-                     const float (&inv_sk)[C::CPT], const float (&bam)[C::CPT])
+                     const float (&inv_sk)[C::CPT / KG], const float (&bam)[C::CPT / KG])
 {
-    // bam[r] (PT): the largest magnitude of the lane's MX block in round r before the row is scaled; rounding is monotone,
+    // bam[i] (PT): the largest magnitude of the run's MX block before the row is scaled; rounding is monotone,
     // so the block maximum of the scaled values is the scaled block maximum.
-    constexpr int KPR = C::T / C::CPR;                       // keys per chunk round
+    constexpr int KR = C::CPT / KG;
+    constexpr int KPR = C::T * KG / C::CPR;                  // keys per round of runs
     constexpr int STRIDE = C::template kstride<FMT>();
     const unsigned ka = pin(kdst + k_lane);
     const unsigned sa = pin(ksdst + s_lane);                  // every lane stores its block's scale: no divergence
-    if constexpr (FMT == FMT_E2M1 && !PT) {
-        // Keys are not pre-scaled: block maximum and converts work on the packed bf16 directly.  The thread's chunks go
-        // through every step side by side: one after the other each is a chain of dependent instructions with wait states
-        // between them (DPP sources, converts that fill one dword byte by byte: 19 s_nop per tile, now 1).  Bound by that chain
-        // where a wave has nothing beside it, by power at the large sizes: 4 / 1 heads, S = 8192 177.5 -> 174.8 us; 32 / 8,
-        // S = 2500 68.3 -> 67.5; S = 8192 at D = 64 303.1 -> 298.3; S = 32768 5967 -> 5937.
-        unsigned am[C::CPT], w4[C::CPT];
-        int code[C::CPT];
-        float sc[C::CPT];
+    auto put_scale = [&](int i, int code) __attribute__((always_inline)) { lds_write<uint8_t>(sa + i * KPR * C::SPK, (uint8_t)code); };
+    if constexpr (FMT == FMT_BF16) {
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) am[r] = amax8_bf16_bits(reg[r]);
-        quad_max_u32(am);
+        for (int r = 0; r < C::CPT; ++r) lds_write<v4i>(ka + r * KPR * STRIDE, reg[r]);
+    } else if constexpr (FMT == FMT_E2M1) {
+        // The thread's chunks go through every step side by side: one after the other each is a chain of dependent instructions
+        // (converts that fill one dword byte by byte).
+        unsigned w4[KR][KG];
+        int code[KR];
+        float sc[KR];
+        unsigned am[KR];
+        if constexpr (!PT) block_max_bits<C, KG, KR>(am, reg);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            code[r] = max((int)(am[r] >> 7) - 2, 0);
-            sc[r] = cvt_scale_operand(code[r]);
-        }
-        static_for<4>([&](auto T) __attribute__((always_inline)) {
-#pragma unroll
-            for (int r = 0; r < C::CPT; ++r) put_e2m1_bf16<decltype(T)::value>(w4[r], reg[r][(int)T], sc[r]);
-        });
-#pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            lds_write<int>(ka + r * KPR * STRIDE, (int)w4[r]);
-            lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code[r]);
-        }
-        return;
-    }
-    if constexpr (FMT == FMT_E2M1 && PT) {
-        // Scaled keys, side by side too; the chunks' elements are unpacked pair by pair, right before their convert.  With
-        // the block maxima on packed bf16 (key_token_scales), 32 / 8 heads, S = 4096 with the tensor scale, its maxima
-        // included, 157.0 -> 153.2 us, S = 8192 526 -> 513, per token 500 -> 499.
-        unsigned w4[C::CPT];
-        int code[C::CPT];
-        float sc[C::CPT];
-#pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            code[r] = e8m0_code<FMT_E2M1>(__fmul_rn(bam[r], inv_sk[r]));
-            sc[r] = cvt_scale_operand(code[r]);
-            w4[r] = 0;
+        for (int i = 0; i < KR; ++i) {
+            if constexpr (PT) code[i] = e8m0_code<FMT_E2M1>(__fmul_rn(bam[i], inv_sk[i]));
+            else code[i] = max((int)(am[i] >> 7) - 2, 0);
+            sc[i] = cvt_scale_operand(code[i]);
         }
         static_for<4>([&](auto T) __attribute__((always_inline)) {
             constexpr int t = decltype(T)::value;
 #pragma unroll
-            for (int r = 0; r < C::CPT; ++r)
-                w4[r] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w4[r], __fmul_rn(bf16_lo(reg[r][t]), inv_sk[r]), __fmul_rn(bf16_hi(reg[r][t]), inv_sk[r]), sc[r], t);
+            for (int i = 0; i < KR; ++i)
+#pragma unroll
+                for (int u = 0; u < KG; ++u) {
+                    const int r = i * KG + u;
+                    if constexpr (!PT) {
+                        // keys are not pre-scaled: block maximum and converts work on the packed bf16 directly
+                        put_e2m1_bf16<t>(w4[i][u], reg[r][t], sc[i]);
+                    } else {
+                        if (t == 0) w4[i][u] = 0;
+                        w4[i][u] = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w4[i][u], __fmul_rn(bf16_lo(reg[r][t]), inv_sk[i]), __fmul_rn(bf16_hi(reg[r][t]), inv_sk[i]), sc[i], t);
+                    }
+                }
         });
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            lds_write<int>(ka + r * KPR * STRIDE, (int)w4[r]);
-            lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code[r]);
+        for (int i = 0; i < KR; ++i) {
+            if constexpr (KG == 4) lds_write<v4i>(ka + i * KPR * STRIDE, v4i{(int)w4[i][0], (int)w4[i][1], (int)w4[i][2], (int)w4[i][3]});
+            else lds_write<v2i>(ka + i * KPR * STRIDE, v2i{(int)w4[i][0], (int)w4[i][1]});
+            put_scale(i, code[i]);
         }
-        return;
-    }
-    if constexpr ((FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) && !PT) {
-        // The same way to the decoded 8-bit formats: 140 vector instructions per tile instead of 208 with a detour through
-        // binary32.  S = 16384, 40 / 8 heads, all MXFP8 2481 -> 2427 us; 4 / 1 heads S = 3700 58.6 -> 52.4; D = 64 S = 4096
-        // 101.8 -> 95.6; the high-format tiles of the default pair, 32 / 8 heads S = 613 18.5 -> 17.8.  (A NaN among the keys
-        // makes its scores NaN here, as in the MXFP4 staging.)
-        unsigned am[C::CPT], lim[C::CPT];
-        float sc[C::CPT];
+    } else if constexpr ((FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) && !PT) {
+        // On packed bf16 too.  (A NaN among the keys makes its scores NaN here, as in the MXFP4 staging.)
+        unsigned am[KR];
+        block_max_bits<C, KG, KR>(am, reg);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) am[r] = amax8_bf16_bits(reg[r]);
-        quad_max_u32(am);
+        for (int i = 0; i < KR; ++i) {
+            const int code = max((int)(am[i] >> 7) - (FMT == FMT_E5M2_X ? 15 : 8), 0);
+            const unsigned lim = mx8_limit<FMT>(code);
+            const float sc = mx8_scale(code);
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            const int code = max((int)(am[r] >> 7) - (FMT == FMT_E5M2_X ? 15 : 8), 0);
-            lim[r] = mx8_limit<FMT>(code);
-            sc[r] = mx8_scale(code);
+            for (int u = 0; u < KG; ++u) {
+                v4i d;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) d[t] = quant_dequant2_bf16<FMT>(reg[i * KG + u][t], (unsigned)reg[i * KG + u][t] & 0x7fff7fffu, lim, sc);
+                lds_write<v4i>(ka + i * KPR * STRIDE + 16 * u, d);
+            }
         }
+    } else {
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) {
-            v4i d;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] = quant_dequant2_bf16<FMT>(reg[r][t], (unsigned)reg[r][t] & 0x7fff7fffu, lim[r], sc[r]);
-            lds_write<v4i>(ka + r * KPR * STRIDE, d);
-        }
-        return;
-    }
-#pragma unroll
-    for (int r = 0; r < C::CPT; ++r) {
-        if constexpr (FMT == FMT_BF16) {
-            lds_write<v4i>(ka + r * KPR * STRIDE, reg[r]);
-        } else {
-            float x[8];
-            unpack8<false>(reg[r], 1.f, x);
+        for (int i = 0; i < KR; ++i) {
             float amax;
             if constexpr (PT) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = __fmul_rn(x[e], inv_sk[r]);
-                amax = __fmul_rn(bam[r], inv_sk[r]);
+                amax = __fmul_rn(bam[i], inv_sk[i]);
             } else {
-                amax = quad_max(amax8(x));
+                amax = 0.f;
+#pragma unroll
+                for (int u = 0; u < KG; ++u) {
+                    float x[8];
+                    unpack8<false>(reg[i * KG + u], 1.f, x);
+                    amax = fmaxf(amax, amax8(x));
+                }
+                if constexpr (KG == 2) amax = fmaxf(amax, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(amax), 0xB1, 0xF, 0xF, true)));
             }
             const int code = e8m0_code<FMT>(amax);
-            if constexpr (FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) {
-                lds_write<v4i>(ka + r * KPR * STRIDE, quant_dequant8<FMT>(x, code));
-            } else {
-                lds_write<v2i>(ka + r * KPR * STRIDE, encode8_e4m3(x, code));
-                lds_write<uint8_t>(sa + r * KPR * C::CPR, (uint8_t)code);
+#pragma unroll
+            for (int u = 0; u < KG; ++u) {
+                float x[8];
+                unpack8<false>(reg[i * KG + u], 1.f, x);
+                if constexpr (PT) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] = __fmul_rn(x[e], inv_sk[i]);
+                }
+                if constexpr (FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) lds_write<v4i>(ka + i * KPR * STRIDE + 16 * u, quant_dequant8<FMT>(x, code));
+                else lds_write<v2i>(ka + i * KPR * STRIDE + 8 * u, encode8_e4m3(x, code));
             }
+            if constexpr (FMT == FMT_E4M3) put_scale(i, code);
         }
     }
 }
@@ -498,8 +536,8 @@ template <int FMT, int H>
 DMA_DEV v16f mfma_mx(const v8i& a, const v8i& b, const v16f& c, int sa, int sb)
 {
     constexpr int code = (FMT == FMT_E2M1) ? 4 : 0;
-    // sa: the K-side scale sits in byte 0 of its own dword; sb: byte H of the query scale dword
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, code, code, 0, sa, H, sb);
+    // the scales of step H are byte H of either dword
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, code, code, H, sa, H, sb);
 }
 
 DMA_DEV v8i widen(const v4i& lo) { return v8i{lo[0], lo[1], lo[2], lo[3], 0, 0, 0, 0}; }
@@ -529,21 +567,20 @@ DMA_DEV void score_products(v16f (&s)[C::NB], const v4i (&qr)[QR], int qscale, u
 
     // ---- S^T = K . Q^T.  Operands are fetched from LDS ahead of the MFMAs that use them.
     if constexpr (FMT == FMT_E2M1) {
-        // operands of two 32-key blocks at a time (2 * NH 16-byte reads + 2 scale dwords) ahead of their MFMAs,
+        // operands of two 32-key blocks at a time (2 * NH 16-byte reads + 2 of scales) ahead of their MFMAs,
         // which go h-major so that the two MFMAs into one accumulator are not adjacent
-        // scale of MX block 2h + g of the lane's key: byte 0 of the dword at chunk 4 (2h + g) of the key's scale row
         const unsigned sa = pin(kssrc + s_lane);
         constexpr int U = C::NB < 2 ? C::NB : 2;
         static_assert(C::NB % U == 0, "one 32-key block or an even number of them");
         v4i a[2][U][C::NH];
-        int ksc[2][U][C::NH];
+        int ksc[2][U];
         auto fetch = [&](int pair) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int kb = U * pair + u;
+                ksc[pair & 1][u] = read_key_scales<C>(sa + kb * 32 * C::SPK);
 #pragma unroll
                 for (int h = 0; h < C::NH; ++h) {
-                    ksc[pair & 1][u][h] = lds_read<int>(sa + kb * 32 * C::CPR + 8 * h);
                     a[pair & 1][u][h] = lds_read<v4i>(ka + kb * 32 * STRIDE + 32 * h);
                 }
             }
@@ -557,7 +594,7 @@ DMA_DEV void score_products(v16f (&s)[C::NB], const v4i (&qr)[QR], int qscale, u
                 const v8i b = widen(qr[h]);
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    s[U * pair + u] = mfma_mx<FMT, h>(widen(a[pair & 1][u][h]), b, h == 0 ? sinit : s[U * pair + u], ksc[pair & 1][u][h], qscale);
+                    s[U * pair + u] = mfma_mx<FMT, h>(widen(a[pair & 1][u][h]), b, h == 0 ? sinit : s[U * pair + u], ksc[pair & 1][u], qscale);
             });
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -565,9 +602,9 @@ DMA_DEV void score_products(v16f (&s)[C::NB], const v4i (&qr)[QR], int qscale, u
         const unsigned sa = pin(kssrc + s_lane);
 #pragma unroll
         for (int kb = 0; kb < C::NB; ++kb) {
+            const int ksc = read_key_scales<C>(sa + kb * 32 * C::SPK);
             static_for<C::NH>([&](auto H) {
                 constexpr int h = H;
-                const int ksc = lds_read<int>(sa + kb * 32 * C::CPR + 8 * h);
                 const v4i lo = lds_read<v4i>(ka + kb * 32 * STRIDE + 64 * h);
                 const v4i hi = lds_read<v4i>(ka + kb * 32 * STRIDE + 64 * h + 32);
                 s[kb] = mfma_mx<FMT, h>(widen(lo, hi), widen(qr[2 * h], qr[2 * h + 1]), h == 0 ? sinit : s[kb], ksc, qscale);
@@ -672,15 +709,15 @@ DMA_DEV float move_max(v16f (&s)[C::NB], v16f (&o)[C::NDB], float mx, float& m, 
 template <typename C>
 DMA_DEV float probabilities(const v16f (&s)[C::NB], PTile<C, false>& pt)
 {
-    float psum[2] = {0.f, 0.f};
+    float psum[2];
 #pragma unroll
     for (int grp = 0; grp < 2 * C::NB; ++grp) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const float p0 = __builtin_amdgcn_exp2f(s[grp >> 1][8 * (grp & 1) + 2 * t]);
             const float p1 = __builtin_amdgcn_exp2f(s[grp >> 1][8 * (grp & 1) + 2 * t + 1]);
-            psum[0] += p0;
-            psum[1] += p1;
+            psum[0] = grp + t == 0 ? p0 : psum[0] + p0;
+            psum[1] = grp + t == 0 ? p1 : psum[1] + p1;
             const v2bf h2 = __builtin_convertvector(v2f{p0, p1}, v2bf);
             pt.b[grp][2 * t] = h2[0];
             pt.b[grp][2 * t + 1] = h2[1];
@@ -828,85 +865,57 @@ DMA_DEV void value_part(unsigned vsrc, int lane, v16f (&o)[C::NDB], const PTile<
 // ---------------------------------------------------------------------------------------------
 // The kernel
 // ---------------------------------------------------------------------------------------------
-// Alg. 2 Step 2 for the keys of a tile: per chunk round the row maximum over the CPR lanes of the row, S_q into LDS
+// Alg. 2 Step 2 for the keys of a tile: per run the row maximum over the lanes of the row (two or four), S_q into LDS
 // (one float per key at ktsdst), 1 / S_q returned for the quantization (inv_sk), and with it the largest magnitude of
 // the lane's MX block before the scaling (bam), from which stage_k gets the block's shared scale without a second pass.
+// The lanes of a row divide alike, the first one stores S_q.
 // kam / given: the maximum of the group each key row belongs to, when the caller supplies group maxima (a coarser
 // granularity than the row) instead of the row's own maximum.
-// The two divisions of a row's scale are the expensive part and every lane of a row would repeat them: the lanes of a
-// quad take one chunk round each instead (lane q of the quad: round base + q), divide once, and hand the reciprocal to
-// the other three with a quad broadcast.
-template <typename C>
-DMA_DEV void key_token_scales(const v4i (&reg)[C::CPT], float (&inv_sk)[C::CPT], float (&bam)[C::CPT], unsigned ktsdst, int tid,
-                              const float (&kam)[C::CPT], bool given)
+template <typename C, int KG, int KR>
+DMA_DEV void key_token_scales(const v4i (&reg)[C::CPT], float (&inv_sk)[KR], float (&bam)[KR], unsigned ktsdst, int tid,
+                              const float (&kam)[KR], bool given)
 {
-    constexpr int KPR = C::T / C::CPR;
-    static_assert(C::CPR % 4 == 0, "a quad of lanes lies inside one key row");
+    constexpr int LPR = C::CPR / KG, KPR = C::T / LPR;       // lanes per key, keys per round of runs
+    static_assert(LPR == 4 || LPR == 2, "a key row lies inside a quad of lanes");
     tid = fresh(tid);
-    const int key0 = tid / C::CPR, dc = tid % C::CPR, ql = tid & 3;
-    unsigned bits[C::CPT];
-    float am[C::CPT];
+    unsigned bits[KR];
+    block_max_bits<C, KG, KR>(bits, reg);                    // the lane's MX block, for stage_k
 #pragma unroll
-    for (int r = 0; r < C::CPT; ++r) bits[r] = amax8_bf16_bits(reg[r]);
-    quad_max_u32(bits);                                  // the lane's MX block (a quad of lanes), for stage_k
-#pragma unroll
-    for (int r = 0; r < C::CPT; ++r) bam[r] = am[r] = __int_as_float((int)(bits[r] << 16));
-    if (given) {
-#pragma unroll
-        for (int r = 0; r < C::CPT; ++r) am[r] = kam[r];
-    } else {                                             // ... and on to the whole row: group_max's remaining steps
-        if constexpr (C::CPR >= 8) {
-#pragma unroll
-            for (int r = 0; r < C::CPT; ++r) am[r] = half_row_max(am[r]);
-        }
-        if constexpr (C::CPR >= 16) {
-#pragma unroll
-            for (int r = 0; r < C::CPT; ++r) am[r] = full_row_max(am[r]);
-        }
-    }
-#pragma unroll
-    for (int base = 0; base < C::CPT; base += 4) {
-        float mine = am[base];
-#pragma unroll
-        for (int j = 1; j < 4; ++j)
-            if (base + j < C::CPT) mine = (ql == j) ? am[base + j] : mine;
-        float sk, inv;
-        token_scale(mine, sk, inv);
-        const int invb = __float_as_int(inv);
-        if (base + 0 < C::CPT) inv_sk[base + 0] = __int_as_float(__builtin_amdgcn_mov_dpp(invb, 0x00, 0xF, 0xF, true));
-        if (base + 1 < C::CPT) inv_sk[base + 1] = __int_as_float(__builtin_amdgcn_mov_dpp(invb, 0x55, 0xF, 0xF, true));
-        if (base + 2 < C::CPT) inv_sk[base + 2] = __int_as_float(__builtin_amdgcn_mov_dpp(invb, 0xAA, 0xF, 0xF, true));
-        if (base + 3 < C::CPT) inv_sk[base + 3] = __int_as_float(__builtin_amdgcn_mov_dpp(invb, 0xFF, 0xF, 0xF, true));
-        // S_q of round base + q goes to LDS from lane q of the row's first quad
-        if (dc < 4 && base + dc < C::CPT) lds_write<float>(ktsdst + 4 * (key0 + (base + dc) * KPR), sk);
+    for (int i = 0; i < KR; ++i) {
+        bam[i] = __int_as_float((int)(bits[i] << 16));
+        const float own = LPR == 4 ? quad_max(bam[i]) : fmaxf(bam[i], __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(bam[i]), 0xB1, 0xF, 0xF, true)));
+        float sk;
+        token_scale(given ? kam[i] : own, sk, inv_sk[i]);
+        if (tid % LPR == 0) lds_write<float>(ktsdst + 4 * (tid / LPR + i * KPR), sk);
     }
 }
 
-// The group maxima of the key rows of a tile, one per chunk round of the thread (rows >= S read as 0 by the bounds of the
+// The group maxima of the key rows of a tile, one per run of the thread (rows >= S read as 0 by the bounds of the
 // resource: a branch around each load made the wave wait for the one before).
-template <typename C>
-DMA_DEV void load_key_amax(float (&kam)[C::CPT], const float* __restrict__ amax_head, int row0, int S, int tid)
+template <typename C, int KG, int KR>
+DMA_DEV void load_key_amax(float (&kam)[KR], const float* __restrict__ amax_head, int row0, int S, int tid)
 {
-    constexpr int KPR = C::T / C::CPR;
+    constexpr int LPR = C::CPR / KG, KPR = C::T / LPR;
     const rsrc_t rs = make_rsrc(amax_head, (uint32_t)S * 4);
-    const unsigned off = (unsigned)(row0 + fresh(tid) / C::CPR) * 4;
+    const unsigned off = (unsigned)(row0 + fresh(tid) / LPR) * 4;
 #pragma unroll
-    for (int r = 0; r < C::CPT; ++r) kam[r] = buffer_load_f32(rs, off + 4 * r * KPR);
+    for (int i = 0; i < KR; ++i) kam[i] = buffer_load_f32(rs, off + 4 * i * KPR);
 }
 
 // K of one key tile from registers into LDS: in the low format if some wave computes the tile in Phase 1, in the high format
 // if some wave computes it in Phase 2.
-template <typename C, int LO, int HI, bool PT>
+template <typename C, int LO, int HI, bool PT, int KR>
 DMA_DEV void stage_key(const v4i (&kreg)[C::CPT], bool any_lo, bool any_hi, unsigned klo, unsigned kslo, unsigned khi, unsigned kshi,
-                       unsigned kts, const LaneOffsets<C, LO>& lo, int tid, const float (&kam)[C::CPT], bool kam_given)
+                       unsigned kts, const LaneOffsets<C, LO>& lo, int tid, const float (&kam)[KR], bool kam_given)
 {
-    float inv_sk[C::CPT], bam[C::CPT];
+    constexpr int KG = C::template kg<LO>();
+    float inv_sk[KR], bam[KR];
 #pragma unroll
-    for (int r = 0; r < C::CPT; ++r) inv_sk[r] = 1.f, bam[r] = 0.f;
-    if constexpr (PT) key_token_scales<C>(kreg, inv_sk, bam, kts, tid, kam, kam_given);
-    if (any_lo) stage_k<C, LO, PT>(kreg, klo, kslo, lo.stage_k, lo.stage_s, inv_sk, bam);
+    for (int i = 0; i < KR; ++i) inv_sk[i] = 1.f, bam[i] = 0.f;
+    if constexpr (PT) key_token_scales<C, KG>(kreg, inv_sk, bam, kts, tid, kam, kam_given);
+    if (any_lo) stage_k<C, KG, LO, PT>(kreg, klo, kslo, lo.stage_k, lo.stage_s, inv_sk, bam);
     if constexpr (LO != HI) {
-        if (any_hi) stage_k<C, HI, PT>(kreg, khi, kshi, stage_k_lane<C, HI>(fresh(tid)), lo.stage_s, inv_sk, bam);
+        if (any_hi) stage_k<C, KG, HI, PT>(kreg, khi, kshi, stage_k_lane<C, KG, HI>(fresh(tid)), lo.stage_s, inv_sk, bam);
     }
 }
 
@@ -932,6 +941,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     constexpr bool TWO = (LO != HI);
     constexpr int KLO = C::template kbytes<LO>();
     constexpr int KHI = TWO ? C::template kbytes<HI>() : 0;
+    constexpr int KG = C::template kg<LO>(), KR = C::template kr<LO>();
     constexpr int QRLO = C::template qregs<LO>();
     constexpr int QRHI = TWO ? C::template qregs<HI>() : 1;
     // LDS map (bytes): V, the low-format K and the high-format K (each + scale bytes) double-buffered for the pipelined
@@ -952,18 +962,19 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     static_assert(D % EPI_COLS == 0, "epilogue works on 64-column slabs");
     __shared__ __attribute__((aligned(16))) uint8_t lds[LDS_TOTAL];
     const unsigned lds0 = (unsigned)(uintptr_t)(DMA_LDS uint8_t*)lds;
-    auto v_at = [&](int buf) { return lds0 + OFF_V + buf * VB; };
-    auto klo_at = [&](int buf) { return lds0 + OFF_KLO + buf * KLO; };
-    auto kslo_at = [&](int buf) { return lds0 + OFF_KSLO + buf * C::KSC; };
+    // of buffer `buf`: V, the low-format K and the scales of either format count from the start of their first buffers (LaneOffsets)
+    auto v_at = [&](int buf) { return (unsigned)(buf * VB); };
+    auto klo_at = [&](int buf) { return (unsigned)(buf * KLO); };
+    auto kslo_at = [&](int buf) { return (unsigned)(buf * C::KSC); };
     auto khi_at = [&](int buf) { return lds0 + OFF_KHI + buf * KHI; };
-    auto kshi_at = [&](int buf) { return lds0 + OFF_KSHI + (HI_SCALES ? buf * C::KSC : 0); };
+    auto kshi_at = [&](int buf) { return (unsigned)(OFF_KSHI - OFF_KSLO + (HI_SCALES ? buf * C::KSC : 0)); };
     auto kts_at = [&](int buf) { return lds0 + OFF_KTS + (PT ? buf * BT * 4 : 0); };
     auto load_v = [&](v4i (&reg)[C::CPT], const uint16_t* mat, int row0, int S_, int tid_) __attribute__((always_inline)) {
         if constexpr (PVMX) load_tile_vmx<C>(reg, mat, row0, S_, tid_);
         else load_tile<C>(reg, mat, row0, S_, tid_);
     };
     auto pv = [&](unsigned vsrc, const LaneOffsets<C, LO>& lo_, int lane_, v16f (&o_)[C::NDB], const PTile<C, PVMX>& p_) __attribute__((always_inline)) {
-        if constexpr (PVMX) value_part<C>(vsrc, lane_, o_, p_);
+        if constexpr (PVMX) value_part<C>(lds0 + OFF_V + vsrc, lane_, o_, p_);
         else value_part<C>(vsrc, lo_.value_v, o_, p_);
     };
 
@@ -971,7 +982,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63;
     LaneOffsets<C, LO> lofs;
-    lofs.init(tid, lane);
+    lofs.init(tid, lane, lds0 + OFF_KLO, lds0 + OFF_KSLO, lds0 + OFF_V);
 
     // ---- static schedule.  The grid is one workgroup per CU; a work item is (batch, query head, group of TPW query
     // tiles), or (pair) (batch, two query heads that share a kv head, query tile): the two logical tiles of the workgroup
@@ -991,7 +1002,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const bool pair = TPW == 2 && pair_arg != 0;
     const int heads_item = pair ? 2 : 1, tstep = pair ? 0 : 1;       // query heads of an item; from one of its tiles to the next
     const int NG = pair ? N : (N + TPW - 1) / TPW;                     // items per query head or pair
-    const int group = Hq / Hkv;
+    const int group = (unsigned)Hq / (unsigned)Hkv;
     const int units = B * Hkv;
     const bool by_xcd = (units % 8 == 0) && (gridDim.x % 8 == 0);
     const int xcd = by_xcd ? (int)(blockIdx.x & 7) : 0;
@@ -1003,19 +1014,18 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     for (int round = 0;; ++round) {
         const int pos = round * workers + ((round & 1) ? workers - 1 - slot : slot);
         if (pos >= items) break;
-        const int blk = pos / (head_block * NG), within = pos % (head_block * NG);
-        const int grp = NG - 1 - within / head_block;
-        const int hx = (blk * head_block + within % head_block) * heads_item;
-        const int unit = by_xcd ? (hx / group) * 8 + xcd : hx / group;
-        const int b = unit / Hkv;
-        const int hkv = unit % Hkv;
-        const int hq = hkv * group + hx % group + (pair ? wave / C::WPT : 0);       // of this wave
-        const uint16_t* qhead = q + ((int64_t)b * Hq + hq) * S * D;
-        const uint16_t* khead = k + ((int64_t)b * Hkv + hkv) * S * D;
-        const uint16_t* vhead = v + ((int64_t)b * Hkv + hkv) * S * D;
-        float* ohead = out + ((int64_t)b * Hq + hq) * S * D;
-        const float* qam_head = amax_given ? q_amax + ((int64_t)b * Hq + hq) * S : nullptr;
-        const float* kam_head = amax_given ? k_amax + ((int64_t)b * Hkv + hkv) * S : nullptr;
+        // (unsigned: a signed division is half as long again, and nothing runs beside this)
+        const unsigned blk = (unsigned)pos / (unsigned)(head_block * NG), within = (unsigned)pos % (unsigned)(head_block * NG);
+        const int grp = NG - 1 - (int)(within / (unsigned)head_block);
+        const unsigned hx = (blk * head_block + within % (unsigned)head_block) * heads_item;
+        const unsigned uh = hx / (unsigned)group, unit = by_xcd ? uh * 8 + xcd : uh;                  // unit: b * Hkv + kv head
+        const unsigned hq = unit * group + hx % (unsigned)group + (pair ? wave / C::WPT : 0);       // of this wave: b * Hq + head
+        const uint16_t* qhead = q + (int64_t)hq * S * D;
+        const uint16_t* khead = k + (int64_t)unit * S * D;
+        const uint16_t* vhead = v + (int64_t)unit * S * D;
+        float* ohead = out + (int64_t)hq * S * D;
+        const float* qam_head = amax_given ? q_amax + (int64_t)hq * S : nullptr;
+        const float* kam_head = amax_given ? k_amax + (int64_t)unit * S : nullptr;
 
         // ---- this wave's logical tile and the precision rule (Alg. 1: for query tile `it`, key tile jt is high
         // precision iff it lies in the diagonal window, it - jt < band; extensions: the first `sink` key tiles are high
@@ -1084,13 +1094,13 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // ---- prologue: key tile 0 and the query operands (all loads in flight together), tile 0 into LDS buffer 0.
         // Invariant from here on: the K/V registers hold the tile after the one staged last, if there is one.
         v4i kreg[C::CPT], vreg[C::CPT];
-        float kam[C::CPT];                               // group maxima of the key rows in kreg (when given)
+        float kam[KR];                                   // group maxima of the key rows in kreg (when given)
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) kam[r] = 0.f;
+        for (int i = 0; i < KR; ++i) kam[i] = 0.f;
         auto load_k = [&](int jt) __attribute__((always_inline)) {                   // K tile jt (and its group maxima) into the registers
-            load_tile<C>(kreg, khead, jt * BT, S, tid);
+            load_tile<C, KG>(kreg, khead, jt * BT, S, tid);
             if constexpr (PT) {
-                if (amax_given) load_key_amax<C>(kam, kam_head, jt * BT, S, tid);
+                if (amax_given) load_key_amax<C, KG>(kam, kam_head, jt * BT, S, tid);
             }
         };
         PTile<C, PVMX> pb;
@@ -1128,7 +1138,7 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             }
         }
         auto stage_value = [&](int buf) __attribute__((always_inline)) {                 // V of the registers into LDS buffer buf
-            if constexpr (PVMX) stage_v_mx<C>(vreg, v_at(buf), tid);
+            if constexpr (PVMX) stage_v_mx<C>(vreg, lds0 + OFF_V + v_at(buf), tid);
             else stage_v<C>(vreg, v_at(buf), lofs.stage_v);
         };
         auto stage_next = [&](int jt, int buf) __attribute__((always_inline)) {         // tile jt from the K/V registers into LDS buffer buf
@@ -1163,12 +1173,16 @@ dma_attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // 246.0 -> 236.4, S = 8192 per token 513 -> 496, D = 64 S = 5200 134.9 -> 129.9; 8k prefill 407.5 -> 397.5, with the MX-format
         // P V 577 -> 524.  V staged with K at the top costs 0.6 % at S = 32768, both of them behind the score MFMAs 1.8 %, in half
         // of the waves 2 %.  Bound by vector issue, and by power at the full sizes (2.2 GHz of 2.4 at S = 32768).
+        // With the Step-2 scale and 8-bit keys at D = 64 the registers allow K behind the score MFMAs too: 16 / 8 heads S = 8000
+        // 223.3 -> 218.6 us (fewer workgroups per CU, and shorter batches lose from that: 64 x 32 / 8 S = 200 55.3 -> 59.2, 61.1
+        // before the keys were staged by blocks).
+        constexpr bool K_EARLY = !PT || (D == 64 && LO != FMT_E2M1);
         auto main_step = [&](int jt) __attribute__((always_inline)) {
             const int buf = jt & 1, nxt = buf ^ 1;
             stage_key<C, LO, HI, PT>(kreg, true, false, klo_at(nxt), kslo_at(nxt), khi_at(nxt), kshi_at(nxt), kts_at(nxt), lofs, tid, kam, amax_given);
             score_part<C, LO, false, PT, PVMX>(qr_lo, qs_lo, klo_at(buf), kslo_at(buf), lofs.score_k, lofs.score_s, kts_at(buf), q_sq, false, BT, qrow_in_tile, lane, c, m, mfloor, l, o, pb,
-                                     [&]() __attribute__((always_inline)) { if (!PT) load_k(jt + 2); });
-            if (PT) load_k(jt + 2);
+                                     [&]() __attribute__((always_inline)) { if (K_EARLY) load_k(jt + 2); });
+            if (!K_EARLY) load_k(jt + 2);
             stage_value(nxt);
             load_v(vreg, vhead, (jt + 2) * BT, S, tid);
             pv(v_at(buf), lofs, lane, o, pb);

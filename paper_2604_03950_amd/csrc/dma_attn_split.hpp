@@ -33,6 +33,7 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     static_assert(BT % ROWS == 0, "an item lies inside one logical tile");
     constexpr int KLO = C::template kbytes<LO>();
     constexpr int KHI = TWO ? C::template kbytes<HI>() : 0;
+    constexpr int KG = C::template kg<LO>(), KR = C::template kr<LO>();
     constexpr int QRLO = C::template qregs<LO>();
     constexpr int QRHI = TWO ? C::template qregs<HI>() : 1;
     // LDS map (bytes): the row maxima of the waves' shares (double-buffered), then V and K as in the unsplit kernel, all
@@ -52,11 +53,11 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     static_assert(LDS_TOTAL <= 160 * 1024, "LDS budget of one CU");
     __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_TOTAL];
     const unsigned lds0 = (unsigned)(uintptr_t)(DMA_LDS uint8_t*)lds;
-    auto v_at = [&](int buf) { return lds0 + OFF_V + buf * C::VBYTES; };
-    auto klo_at = [&](int buf) { return lds0 + OFF_KLO + buf * KLO; };
-    auto kslo_at = [&](int buf) { return lds0 + OFF_KSLO + buf * C::KSC; };
+    auto v_at = [&](int buf) { return (unsigned)(buf * C::VBYTES); };              // as in the unsplit kernel
+    auto klo_at = [&](int buf) { return (unsigned)(buf * KLO); };
+    auto kslo_at = [&](int buf) { return (unsigned)(buf * C::KSC); };
     auto khi_at = [&](int buf) { return lds0 + OFF_KHI + buf * KHI; };
-    auto kshi_at = [&](int buf) { return lds0 + OFF_KSHI + (HI_SCALES ? buf * C::KSC : 0); };
+    auto kshi_at = [&](int buf) { return (unsigned)(OFF_KSHI - OFF_KSLO + (HI_SCALES ? buf * C::KSC : 0)); };
     auto kts_at = [&](int buf) { return lds0 + OFF_KTS + (PT ? buf * BT * 4 : 0); };
 
     const bool amax_given = PT && q_amax != nullptr;
@@ -66,13 +67,13 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     const int rg = wave % RG, kh = wave / RG;            // the wave's query rows and its share of the keys
     const int key0 = kh * C::NB * 32;
     LaneOffsets<C, LO> lofs;
-    lofs.init(tid, lane);
+    lofs.init(tid, lane, lds0 + OFF_KLO, lds0 + OFF_KSLO, lds0 + OFF_V);
     const unsigned mx_slot = pin((kh * RG + rg) * 128 + 4 * (lane & 31));      // the wave's maxima; the others' are a xor away
 
     // ---- static schedule: as in the unsplit kernel, with items of ROWS query rows
     const int N = (S + BT - 1) / BT;
     const int NG = (S + ROWS - 1) / ROWS;
-    const int group = Hq / Hkv;
+    const int group = (unsigned)Hq / (unsigned)Hkv;
     const int units = B * Hkv;
     const bool by_xcd = (units % 8 == 0) && (gridDim.x % 8 == 0);
     const int xcd = by_xcd ? (int)(blockIdx.x & 7) : 0;
@@ -84,19 +85,17 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
     for (int round = 0;; ++round) {
         const int pos = round * workers + ((round & 1) ? workers - 1 - slot : slot);
         if (pos >= items) break;
-        const int blk = pos / (head_block * NG), within = pos % (head_block * NG);
-        const int grp = NG - 1 - within / head_block;
-        const int hx = blk * head_block + within % head_block;
-        const int unit = by_xcd ? (hx / group) * 8 + xcd : hx / group;
-        const int b = unit / Hkv;
-        const int hkv = unit % Hkv;
-        const int hq = hkv * group + hx % group;
-        const uint16_t* qhead = q + ((int64_t)b * Hq + hq) * S * D;
-        const uint16_t* khead = k + ((int64_t)b * Hkv + hkv) * S * D;
-        const uint16_t* vhead = v + ((int64_t)b * Hkv + hkv) * S * D;
-        float* ohead = out + ((int64_t)b * Hq + hq) * S * D;
-        const float* qam_head = amax_given ? q_amax + ((int64_t)b * Hq + hq) * S : nullptr;
-        const float* kam_head = amax_given ? k_amax + ((int64_t)b * Hkv + hkv) * S : nullptr;
+        const unsigned blk = (unsigned)pos / (unsigned)(head_block * NG), within = (unsigned)pos % (unsigned)(head_block * NG);
+        const int grp = NG - 1 - (int)(within / (unsigned)head_block);
+        const unsigned hx = blk * head_block + within % (unsigned)head_block;
+        const unsigned uh = hx / (unsigned)group, unit = by_xcd ? uh * 8 + xcd : uh;                  // unit: b * Hkv + kv head
+        const unsigned hq = unit * group + hx % (unsigned)group;                                      // b * Hq + head
+        const uint16_t* qhead = q + (int64_t)hq * S * D;
+        const uint16_t* khead = k + (int64_t)unit * S * D;
+        const uint16_t* vhead = v + (int64_t)unit * S * D;
+        float* ohead = out + (int64_t)hq * S * D;
+        const float* qam_head = amax_given ? q_amax + (int64_t)hq * S : nullptr;
+        const float* kam_head = amax_given ? k_amax + (int64_t)unit * S : nullptr;
 
         const int row0 = grp * ROWS, it = row0 / BT;
         const int qrow = row0 + rg * 32, qrow_in_tile = qrow - it * BT;
@@ -128,26 +127,26 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
         for (int db = 0; db < C::NDB; ++db) o[db] = v16f{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 
         v4i kreg[C::CPT], vreg[C::CPT];
-        float kam[C::CPT];
+        float kam[KR];
 #pragma unroll
-        for (int r = 0; r < C::CPT; ++r) kam[r] = 0.f;
+        for (int i = 0; i < KR; ++i) kam[i] = 0.f;
         auto load_k = [&](int jt) __attribute__((always_inline)) {
-            load_tile<C>(kreg, khead, jt * BT, S, tid);
+            load_tile<C, KG>(kreg, khead, jt * BT, S, tid);
             if constexpr (PT) {
-                if (amax_given) load_key_amax<C>(kam, kam_head, jt * BT, S, tid);
+                if (amax_given) load_key_amax<C, KG>(kam, kam_head, jt * BT, S, tid);
             }
         };
         auto load_v = [&](int jt) __attribute__((always_inline)) { load_tile<C>(vreg, vhead, jt * BT, S, tid); };
         auto stage_key = [&](int jt, bool lo_known) __attribute__((always_inline)) {                 // K tile jt from the registers into LDS
             const int buf = jt & 1;
-            float inv_sk[C::CPT], bam[C::CPT];
+            float inv_sk[KR], bam[KR];
 #pragma unroll
-            for (int r = 0; r < C::CPT; ++r) inv_sk[r] = 1.f, bam[r] = 0.f;
-            if constexpr (PT) key_token_scales<C>(kreg, inv_sk, bam, kts_at(buf), tid, kam, amax_given);
+            for (int i = 0; i < KR; ++i) inv_sk[i] = 1.f, bam[i] = 0.f;
+            if constexpr (PT) key_token_scales<C, KG>(kreg, inv_sk, bam, kts_at(buf), tid, kam, amax_given);
             const bool h = !lo_known && tile_hi(jt);
-            if (!h) stage_k<C, LO, PT>(kreg, klo_at(buf), kslo_at(buf), lofs.stage_k, lofs.stage_s, inv_sk, bam);
+            if (!h) stage_k<C, KG, LO, PT>(kreg, klo_at(buf), kslo_at(buf), lofs.stage_k, lofs.stage_s, inv_sk, bam);
             if constexpr (TWO) {
-                if (h) stage_k<C, HI, PT>(kreg, khi_at(buf), kshi_at(buf), stage_k_lane<C, HI>(fresh(tid)), lofs.stage_s, inv_sk, bam);
+                if (h) stage_k<C, KG, HI, PT>(kreg, khi_at(buf), kshi_at(buf), stage_k_lane<C, KG, HI>(fresh(tid)), lofs.stage_s, inv_sk, bam);
             }
         };
 
@@ -191,9 +190,9 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
             const unsigned kts = kts_at(buf) + 4 * key0;
             v16f s[C::NB];
             if (main || !tile_hi(jt)) {
-                score_products<C, LO, PT>(s, qr_lo, qs_lo, klo_at(buf) + key0 * C::template kstride<LO>(), kslo_at(buf) + key0 * C::CPR, lofs.score_k, lofs.score_s, kts, q_sq, g, c, m);
+                score_products<C, LO, PT>(s, qr_lo, qs_lo, klo_at(buf) + key0 * C::template kstride<LO>(), kslo_at(buf) + key0 * C::SPK, lofs.score_k, lofs.score_s, kts, q_sq, g, c, m);
             } else if constexpr (TWO) {
-                score_products<C, HI, PT>(s, qr_hi, qs_hi, khi_at(buf) + key0 * C::template kstride<HI>(), kshi_at(buf) + key0 * C::CPR, score_k_lane<C, HI>(fresh(lane)), lofs.score_s, kts, q_sq, g, c, m);
+                score_products<C, HI, PT>(s, qr_hi, qs_hi, khi_at(buf) + key0 * C::template kstride<HI>(), kshi_at(buf) + key0 * C::SPK, score_k_lane<C, HI>(fresh(lane)), lofs.score_s, kts, q_sq, g, c, m);
             }
             if (!main) mask_scores<C>(s, causal && jt == it, causal ? BT : min(BT, S - jt * BT), qrow_in_tile, key0, ln & 31, g);
             float mx = score_max<C>(s);

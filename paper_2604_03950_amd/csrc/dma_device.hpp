@@ -33,6 +33,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef short v2s __attribute__((ext_vector_type(2)));
 typedef short v4s __attribute__((ext_vector_type(4)));
+typedef unsigned short v2us __attribute__((ext_vector_type(2)));
 typedef short v8s __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -108,25 +109,19 @@ DMA_DEV void token_scale(float amax, float& s_q, float& inv_s_q)
     inv_s_q = ok ? __fdiv_rn(2688.0f, amax) : 1.0f;
 }
 
-// quad_max for N unsigned values per lane, side by side (a DPP source needs two wait states after its last write).
-template <int N>
-DMA_DEV void quad_max_u32(unsigned (&a)[N])
+// Largest magnitude among eight packed bf16, as 15-bit patterns (sign cleared), one of the even and one of the odd elements; the
+// patterns of non-negative bf16 order like unsigned integers.  Biased exponent = pattern >> 7.
+DMA_DEV unsigned amax8_bf16_packed(const v4i& w)
 {
-#pragma unroll
-    for (int i = 0; i < N; ++i) a[i] = max(a[i], (unsigned)__builtin_amdgcn_mov_dpp((int)a[i], 0xB1, 0xF, 0xF, true));
-#pragma unroll
-    for (int i = 0; i < N; ++i) a[i] = max(a[i], (unsigned)__builtin_amdgcn_mov_dpp((int)a[i], 0x4E, 0xF, 0xF, true));
-}
-
-// Largest magnitude among eight packed bf16, returned as its 15-bit pattern (sign cleared); the
-// patterns of non-negative bf16 order like unsigned integers.  Biased exponent = result >> 7.
-DMA_DEV unsigned amax8_bf16_bits(const v4i& w)
-{
-    typedef unsigned short v2us __attribute__((ext_vector_type(2)));
     const v2us a0 = __builtin_bit_cast(v2us, w[0] & 0x7fff7fff), a1 = __builtin_bit_cast(v2us, w[1] & 0x7fff7fff);
     const v2us a2 = __builtin_bit_cast(v2us, w[2] & 0x7fff7fff), a3 = __builtin_bit_cast(v2us, w[3] & 0x7fff7fff);
-    const v2us m = __builtin_elementwise_max(__builtin_elementwise_max(a0, a1), __builtin_elementwise_max(a2, a3));
-    return max((unsigned)m[0], (unsigned)m[1]);
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_elementwise_max(a0, a1), __builtin_elementwise_max(a2, a3)));
+}
+
+// Element-wise maximum of two packed 16-bit magnitudes (two per dword).
+DMA_DEV unsigned pk_max_u16(unsigned a, unsigned b)
+{
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(v2us, a), __builtin_bit_cast(v2us, b)));
 }
 
 // E8M0 byte of a block with absolute maximum amax >= 0 (Alg. 2 Steps 6-7):
@@ -264,7 +259,6 @@ DMA_DEV unsigned mx8_limit(int code)
 template <int FMT>
 DMA_DEV int quant_dequant2_bf16(int w, unsigned mag, unsigned lim, float sc)
 {
-    typedef unsigned short v2us __attribute__((ext_vector_type(2)));
     const unsigned m = __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(v2us, mag), __builtin_bit_cast(v2us, lim)));
     const v2bf x = __builtin_bit_cast(v2bf, m | ((unsigned)w & 0x80008000u));
     v2s q = __builtin_bit_cast(v2s, x);                   // the convert fills the lower half, the upper one is not used
@@ -324,14 +318,6 @@ DMA_DEV float cross_half_sum(float x)
 // ---------------------------------------------------------------------------------------------
 // MX-format P V: helpers for blocks that run along the key axis
 // ---------------------------------------------------------------------------------------------
-typedef unsigned short v2us __attribute__((ext_vector_type(2)));
-
-// Element-wise maximum of two packed 16-bit magnitudes (two per dword).
-DMA_DEV unsigned pk_max_u16(unsigned a, unsigned b)
-{
-    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(v2us, a), __builtin_bit_cast(v2us, b)));
-}
-
 // Maximum over the lanes that share lane % CW (CW = 4, 8 or 16), of two packed 16-bit magnitudes: rotations inside
 // the 16-lane rows, then the rows pairwise (v_permlane16_swap), then the two half-waves (v_permlane32_swap).
 // (One dword at a time, in a scalar variable of its own: see put_e2m1_bf16 for why no vector element is named in
