@@ -418,19 +418,31 @@ DMA_DEV void stage_k(const v4i (&reg)[C::CPT], unsigned kdst, unsigned ksdst, un
             put_scale(i, code[i]);
         }
     } else if constexpr ((FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) && !PT) {
-        // On packed bf16 too.  (A NaN among the keys makes its scores NaN here, as in the MXFP4 staging.)
+        // On packed bf16 too, with converts that saturate instead of a clamp in front of them (a mask, a minimum and a bit field
+        // insert per dword, a third of the tile's staging): S = 16384, 40 / 8 heads, all MXFP8 2415 -> 2395 us; the high-format
+        // tiles of the default pair, 8 x 32 / 8 heads S = 500 34.9 -> 34.6, 32 / 8 S = 613 17.5 -> 17.3.
         unsigned am[KR];
+        int q[KR][KG][4];
+        float sc[KR];
         block_max_bits<C, KG, KR>(am, reg);
 #pragma unroll
+        for (int i = 0; i < KR; ++i) sc[i] = mx8_scale(max((int)(am[i] >> 7) - (FMT == FMT_E5M2_X ? 15 : 8), 0));
+        saturate_converts<true>();
+#pragma unroll
+        for (int i = 0; i < KR; ++i)
+#pragma unroll
+            for (int u = 0; u < KG; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) q[i][u][t] = quant2_bf16<FMT>(reg[i * KG + u][t], sc[i]);
+        saturate_converts<false>();
+#pragma unroll
         for (int i = 0; i < KR; ++i) {
-            const int code = max((int)(am[i] >> 7) - (FMT == FMT_E5M2_X ? 15 : 8), 0);
-            const unsigned lim = mx8_limit<FMT>(code);
-            const float sc = mx8_scale(code);
+            const float back = mx8_scale_back<FMT>(am[i], sc[i]);
 #pragma unroll
             for (int u = 0; u < KG; ++u) {
                 v4i d;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) d[t] = quant_dequant2_bf16<FMT>(reg[i * KG + u][t], (unsigned)reg[i * KG + u][t] & 0x7fff7fffu, lim, sc);
+                for (int t = 0; t < 4; ++t) d[t] = dequant2_bf16<FMT>(q[i][u][t], back);
                 lds_write<v4i>(ka + i * KPR * STRIDE + 16 * u, d);
             }
         }

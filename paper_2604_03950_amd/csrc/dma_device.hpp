@@ -245,31 +245,40 @@ DMA_DEV v4i quant_dequant8(const float (&x)[8], int code)
     else return quant_dequant8_e4m3(x, code);
 }
 
-// The same from packed bf16 magnitudes and signs (no pre-scale), one dword (two elements) at a time, without a detour
-// through binary32: clamp on the bit patterns (the limit 1.75 * 2^(code + e_max - 127) is a bf16, and patterns of
-// magnitudes order like unsigned integers; lim holds it twice), convert, decode.  mag: the dword without its signs; sc: the
-// scale 2^(code - 127) as mx8_scale gives it, which both converts take.
+// quant_dequant8 from packed bf16 (no pre-scale), a dword (two elements) at a time, without a detour through binary32 and
+// without a clamp: between saturate_converts<true>() and <false>() (MODE.FP16_OVFL) the converts to 8-bit elements give the
+// largest finite element for everything that rounds above it, infinities included, as a clamp of the operand does; NaN stays NaN.
+// The mode holds for these converts only, because the matrix instructions lose NaN and infinities in it: they are volatile
+// statements, which keep their order, and nothing else in between depends on the mode.
+template <bool ON>
+DMA_DEV void saturate_converts()
+{
+    constexpr int NO_MFMA = 0x2 | 0x4 | 0x10 | 0x80 | 0x400;      // what may pass: vector, scalar, global memory, LDS, exp2
+    if (ON) __builtin_amdgcn_sched_barrier(NO_MFMA);
+    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 23, 1), %0" :: "n"(ON ? 1 : 0));
+    if (!ON) __builtin_amdgcn_sched_barrier(NO_MFMA);
+}
 DMA_DEV float mx8_scale(int code) { return __int_as_float(max(code << 23, 0x00400000)); }
+// Two bf16 -> two elements in the lower half of the result (the upper one is not used); sc: 2^(code - 127) from mx8_scale.
 template <int FMT>
-DMA_DEV unsigned mx8_limit(int code)
+DMA_DEV int quant2_bf16(int w, float sc)
 {
-    const unsigned lim = ((unsigned)code << 7) + ((FMT == FMT_E5M2_X ? 15u : 8u) << 7 | 0x60u);
-    return lim << 16 | lim;
+    int q;
+    if constexpr (FMT == FMT_E5M2_X) asm volatile("v_cvt_scalef32_pk_bf8_bf16 %0, %1, %2" : "=v"(q) : "v"(w), "v"(sc));
+    else asm volatile("v_cvt_scalef32_pk_fp8_bf16 %0, %1, %2" : "=v"(q) : "v"(w), "v"(sc));
+    return q;
 }
+// ... and back to two bf16.
 template <int FMT>
-DMA_DEV int quant_dequant2_bf16(int w, unsigned mag, unsigned lim, float sc)
+DMA_DEV int dequant2_bf16(int q, float sc)
 {
-    const unsigned m = __builtin_bit_cast(unsigned, __builtin_elementwise_min(__builtin_bit_cast(v2us, mag), __builtin_bit_cast(v2us, lim)));
-    const v2bf x = __builtin_bit_cast(v2bf, m | ((unsigned)w & 0x80008000u));
-    v2s q = __builtin_bit_cast(v2s, x);                   // the convert fills the lower half, the upper one is not used
-    if constexpr (FMT == FMT_E5M2_X) {
-        q = __builtin_amdgcn_cvt_scalef32_pk_bf8_bf16(q, x, sc, false);
-        return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8((unsigned)__builtin_bit_cast(int, q), sc, false));
-    } else {
-        q = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(q, x, sc, false);
-        return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)__builtin_bit_cast(int, q), sc, false));
-    }
+    if constexpr (FMT == FMT_E5M2_X) return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_bf8((unsigned)q, sc, false));
+    else return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)q, sc, false));
 }
+// The scale of the way back: E4M3 has no infinity, so a block that holds one comes back as NaN, like one that holds a NaN.
+// (E5M2: 57344 x 2^113 is the infinity again.)
+template <int FMT>
+DMA_DEV float mx8_scale_back(unsigned amax_bits, float sc) { return FMT == FMT_E5M2_X || amax_bits < 0x7f80u ? sc : __int_as_float(0x7fc00000); }
 
 // Unpack a 16-byte chunk of eight bf16 into binary32, optionally pre-scaled (one multiply each).
 template <bool PRESCALE>

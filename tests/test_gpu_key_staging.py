@@ -52,3 +52,43 @@ def test_forward_sees_the_oracles_keys(oracle, D, fmt, reps):
     assert torch.isfinite(a).all()
     assert torch.equal(a, b)
     assert not torch.equal(a, forward(k ^ 0x8000))      # the keys matter at all
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("lo,hi", [("e4m3", "e4m3"), ("e5m2", "e5m2"), ("e2m1", "e4m3")])
+@pytest.mark.parametrize("reps", [1, 400])
+def test_infinities_and_nans(D, lo, hi, reps):
+    """The keys' converts to 8 bits saturate in a mode in which the matrix instructions would lose infinities and NaN: neither may
+    show.  A NaN among E4M3 or E5M2 keys, and an infinity among E4M3 ones, gives the key scores of NaN; a NaN among the values
+    reaches every row that sees it; rows before the key and the other head are untouched."""
+    from paper_2604_03950_amd import binding as dma
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    S = 3 * D + 37
+    at = 2 * D + 11
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((1, 2, S, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+
+    def forward(k, v):
+        out = dma.dma_attn_fwd(*(t.repeat(reps, 1, 1, 1) for t in (q, k, v)), diag_band_tiles=4, lo_fmt=FMTS[lo], hi_fmt=FMTS[hi],
+                               tile=64 if D == 64 else None)                  # the band covers every tile
+        assert torch.equal(out.nan_to_num(), out[:1].nan_to_num().expand_as(out))
+        return out[0]
+
+    plain = forward(k, v)
+    assert torch.isfinite(plain).all()
+    for value in (float("nan"), float("inf"), float("-inf")):
+        for column in (0, 31, D - 1):
+            bad = k.clone()
+            bad[:, 0, at, column] = value
+            out = forward(bad, v)
+            assert torch.equal(out[0, :at], plain[0, :at]) and torch.equal(out[1], plain[1]), (value, column)
+            if hi == "e4m3" or value != value:
+                assert out[0, at:].isnan().all(), (value, column)
+    for column in (0, D - 1):
+        bad = v.clone()
+        bad[:, 0, at, column] = float("nan")
+        out = forward(k, bad)
+        seen = torch.arange(D, device="cuda") == column
+        assert out[0, at:, seen].isnan().all() and torch.equal(out[0, :, ~seen], plain[0, :, ~seen]) and torch.equal(out[1], plain[1])

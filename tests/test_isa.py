@@ -110,3 +110,19 @@ def test_instances(lo, hi):
     # the pairs on the native FP8 MFMA refuse the Step-2 scale, unquantized operands have none: no instances for either
     scaled = [k for k in resources(lo, hi, "dma_attn_fwd_kernel") if k[6]] + [k for k in resources(lo, hi, "dma_attn_split_kernel") if k[5]]
     assert bool(scaled) == (lo != 0 and hi != 1), scaled
+
+
+@pytest.mark.parametrize("lo,hi", [(2, 3), (2, 4), (3, 3), (4, 4)])      # every pair with keys decoded from 8 bits
+def test_no_matrix_instruction_while_converts_saturate(lo, hi):
+    """MODE.FP16_OVFL holds for the keys' converts only: in it the matrix instructions turn NaN and infinities into numbers."""
+    on = sections = 0
+    for ln in listing(lo, hi).splitlines():
+        m = re.match(r"\s+s_setreg_imm32_b32 hwreg\(HW_REG_MODE, 23, 1\), ([01])", ln)
+        if m:
+            assert int(m.group(1)) != on, ln
+            on = int(m.group(1))
+            sections += on
+        if on:
+            assert not re.match(r"\s+(v_mfma|s_cbranch|s_branch|s_endpgm|s_barrier)", ln), ln
+        assert on or not re.match(r"\s+v_cvt_scalef32_pk_(fp8|bf8)_bf16", ln), ln
+    assert on == 0 and sections
