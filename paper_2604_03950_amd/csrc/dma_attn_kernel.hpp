@@ -608,7 +608,7 @@ DMA_DEV void score_products(v16f (&s)[C::NB], const v4i (&qr)[QR], int qscale, u
                 for (int u = 0; u < U; ++u)
                     s[U * pair + u] = mfma_mx<FMT, h>(widen(a[pair & 1][u][h]), b, h == 0 ? sinit : s[U * pair + u], ksc[pair & 1][u], qscale);
             });
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (C::NB > 1) __builtin_amdgcn_sched_barrier(0);      // one block: what follows fills its latencies
         }
     } else if constexpr (FMT == FMT_E4M3) {
         const unsigned sa = pin(kssrc + s_lane);

@@ -194,11 +194,17 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
             } else if constexpr (TWO) {
                 score_products<C, HI, PT>(s, qr_hi, qs_hi, khi_at(buf) + key0 * C::template kstride<HI>(), kshi_at(buf) + key0 * C::SPK, score_k_lane<C, HI>(fresh(lane)), lofs.score_s, kts, q_sq, g, c, m);
             }
+            // Where a wave has one 32-key block of the tile, its products are a chain of LDS reads and dependent MFMAs with nothing
+            // else to issue: the next tile's staging fills it.  4 / 1 heads S = 8192 92.1 -> 89.8 us, 8 / 2 S = 4000 53.7 -> 52.4, D = 64
+            // 16 / 8 S = 1500 19.4 -> 19.1, unquantized 4 / 1 S = 3700 43.2 -> 41.6.  Not with two blocks (32 / 8 S = 1000 22.3 -> 22.4),
+            // nor with the Step-2 scale, whose staging is long (4 / 1 S = 3700 55.2 -> 57.7: it delays the row maxima).
+            constexpr bool STAGE_EARLY = main && C::NB == 1 && !PT;
+            if (STAGE_EARLY) stage_key(jt + 1, true);
             if (!main) mask_scores<C>(s, causal && jt == it, causal ? BT : min(BT, S - jt * BT), qrow_in_tile, key0, ln & 31, g);
             float mx = score_max<C>(s);
             const unsigned maxima = lds0 + buf * MAXIMA;
             lds_write<float>(maxima + mx_slot, mx);
-            if (main || jt + 1 < nt) stage_key(jt + 1, main);
+            if (!STAGE_EARLY && (main || jt + 1 < nt)) stage_key(jt + 1, main);
             const int ahead = main || jt + 2 < nt ? jt + 2 : N;
             load_k(ahead);
             __syncthreads();
