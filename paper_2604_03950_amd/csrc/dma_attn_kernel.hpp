@@ -154,9 +154,52 @@ DMA_DEV float q_row_amax(const v4i (&raw)[C::NKK], float c)
     return cross_half_max(amax);
 }
 
-// qr / qscale from raw (scaled MFMA formats fill `qscale`: byte h = E8M0 of block 2h + g of the lane's row).
+// The operand registers of one MX block (2h + g) of the lane's row, from its four chunks; returns the block's E8M0 byte.
 // inv_sq: the factor 1 / S_q of Alg. 2 Step 2 for the lane's row (1 when the per-token scale is off): one more
 // binary32 multiply per element before the shared scales are formed.
+template <int FMT, bool PT, int N>
+DMA_DEV int make_q_block(v4i (&out)[N], const v4i (&raw)[4], float c, float inv_sq)
+{
+    float x[4][8];
+    float amax = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        unpack8<true>(raw[t], c, x[t]);
+        if constexpr (PT) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[t][e] = __fmul_rn(x[t][e], inv_sq);
+        }
+        amax = fmaxf(amax, amax8(x[t]));
+    }
+    const int code = e8m0_code<FMT>(amax);
+    if constexpr (FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) out[t] = quant_dequant8<FMT>(x[t], code);
+    } else if constexpr (FMT == FMT_E2M1) {
+        v4i r;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r[t] = encode8_e2m1(x[t], code);
+        out[0] = r;
+    } else {
+        int r[8];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const v2i e = encode8_e4m3(x[t], code);
+            r[2 * t] = e[0];
+            r[2 * t + 1] = e[1];
+        }
+        // E4M3 operand layout: VGPR 0-3 = first half of block 2h (lower lanes) / second half of
+        // block 2h (upper lanes); VGPR 4-7 the same for block 2h+1.  Each lane encoded one whole
+        // block, so the lower lanes' VGPR 4-7 trade places with the upper lanes' VGPR 0-3.
+#pragma unroll
+        for (int t = 0; t < 4; ++t) swap_halves(r[t], r[4 + t]);
+        out[0] = v4i{r[0], r[1], r[2], r[3]};
+        out[1] = v4i{r[4], r[5], r[6], r[7]};
+    }
+    return code;
+}
+
+// qr / qscale from raw (scaled MFMA formats fill `qscale`: byte h = E8M0 of block 2h + g of the lane's row).
 template <typename C, int FMT, bool PT, int QR>
 DMA_DEV void make_q(v4i (&qr)[QR], int& qscale, const v4i (&raw)[C::NKK], float c, float inv_sq)
 {
@@ -166,45 +209,13 @@ DMA_DEV void make_q(v4i (&qr)[QR], int& qscale, const v4i (&raw)[C::NKK], float 
         for (int kk = 0; kk < C::NKK; ++kk) qr[kk] = raw[kk];
     } else {
         static_for<C::NH>([&](auto H) {
-            constexpr int h = H;
-            float x[4][8];
-            float amax = 0.f;
+            constexpr int h = H, N = QR / C::NH;
+            const v4i part[4] = {raw[4 * h], raw[4 * h + 1], raw[4 * h + 2], raw[4 * h + 3]};
+            v4i r[N];
+            const int code = make_q_block<FMT, PT>(r, part, c, inv_sq);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                unpack8<true>(raw[4 * h + t], c, x[t]);
-                if constexpr (PT) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) x[t][e] = __fmul_rn(x[t][e], inv_sq);
-                }
-                amax = fmaxf(amax, amax8(x[t]));
-            }
-            const int code = e8m0_code<FMT>(amax);
-            if constexpr (FMT == FMT_E4M3_X || FMT == FMT_E5M2_X) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) qr[4 * h + t] = quant_dequant8<FMT>(x[t], code);
-            } else if constexpr (FMT == FMT_E2M1) {
-                qscale |= code << (8 * h);
-                v4i r;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) r[t] = encode8_e2m1(x[t], code);
-                qr[h] = r;
-            } else {
-                qscale |= code << (8 * h);
-                int r[8];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const v2i e = encode8_e4m3(x[t], code);
-                    r[2 * t] = e[0];
-                    r[2 * t + 1] = e[1];
-                }
-                // E4M3 operand layout: VGPR 0-3 = first half of block 2h (lower lanes) / second half of
-                // block 2h (upper lanes); VGPR 4-7 the same for block 2h+1.  Each lane encoded one whole
-                // block, so the lower lanes' VGPR 4-7 trade places with the upper lanes' VGPR 0-3.
-#pragma unroll
-                for (int t = 0; t < 4; ++t) swap_halves(r[t], r[4 + t]);
-                qr[2 * h] = v4i{r[0], r[1], r[2], r[3]};
-                qr[2 * h + 1] = v4i{r[4], r[5], r[6], r[7]};
-            }
+            for (int i = 0; i < N; ++i) qr[N * h + i] = r[i];
+            if constexpr (!uses_bf16_mfma(FMT)) qscale |= code << (8 * h);
         });
     }
 }
@@ -225,6 +236,17 @@ template <typename T>
 DMA_DEV void lds_write(unsigned addr, T v) { *(DMA_LDS T*)(uintptr_t)addr = v; }
 DMA_DEV v4s lds_read_tr16(unsigned addr) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((DMA_LDS v4s*)(uintptr_t)addr); }
 DMA_DEV v2i lds_read_tr8(unsigned addr) { return __builtin_amdgcn_ds_read_tr8_b64_v2i32((DMA_LDS v2i*)(uintptr_t)addr); }
+
+// Keeps registers that an LDS write has just taken as its data from being used for something else up to here: a vector
+// instruction that writes one of them waits until the queued LDS write has read it.  In the split kernel the allocator used the
+// V registers for the row maximum right behind the V staging: 4 / 1 heads S = 8192 93.5 us, with hold() 85.9; 8 / 2 S = 4000
+// 53.5, 49.4.
+template <typename T, int N>
+DMA_DEV void hold(const T (&reg)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" :: "v"(reg[i]));
+}
 
 // ---------------------------------------------------------------------------------------------
 // Staging of one key/value tile

@@ -155,7 +155,41 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
         v4i qr_lo[QRLO], qr_hi[QRHI];
         int qs_lo = 0, qs_hi = 0;
         float q_sq = 1.f;
-        {
+        // Four waves that share query rows make a quarter of their operands each (one of the two blocks of a lane's row, in one of the
+        // formats) and trade them through the V buffer that tile 1 is staged into behind the first barrier of the tile loop.
+        // (All four read the same rows and quantized them to both formats before, 1.2 us of an item's 8 beyond its steps.)
+        // 32 / 8 heads S = 300 11.9 -> 11.0 us, S = 613 17.2 -> 14.9, S = 700 19.0 -> 16.7; 4 / 1 heads S = 3700 all MXFP8 49.2 -> 47.4.
+        // With the Step-2 scale a row's own maximum needs the whole row; unquantized rows are only copied.
+        constexpr bool SHARE_Q = KS == 4 && !PT && LO != FMT_BF16;
+        constexpr int NL = QRLO / C::NH, NHI = TWO ? QRHI / C::NH : 1;
+        constexpr int SHARE_HI = RG * QRLO * 1024, SHARE_SLO = SHARE_HI + (TWO ? RG * QRHI * 1024 : 0), SHARE_SHI = SHARE_SLO + RG * 256;
+        static_assert(!SHARE_Q || (C::NH == 2 && SHARE_SHI + RG * 256 <= C::VBYTES), "query operands of a workgroup in one V buffer");
+        const unsigned share = lds0 + OFF_V + C::VBYTES;
+        if constexpr (SHARE_Q) {
+            const int h = kh & 1, ln = fresh(lane);
+            v4i raw[4];
+            const rsrc_t qmat = make_rsrc(qhead, (uint32_t)S * (D * 2));
+            const unsigned off = (unsigned)(qrow + (ln & 31)) * (D * 2) + 64 * (ln >> 5) + 128 * h;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) raw[t] = buffer_load16(qmat, off + 16 * t);
+            load_k(0);
+            load_v(0);
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned at = pin(share + ln * 16), sc = pin(share + SHARE_SLO + (rg * 64 + ln) * 4 + h);
+            if (kh < 2) {
+                v4i r[NL];
+                const int code = make_q_block<LO, false>(r, raw, c, 1.f);
+#pragma unroll
+                for (int i = 0; i < NL; ++i) lds_write<v4i>(at + (rg * QRLO + h * NL + i) * 1024, r[i]);
+                if constexpr (!uses_bf16_mfma(LO)) lds_write<uint8_t>(sc, (uint8_t)code);
+            } else if constexpr (TWO) {
+                v4i r[NHI];
+                const int code = make_q_block<HI, false>(r, raw, c, 1.f);
+#pragma unroll
+                for (int i = 0; i < NHI; ++i) lds_write<v4i>(at + SHARE_HI + (rg * QRHI + h * NHI + i) * 1024, r[i]);
+                if constexpr (!uses_bf16_mfma(HI)) lds_write<uint8_t>(sc + (SHARE_SHI - SHARE_SLO), (uint8_t)code);
+            }
+        } else {
             v4i qraw[C::NKK];
             load_q_raw<C>(qraw, make_rsrc(qhead, (uint32_t)S * (D * 2)), qrow, fresh(lane) & 31, fresh(lane) >> 5);
             load_k(0);
@@ -182,6 +216,18 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
         load_k(1 < nt ? 1 : N);
         load_v(1 < nt ? 1 : N);
         __syncthreads();
+        if constexpr (SHARE_Q) {
+            const int ln = fresh(lane);
+            const unsigned at = pin(share + ln * 16), sc = pin(share + SHARE_SLO + (rg * 64 + ln) * 4);
+#pragma unroll
+            for (int i = 0; i < QRLO; ++i) qr_lo[i] = lds_read<v4i>(at + (rg * QRLO + i) * 1024);
+            if constexpr (!uses_bf16_mfma(LO)) qs_lo = lds_read<int>(sc);
+            if constexpr (TWO) {
+#pragma unroll
+                for (int i = 0; i < QRHI; ++i) qr_hi[i] = lds_read<v4i>(at + SHARE_HI + (rg * QRHI + i) * 1024);
+                if constexpr (!uses_bf16_mfma(HI)) qs_hi = lds_read<int>(sc + (SHARE_SHI - SHARE_SLO));
+            }
+        }
 
         // ---- tile loop.  MAIN: a main tile followed by another one, so that nothing of the step depends on jt.
         auto step = [&](int jt, auto MAIN) __attribute__((always_inline)) {
@@ -212,11 +258,15 @@ dma_attn_split_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict
 #pragma unroll
             for (int i = 1; i < KS; ++i) other[i - 1] = lds_read<float>(maxima + (mx_slot ^ (i * RG * 128)));
             if (main || jt + 1 < nt) stage_v<C>(vreg, v_at(buf ^ 1), lofs.stage_v);
-            load_v(ahead);
+            if (D == 64) load_v(ahead);               // 16 / 8 heads S = 1500 19.1 us, behind the rescale 19.25
 #pragma unroll
             for (int i = 1; i < KS; ++i) mx = fmaxf(mx, other[i - 1]);
             float alpha;
             move_max<C>(s, o, mx, m, mfloor, alpha);
+            if (D != 64) {
+                hold(vreg);
+                load_v(ahead);
+            }
             l = l * alpha + probabilities<C>(s, pb);
             value_part<C>(v_at(buf) + key0 * C::VS, lofs.value_v, o, pb);
         };
