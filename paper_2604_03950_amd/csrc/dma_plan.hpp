@@ -143,6 +143,9 @@ inline Load dealt_load(const AttnArgs& a, int rows, int heads_item, int64_t cus,
 // split of each: D = 128 (2764 problems) 0.05 % on average, 10 % at worst; D = 64 (6865) 0.12 %, 12 %; by the ratios of the table,
 // with two workgroups per CU at D = 64, 0.15 %, 16 % and 1.0 %, 22 %.  Unquantized problems at D = 128 lose more, not less, by
 // ratios of their own.
+// (Since four waves share the making of the query operands an item of theirs costs less: on 154 default-format problems at D = 128,
+// 4 to 40 heads, batches of 1 to 8 and S = 140 to 9000, the choice is 0.17 % from the best split on average and 13 % at worst, with
+// 1.9 per item 0.09 % and 7 %.)
 constexpr float CROWD = 0.3f;
 inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident2, int resident4)
 {
