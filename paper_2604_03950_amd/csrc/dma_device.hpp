@@ -248,8 +248,10 @@ DMA_DEV v4i quant_dequant8(const float (&x)[8], int code)
 // quant_dequant8 from packed bf16 (no pre-scale), a dword (two elements) at a time, without a detour through binary32 and
 // without a clamp: between saturate_converts<true>() and <false>() (MODE.FP16_OVFL) the converts to 8-bit elements give the
 // largest finite element for everything that rounds above it, infinities included, as a clamp of the operand does; NaN stays NaN.
-// The mode holds for these converts only, because the matrix instructions lose NaN and infinities in it: they are volatile
-// statements, which keep their order, and nothing else in between depends on the mode.
+// The mode ends with these converts, because the matrix instructions lose NaN and infinities in it: the converts are volatile
+// statements, which keep their order, and the scheduling barriers keep matrix instructions out.  Other vector instructions may
+// move in: integer ones, and converts of the way back (dequant2_bf16), which give the same in either mode (every E5M2 code at
+// 2^113, the largest scale of keys, and every E4M3 code at 2^120: overflow to infinity both ways).
 template <bool ON>
 DMA_DEV void saturate_converts()
 {
@@ -276,7 +278,7 @@ DMA_DEV int dequant2_bf16(int q, float sc)
     else return __builtin_bit_cast(int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8((unsigned)q, sc, false));
 }
 // The scale of the way back: E4M3 has no infinity, so a block that holds one comes back as NaN, like one that holds a NaN.
-// (E5M2: 57344 x 2^113 is the infinity again.)
+// (E5M2: 57344 x 2^113 is the infinity again, in either mode.)
 template <int FMT>
 DMA_DEV float mx8_scale_back(unsigned amax_bits, float sc) { return FMT == FMT_E5M2_X || amax_bits < 0x7f80u ? sc : __int_as_float(0x7fc00000); }
 
