@@ -130,22 +130,22 @@ inline Load dealt_load(const AttnArgs& a, int rows, int heads_item, int64_t cus,
 // a step does not get shorter in proportion, because every step still quantizes and stages a whole key tile: so the split
 // pays exactly where the chip would otherwise wait for the longest list of items.  us per step of the unsplit, 2-way and
 // 4-way kernel where nothing else limits it (4 heads, S = 900 to 3700):
-//   D = 128  MXFP4 tiles 2.40, 1.72, 1.27; all MXFP8 2.94, 2.14, 1.60; unquantized 2.85, 1.89, 1.32; with the Step-2 scale
-//            MXFP4 3.27, 2.39, 1.91, MXFP8 3.81, 2.82, 2.23
-//   D = 64   MXFP4 tiles 0.83, 0.59; all MXFP8 0.96, 0.71; unquantized 0.84, 0.61; Step-2 scale 1.23, 0.90
+//   D = 128  MXFP4 tiles 2.41, 1.76, 1.23; all MXFP8 2.96, 2.22, 1.59; unquantized 2.90, 2.01, 1.35; with the Step-2 scale
+//            MXFP4 3.08, 2.22, 1.77, MXFP8 3.59, 2.67, 2.09
+//   D = 64   MXFP4 tiles 0.83, 0.63; all MXFP8 0.94, 0.72; unquantized 0.85, 0.66; Step-2 scale 1.19, 0.87, MXFP8 1.35, 1.02
 // A CU holds one workgroup at D = 128 and three or four at D = 64 (the occupancy that the launch uses): there a step
-// takes longer the more of them share the CU, by CROWD of the work of the others.  us with 1 / 2 / 4 waves: 4 / 1 heads S = 3700
-// 80 / 57 / 44; 8 / 2 heads S = 7400 155 / 119 / 163, S = 10500 219 / 230 / 310; 16 / 8 heads S = 3700 82 / 66 / 97, S = 5200
-// 115 / 127 / 176; 32 / 8 heads S = 640 21 / 18.3 / 18.7, S = 1800 47.5 / 43.9 / 64.8, S = 2600 65 / 79 / 110; all MXFP8, 32 / 8 heads,
-// S = 2048 58 / 54 / 79, S = 3000 88 / 111 / 151.
-// The costs below are the ones whose choice loses least on problems timed with every split (default, all MXFP8, all MXFP4 and
-// unquantized, with and without the per-token scale and the mask; 2 to 500 heads over the batch, S up to 8200).  From the best
-// split of each: D = 128 (2764 problems) 0.05 % on average, 10 % at worst; D = 64 (6865) 0.12 %, 12 %; by the ratios of the table,
-// with two workgroups per CU at D = 64, 0.15 %, 16 % and 1.0 %, 22 %.  Unquantized problems at D = 128 lose more, not less, by
-// ratios of their own.
-// (Since four waves share the making of the query operands an item of theirs costs less: on 154 default-format problems at D = 128,
-// 4 to 40 heads, batches of 1 to 8 and S = 140 to 9000, the choice is 0.17 % from the best split on average and 13 % at worst, with
-// 1.9 per item 0.09 % and 7 %.)
+// takes longer the more of them share the CU, by CROWD of the work of the others.  us with 1 / 2 / 4 waves, D = 128: 4 / 1 heads
+// S = 3700 78 / 57 / 41; 8 / 2 heads S = 7400 150 / 115 / 153, S = 10500 218 / 229 / 285; 16 / 8 heads S = 3700 79 / 64 / 87, S = 5200
+// 114 / 125 / 157; 32 / 8 heads S = 640 20.3 / 17.8 / 15.5, S = 1800 45.2 / 41.5 / 55.7, S = 2600 62 / 77 / 94; all MXFP8, 32 / 8 heads,
+// S = 2048 58 / 52 / 69, S = 3000 87 / 108 / 134.
+// The costs below were fitted on problems timed with every split (2764 at D = 128, 6865 at D = 64; default, all MXFP8, all MXFP4 and
+// unquantized, with and without the per-token scale and the mask; 2 to 500 heads over the batch, S up to 8200) on kernels whose
+// waves each made their own query operands, as the ones whose choice loses least: less than by the ratios of the table, and
+// unquantized problems at D = 128 lose more by ratios of their own.  On the present kernels (2 to 320 heads over the batch, S from a
+// little over a tile to 9000, every pair of formats, of more than 9 us) the choice is from the best split of each, on average and
+// at worst: D = 128 2486 problems 0.20 %, 13.7 % (one quantized format 0.29 %, 13.7 %; two 0.18 %, 10.8 %; unquantized 0.25 %, 10.5 %;
+// Step-2 scale 0.06 %, 5.7 %); D = 64 985 problems 0.07 %, 8.4 %.  With 2.05 steps for every item of four waves, as it was fitted, the
+// 873 of one quantized format at D = 128 lose 0.66 %, 21 %.
 constexpr float CROWD = 0.3f;
 inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident2, int resident4)
 {
@@ -169,7 +169,12 @@ inline int key_split(const AttnArgs& a, int64_t cus, int resident1, int resident
         return 0.5f + cost(a.tile, 1, resident2, step, 2.f * step) < whole ? 2 : 1;
     }
     const float two = cost(a.tile, 1, resident2, 0.70f, 2.2f);
-    const float four = cost(a.tile / 2, 1, resident4, 0.51f, 2.05f);
+    // One quantized format without the Step-2 scale: the four waves of an item share the making of its query operands.  On 70
+    // problems between the two costs four waves take 0.91 of the time of two, 0.95 on the native FP8 MFMA (0.75 to 0.99; 1.01 to 1.08
+    // on three of 5 heads with S = 7300).  Sharing them in two formats, four waves take 0.84 to 1.07 there, 0.99 on average (32 / 8
+    // heads S = 822 20.5 us, two waves 20.1).  Where they are not shared: 40 / 8 heads S = 400 unquantized 15.3, 14.6, per token 18.8, 18.0.
+    const bool shared = a.lo_fmt == a.hi_fmt && a.lo_fmt != 0 && !a.per_token;
+    const float four = cost(a.tile / 2, 1, resident4, 0.51f, shared ? 1.9f : 2.05f);
     return four < two ? (four < whole ? 4 : 1) : two < whole ? 2 : 1;
 }
 

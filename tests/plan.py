@@ -13,7 +13,7 @@ SHIM = r"""
 static dma::AttnArgs args(const int* p)
 {
     dma::AttnArgs a = {};
-    a.B = p[0]; a.Hq = p[1]; a.Hkv = p[2]; a.S = p[3]; a.D = p[4]; a.tile = p[4]; a.causal = p[5]; a.lo_fmt = p[6]; a.per_token = p[7];
+    a.B = p[0]; a.Hq = p[1]; a.Hkv = p[2]; a.S = p[3]; a.D = p[4]; a.tile = p[4]; a.causal = p[5]; a.lo_fmt = p[6]; a.per_token = p[7]; a.hi_fmt = p[8];
     return a;
 }
 extern "C" void dealt_load(const int* p, int rows, int heads_item, int cus, int resident, float step, float item, float* out)
@@ -39,8 +39,8 @@ def library():
 
 
 def problem(B, Hq, Hkv, S, D=128, causal=True, lo=2, per_token=False):
-    """lo: product-path id of the low format (dma_device.hpp)."""
-    return (ctypes.c_int * 8)(B, Hq, Hkv, S, D, int(causal), lo, int(per_token))
+    """lo: product-path id of the low format (dma_device.hpp); the high one is 3 (key_split: its own)."""
+    return (ctypes.c_int * 9)(B, Hq, Hkv, S, D, int(causal), lo, int(per_token), 3)
 
 
 def dealt_load(p, rows, heads_item, cus, resident, step, item):
@@ -62,6 +62,7 @@ def resident(D, lo, hi, per_token=False):
 
 def key_split(p, hi=3, cus=256):
     """Waves that share 32 query rows: 1, 2 or 4."""
+    p[8] = hi
     return library().key_split(p, cus, (ctypes.c_int * 3)(*resident(p[4], p[6], hi, bool(p[7]))))
 
 

@@ -75,9 +75,16 @@ def test_split_at_the_occupancy_of_the_launch(B, Hq, Hkv, S, causal, lo, hi, spl
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,lo,hi,split", [
-    (1, 40, 8, 400, 128, 2, 2, 2),           # us with two waves and four: 13.7, 15.9
-    (1, 40, 8, 400, 128, 3, 3, 2),           # 15.8, 17.3
-    (1, 32, 8, 822, 128, 2, 2, 2),           # 19.3, 21.5
+    (1, 40, 8, 400, 128, 2, 2, 4),           # us with two waves and four: 15.1, 13.5
+    (1, 40, 8, 400, 128, 3, 3, 4),           # 17.0, 14.0
+    (1, 40, 8, 400, 128, 4, 4, 4),           # 17.0, 14.1
+    (1, 40, 8, 400, 128, 1, 1, 4),           # 15.9, 13.8
+    (1, 40, 8, 400, 128, 0, 0, 2),           # 14.6, 15.3: no query operands to make
+    (1, 32, 8, 822, 128, 2, 2, 4),           # 18.6, 17.1
+    (1, 32, 8, 822, 128, 2, 3, 2),           # 20.1, 20.5
+    (3, 8, 2, 1199, 128, 3, 3, 4),           # 27.3, 24.7
+    (3, 8, 2, 1199, 128, 2, 3, 2),           # 25.5, 26.0
+    (1, 8, 1, 4387, 128, 3, 3, 4),           # 0.93 of the time with two
     (1, 32, 8, 1800, 64, 0, 0, 2),           # two waves and unsplit: 28.0, 31.6
     (45, 5, 1, 298, 64, 2, 2, 1),            # 13.8, 11.9: more than two items per compute unit
     (16, 16, 16, 292, 64, 2, 2, 1),          # 14.7, 12.4
@@ -88,6 +95,16 @@ def test_split_at_the_occupancy_of_the_launch(B, Hq, Hkv, S, causal, lo, hi, spl
 def test_split_costs(B, Hq, Hkv, S, D, lo, hi, split):
     """Problems close to where the choice turns, as timed."""
     assert plan.key_split(plan.problem(B, Hq, Hkv, S, D, lo=lo), hi) == split
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,lo,hi", [
+    (1, 40, 8, 400, 3, 3),                   # us with two waves and four: 17.6, 18.1
+    (1, 32, 8, 822, 3, 3),                   # 25.3, 25.9
+    (1, 32, 8, 822, 2, 3),                   # 24.0, 26.5
+])
+def test_split_costs_with_the_step_2_scale(B, Hq, Hkv, S, lo, hi):
+    """Its query operands are made by every wave for itself: an item of four waves costs what it did."""
+    assert plan.key_split(plan.problem(B, Hq, Hkv, S, 128, True, lo, True), hi) == 2
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,S,D,item", [
