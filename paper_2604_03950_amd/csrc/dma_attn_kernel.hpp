@@ -19,7 +19,7 @@
 // so the row maximum / sum need one cross-half exchange and the running state (m, l) is per lane.
 //
 // Pipeline.  While tile jt is computed out of LDS buffer jt & 1, tile jt+1 goes from registers into buffer (jt+1) & 1, K
-// quantized on the way (a thread has whole MX blocks: maximum, E8M0 scale, hardware scaled converts) at the top of the
+// quantized on the way (a thread has whole MX blocks, or half of one beside its neighbour: maximum, E8M0 scale, hardware scaled converts) at the top of the
 // step and V behind the softmax, and each is requested for tile jt+2 (16 B per lane, coalesced) once its registers are
 // free: one barrier per tile.
 // Two waves per SIMD (the register budget allows no more): the matrix work of one overlaps the vector
@@ -79,7 +79,7 @@ struct Cfg {
     // A thread's chunks of a K tile are KR runs of KG consecutive ones (half an MX block or a whole one, as many as it has): the
     // block maximum stays in the thread (or a pair), a block has one scale computation and its codes leave in one store.  With
     // chunks of four different rows per thread and the maximum over a quad of lanes a D = 128 main step had 309 vector and 88 LDS
-    // instructions, now 289 and 82, and the loads, which then touch 64-byte segments per lane instead of whole rows per 16 lanes,
+    // instructions, now 286 and 82, and the loads, which then touch 64-byte segments per lane instead of whole rows per 16 lanes,
     // are no slower.  (us, same box, before and after) 32 / 32 heads S = 8192 410.7 -> 404.5, 32 / 8 S = 32768 5814 -> 5682,
     // 4 / 1 S = 8192 96.8 -> 93.5, 32 / 8 S = 4096 with the tensor scale 153.1 -> 147.9, S = 8192 per token 537 -> 515.  Runs of two
     // chunks throughout: 32 / 32 S = 8192 0.8 % slower, the tensor scale 3 %.
@@ -238,9 +238,9 @@ DMA_DEV v4s lds_read_tr16(unsigned addr) { return __builtin_amdgcn_ds_read_tr16_
 DMA_DEV v2i lds_read_tr8(unsigned addr) { return __builtin_amdgcn_ds_read_tr8_b64_v2i32((DMA_LDS v2i*)(uintptr_t)addr); }
 
 // Keeps registers that an LDS write has just taken as its data from being used for something else up to here: a vector
-// instruction that writes one of them waits until the queued LDS write has read it.  In the split kernel the allocator used the
-// V registers for the row maximum right behind the V staging: 4 / 1 heads S = 8192 93.5 us, with hold() 85.9; 8 / 2 S = 4000
-// 53.5, 49.4.
+// instruction that writes one of them waits until the queued LDS write has read it.  In the split kernel with shared query operands
+// the allocator used the V registers for the row maximum right behind the V staging: 4 / 1 heads S = 8192 93.5 us, with hold() 85.9;
+// 8 / 2 S = 4000 53.5, 49.4.  (Before the operands were shared 89.4 and 52.2: sharing alone made long sequences slower.)
 template <typename T, int N>
 DMA_DEV void hold(const T (&reg)[N])
 {
@@ -362,7 +362,7 @@ DMA_DEV void load_tile_vmx(v4i (&reg)[C::CPT], const uint16_t* __restrict__ mat,
 }
 
 // Largest magnitude among the thread's run of KG chunks, and of the MX block it belongs to (KG = 2: the block's other half is
-// the neighbouring lane's), as 15-bit patterns (see amax8_bf16_bits).
+// the neighbouring lane's), as 15-bit patterns (see amax8_bf16_packed).
 template <typename C, int KG, int KR>
 DMA_DEV void block_max_bits(unsigned (&am)[KR], const v4i (&reg)[C::CPT])
 {
